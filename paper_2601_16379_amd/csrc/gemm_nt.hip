@@ -1,33 +1,46 @@
-// Complex "NT" GEMM on CDNA4 matrix cores for the three large contractions
-// of the path (V^q of eq. (7), U^q = R^q W^q and the fragment contraction of
-// eq. (19)):
+// FP64 complex "NT" GEMM on CDNA4 matrix cores for the large contractions of
+// the path (V^q of eq. (7), U^q = R^q W^q and the fragment contraction of
+// eq. (19), the factorisation updates and the two-sided solve of eq. (8)):
 //
 //   C[m][n] (+)= sum_{s < nseg} sum_{k} opA(A_s[m][k]) * opB(B_s[n][k])
 //
-// Both operands are k-contiguous rows (no transposes anywhere), stored in the
-// format of the precision:
-//   FP64    complex128 interleaved rows; v_mfma_f64_16x16x4;
-//   FP32    two float planes (re, im), rows zero-padded to a multiple of 8;
-//           v_mfma_f32_16x16x4.
-// (bf16x3 operands use the kernel of gemm_x3.hip.)  A lane-local permutation
-// of k (lane l of an MFMA step s takes k = K_l + s with K_l = (l/16) * steps)
-// lets every lane read its operand fragment with 16-byte LDS loads; A and B
-// use the same permutation, so the sum over k is unchanged.  In FP32 each K
-// segment (one q, or one block of grid points) accumulates in FP32 and is
-// added into FP64 registers, so sums over q are FP64.
+// Both operands are complex128 interleaved, k-contiguous rows (no transposes
+// anywhere); v_mfma_f64_16x16x4.  (The mixed formats have their own kernels in
+// gemm_big.hip and gemm_x3.hip.)  K advances in stages of 16: MFMA step s
+// of a stage takes k = 4 (l/16) + s from lane l, the same for A and B.
 //
-// Workgroup: 256 threads, 64x64 output tile, four waves in 2x2, each wave
-// 2x2 MFMA tiles of 16x16; persistent over a global tile list that
-// concatenates descriptors (batches over q, or fragments of different sizes).
+// Bound: the FP64 matrix cores (64 cycles a 16x16x4 MFMA), in practice the
+// power they draw: with the cores busy 0.84 of the cycles the clock falls
+// from 2.4 to 2.0-2.25 GHz.  A workgroup of 256 threads takes a 64 x 64 tile
+// (four waves of 2 x 2 blocks of 16 x 16), two workgroups a CU.  A stage of
+// both operands (2 x 16 KB) is copied from global memory straight into LDS
+// (global_load_lds_dwordx4) one stage ahead, one barrier a stage; the
+// fragments of MFMA step s + 1 are read from LDS under the MFMAs of step s.
+// In LDS a row keeps its 16 values in an order XOR-permuted by the row, so the
+// fragment reads (16 rows x 4 k) fall on distinct banks.  Measured on the
+// tiles' own flops (random operands): 62.8 TFLOP/s for V^q products of 640 x
+// 640 x 32768, 66.6 for 1024^3 products, 64.7 for U^q (3765 x 520 x 520),
+// against 40, 49 and 49 with operands staged through registers, two barriers a
+// stage; a vendor GEMM reaches 72-74.  A 128 x 128 tile of eight waves was
+// 5 % faster on 1024^3 but loses more to the edges of 520 or 1040 rows.
+//
+// Tile size: products of few tiles take 32 x 32 tiles (one block of 16 x 16 a
+// wave, four or five workgroups a CU) so that every CU has work; the MFMAs of
+// an output element and their order are the same in both, so the results are
+// too, bit for bit.  Tiles with at most 32 (16) valid rows or columns are
+// dealt to the four waves as strips.
 #include "kernels.hpp"
 
 namespace {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) void glb_void;
 
-constexpr int TM = 64, TN = 64;
+constexpr int MT = 64;            // edge of the tiles that the tile list counts
+constexpr int BK = 16;            // k per stage
+constexpr int ROW_B = BK * 16;    // bytes of one row of one stage
 
 __device__ inline int isqrt_floor(long long x) {
   long long r = (long long)sqrt((double)x);
@@ -36,95 +49,207 @@ __device__ inline int isqrt_floor(long long x) {
   return (int)r;
 }
 
-template <int P> struct NtCfg;
-// FP64: BK = 16, LDS planes re/im of doubles, row pitch 18 (16 + 2 pad)
-template <> struct NtCfg<0> { static constexpr int BK = 16, PITCH = 18, PLANES = 2; typedef double T; };
-// FP32: BK = 32, planes re/im of floats, pitch 36
-template <> struct NtCfg<1> { static constexpr int BK = 32, PITCH = 36, PLANES = 2; typedef float T; };
+// Values at or past the end of the K segment are copied from here.
+__device__ __attribute__((aligned(16))) double kZeroC[2];
 
-// Stage one operand tile (64 rows x BK) from global memory into registers.
-// Returns per-thread vectors; rows >= nrows or k >= kcur read as zero.
-template <int P, bool CONJ>
-__device__ inline void load_tile(const void* base, long long ld, long long plane, int row0, int nrows,
-                                 int k0, int kcur, u4 (&r)[4]) {
-  const int tid = threadIdx.x;
+__device__ inline double flip(double x, unsigned long long sign) {
+  return __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, x) ^ sign);
+}
+
+// Position of a K stage: segment and first k of it.
+struct KPos {
+  int seg, k0;
+};
+
+// Sources of this lane's copies of one operand: a wave-instruction copies 4
+// rows x 256 bytes; lane l copies value kk of row l/16 to position l%16.
+template <int T>
+struct Src {
+  const cplx* p[T / 16];
+  int kk[T / 16];
+};
+
+template <int T>
+__device__ inline void make_src(Src<T>& s, const cplx* base, long long ld, int row0, int nrows, int wave, int lane) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int v = tid + 256 * i;
-    u4 x = u4{0, 0, 0, 0};
-    if constexpr (P == 0) {
-      // 64 rows x 16 complex: v -> row v/16, k v%16 (one complex per vector)
-      const int row = v >> 4, k = v & 15;
-      if (row0 + row < nrows && k0 + k < kcur) {
-        const cplx* p = (const cplx*)base + (long long)(row0 + row) * ld + k0 + k;
-        x = *(const u4*)p;
-        if (CONJ) {
-          double im = -__builtin_bit_cast(double, (unsigned long long)x.z | ((unsigned long long)x.w << 32));
-          unsigned long long b = __builtin_bit_cast(unsigned long long, im);
-          x.z = (unsigned int)b;
-          x.w = (unsigned int)(b >> 32);
-        }
-      }
-    } else {
-      // 2 planes x 64 rows x 8 chunks of 4 floats: v -> plane v/512, row, chunk
-      const int pl = v >> 9, row = (v >> 3) & 63, c = v & 7;
-      if (row0 + row < nrows && k0 + 4 * c < kcur) {
-        const float* p = (const float*)base + pl * plane + (long long)(row0 + row) * ld + k0 + 4 * c;
-        x = *(const u4*)p;
-        if (CONJ && pl == 1) x = u4{x.x ^ 0x80000000u, x.y ^ 0x80000000u, x.z ^ 0x80000000u, x.w ^ 0x80000000u};
-      }
-    }
-    r[i] = x;
+  for (int j = 0; j < T / 16; ++j) {
+    const int row = (wave + 4 * j) * 4 + (lane >> 4);
+    s.kk[j] = (lane & 15) ^ (row & 15);
+    // rows past the end repeat the last one (their outputs are not stored)
+    s.p[j] = base + (long long)min(row0 + row, nrows - 1) * ld + s.kk[j];
   }
 }
 
-template <int P>
-__device__ inline void store_tile(typename NtCfg<P>::T* s, const u4 (&r)[4]) {
-  constexpr int PITCH = NtCfg<P>::PITCH;
-  const int tid = threadIdx.x;
+template <int T>
+__device__ inline void stage_copy(const Src<T>& s, long long off, int k0, int kcur, char* dst, int wave) {
+  const bool tail = k0 + BK > kcur;      // the same for the whole workgroup
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int v = tid + 256 * i;
-    if constexpr (P == 0) {
-      const int row = v >> 4, k = v & 15;
-      double* sd = (double*)s;
-      sd[(0 * 64 + row) * PITCH + k] =
-          __builtin_bit_cast(double, (unsigned long long)r[i].x | ((unsigned long long)r[i].y << 32));
-      sd[(1 * 64 + row) * PITCH + k] =
-          __builtin_bit_cast(double, (unsigned long long)r[i].z | ((unsigned long long)r[i].w << 32));
-    } else {
-      const int pl = v >> 9, row = (v >> 3) & 63, c = v & 7;
-      *(u4*)((float*)s + (pl * 64 + row) * PITCH + 4 * c) = r[i];
+  for (int j = 0; j < T / 16; ++j) {
+    const cplx* g = s.p[j] + off;
+    if (tail && k0 + s.kk[j] >= kcur) g = (const cplx*)kZeroC;
+    __builtin_amdgcn_global_load_lds((glb_void*)g, (lds_void*)(dst + (wave + 4 * j) * 4 * ROW_B), 16, 0, 0);
+  }
+}
+
+// The K loop over segments [s0, s1) and the epilogue of one tile: this wave
+// computes NI x NJ blocks of 16 x 16 at rows rb, columns cb of the T x T tile
+// (idle: it only helps with the copies).  part: the block goes there (T x T,
+// row-major) instead of into C; first: the first chunk of the K range.
+template <int T, int NI, int NJ>
+__device__ inline void tile_body(const NtDesc& d, const Src<T>& sa, const Src<T>& sb, int s0, int s1, int m0, int n0,
+                                 int rb, int cb, bool idle, bool mirror, cplx* Cb, cplx* part, bool first,
+                                 unsigned long long sx, unsigned long long sy, unsigned long long sz, char* smem,
+                                 int wave, int lane) {
+  constexpr int SA = T * ROW_B, STAGE = 2 * SA;
+  const int lr = lane & 15, lk = lane >> 4;
+  d4 re[NI][NJ], im[NI][NJ];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      re[i][j] = d4{0, 0, 0, 0};
+      im[i][j] = d4{0, 0, 0, 0};
+    }
+  const int sw = ((4 * lk) ^ lr) << 4;
+  const int aoff = (rb + lr) * ROW_B + sw, boff = SA + (cb + lr) * ROW_B + sw;
+  auto kcur_of = [&](int seg) { return seg == d.nseg - 1 ? d.Klast : d.Kseg; };
+  auto copy = [&](const KPos& p, char* buf) {
+    const int kcur = kcur_of(p.seg);
+    stage_copy<T>(sa, (long long)p.seg * d.sA_seg + p.k0, p.k0, kcur, buf, wave);
+    stage_copy<T>(sb, (long long)p.seg * d.sB_seg + p.k0, p.k0, kcur, buf + SA, wave);
+  };
+  auto rd = [&](const char* buf, int q, d2 (&a)[NI], d2 (&b)[NJ]) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) a[i] = *(const d2*)(buf + ((aoff ^ (q << 4)) + i * 16 * ROW_B));
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) b[j] = *(const d2*)(buf + ((boff ^ (q << 4)) + j * 16 * ROW_B));
+  };
+  // re += a_r b_r - a_i b_i, im += a_r b_i + a_i b_r, the signs of the
+  // conjugations on a copy of A's components
+  auto mm = [&](const d2 (&a)[NI], const d2 (&b)[NJ]) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, re[i][j], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const double x = flip(a[i].x, sx);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, b[j].y, im[i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const double x = flip(a[i].y, sy);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, b[j].y, re[i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const double x = flip(a[i].y, sz);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, b[j].x, im[i][j], 0, 0, 0);
+    }
+  };
+  // the stage after p (seg = s1: none)
+  auto next = [&](KPos p) {
+    p.k0 += BK;
+    if (p.k0 >= kcur_of(p.seg)) {
+      ++p.seg;
+      p.k0 = 0;
+    }
+    return p;
+  };
+  KPos nx{s0, 0};                        // the stage to copy next
+  __syncthreads();                       // LDS of the previous tile no longer read
+  copy(nx, smem);
+  nx = next(nx);
+  int par = 0;
+  for (bool more = true; more; par ^= 1) {
+    const char* buf = smem + par * STAGE;
+    // this stage's copies have landed; after the barrier everyone's have, and
+    // every wave has read the previous stage, whose buffer takes the next
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    more = nx.seg < s1;
+    d2 a0[NI], b0[NJ], a1[NI], b1[NJ];
+    rd(buf, 0, a0, b0);
+    if (more) {
+      copy(nx, smem + (par ^ 1) * STAGE);
+      nx = next(nx);
+    }
+    rd(buf, 1, a1, b1);
+    if (!idle) {
+      __builtin_amdgcn_sched_barrier(0);
+      mm(a0, b0);
+      __builtin_amdgcn_sched_barrier(0);
+      rd(buf, 2, a0, b0);
+      __builtin_amdgcn_sched_barrier(0);
+      mm(a1, b1);
+      __builtin_amdgcn_sched_barrier(0);
+      rd(buf, 3, a1, b1);
+      __builtin_amdgcn_sched_barrier(0);
+      mm(a0, b0);
+      mm(a1, b1);
     }
   }
+  if (idle) return;
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int ml = rb + i * 16 + 4 * v + lk, nl = cb + j * 16 + lr;
+        const int m = m0 + ml, n = n0 + nl;
+        if (m >= d.M || n >= d.N) continue;
+        cplx val = cmk(re[i][j][v], im[i][j][v]);
+        if (part) {
+          part[ml * T + nl] = val;
+          continue;
+        }
+        const long long o = (long long)m * d.ldc + n;
+        if (d.epi == 4) val = csub(Cb[o], val);
+        else if (d.epi == 1 && !first) val = cadd(Cb[o], val);
+        Cb[o] = val;
+        if (mirror) Cb[(long long)n * d.ldc + m] = cconj(val);
+      }
 }
 
 // KIND only names the call site in profiles (0 generic, 1 V^q, 2 U^q,
-// 3 fragment contraction); the code is the same.
-template <int P, bool A_CONJ, bool B_CONJ, int KIND>
-__global__ __launch_bounds__(256, 2) void zgemm_nt_kernel(const NtDesc* __restrict__ descs, int ndesc,
-                                                       long long total_tiles) {
-  typedef typename NtCfg<P>::T T;
-  constexpr int BK = NtCfg<P>::BK, PITCH = NtCfg<P>::PITCH, PLANES = NtCfg<P>::PLANES;
-  __shared__ __attribute__((aligned(16))) T sA[PLANES * 64 * PITCH];
-  __shared__ __attribute__((aligned(16))) T sB[PLANES * 64 * PITCH];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int lr = lane & 15;     // row / column within a 16x16 MFMA tile
-  const int lk = lane >> 4;     // k group of the lane
+// 3 fragment contraction); the code is the same.  Units: the tiles
+// [t0, t0 + nt) of the tile list (64 x 64 each; T = 32: four units a tile).
+// With nch > 1 the K segments run in nch chunks of d.cseg segments, the
+// chunks added one after the other: by the workgroup of the tile (C is
+// stored by the first chunk, added to by the later ones), or, with part, by a
+// unit of its own each, which leaves its partial block in part for
+// nt_fold_kernel.
+template <int T, int KIND>
+__global__ __launch_bounds__(256, T == 64 ? 2 : 4) void zgemm_nt_kernel(const NtDesc* __restrict__ descs, int ndesc,
+                                                                        long long t0, long long nt, int nch,
+                                                                        cplx* part, int conj) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];   // two stages of (A, B)
+  constexpr int SUB = (MT / T) * (MT / T);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr unsigned long long NEG = 0x8000000000000000ull;
+  const bool ca = conj & 1, cb_ = (conj & 2) != 0;
+  const unsigned long long sx = cb_ ? NEG : 0, sy = ca == cb_ ? NEG : 0, sz = ca ? NEG : 0;
 
   // XCD-aware order: workgroups are dispatched round-robin over the 8 XCDs,
-  // so iteration `it` of workgroup b maps to a tile such that each XCD walks
-  // a contiguous range of the tile list (tiles that share operand rows then
+  // so iteration `it` of workgroup b maps to a unit such that each XCD walks
+  // a contiguous range of the units (tiles that share operand rows then
   // share that XCD's L2).  gridDim.x is a multiple of 8.
-  const long long t8 = (total_tiles + 7) / 8 * 8;
-  const long long per = t8 / 8;
-  for (long long it = blockIdx.x; it < t8; it += gridDim.x) {
-    const long long t = (it % 8) * per + it / 8;
-    if (t >= total_tiles) continue;
+  const long long units = nt * SUB * (part ? nch : 1);
+  const long long u8 = (units + 7) / 8 * 8;
+  const long long per = u8 / 8;
+  for (long long it = blockIdx.x; it < u8; it += gridDim.x) {
+    const long long u = (it % 8) * per + it / 8;
+    if (u >= units) continue;
+    const int ch = part ? (int)(u / (nt * SUB)) : 0;
+    const long long ut = u - (long long)ch * nt * SUB;
+    const long long t = t0 + ut / SUB;
+    const int sub = (int)(ut % SUB);
     int lo = 0, hi = ndesc - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -142,192 +267,52 @@ __global__ __launch_bounds__(256, 2) void zgemm_nt_kernel(const NtDesc* __restri
       tm = lt / d.tiles_n;
       tn = lt - tm * d.tiles_n;
     }
-    const int m0 = tm * TM, n0 = tn * TN;
-    const size_t esz = (P == 0) ? sizeof(cplx) : sizeof(float);
-    const char* Ab = (const char*)d.A + (long long)b * d.sA_bat * esz;
-    const char* Bb = (const char*)d.B + (long long)b * d.sB_bat * esz;
-
-    d4 acc_re[2][2], acc_im[2][2];
-    f4 c_re[2][2], c_im[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        acc_re[i][j] = d4{0, 0, 0, 0};
-        acc_im[i][j] = d4{0, 0, 0, 0};
-        c_re[i][j] = f4{0, 0, 0, 0};
-        c_im[i][j] = f4{0, 0, 0, 0};
+    const int m0 = tm * MT + (T == 32 ? 32 * (sub >> 1) : 0), n0 = tn * MT + (T == 32 ? 32 * (sub & 1) : 0);
+    if (m0 >= d.M || n0 >= d.N) continue;            // a quarter outside the matrix
+    // entries above the diagonal of a 64 x 64 diagonal tile: computed where
+    // the matrix is wanted whole (herm 1: the other tiles are mirrored), left
+    // out where the consumer reads the lower triangle only (herm 2)
+    const bool diag2 = d.herm == 2 && tm == tn;
+    if (T == 32 && diag2 && sub == 1) continue;
+    const bool mirror = d.herm == 1 && tm != tn;
+    const int rv = min(T, d.M - m0), cv = min(T, d.N - n0);
+    Src<T> sa, sb;
+    make_src<T>(sa, (const cplx*)d.A + (long long)b * d.sA_bat, d.lda, m0, d.M, wave, lane);
+    make_src<T>(sb, (const cplx*)d.B + (long long)b * d.sB_bat, d.ldb, n0, d.N, wave, lane);
+    cplx* Cb = (cplx*)d.C + (long long)b * d.sC_bat;
+    cplx* pt = part ? part + (u * T) * T : nullptr;
+    const int wm = wave >> 1, wn = wave & 1;
+    for (int c = part ? ch : 0; c < (part ? ch + 1 : nch); ++c) {
+      const int s0 = nch > 1 ? c * d.cseg : 0, s1 = nch > 1 ? min(d.nseg, s0 + d.cseg) : d.nseg;
+      const bool first = c == 0;
+#define NT_BODY(NI, NJ, RB, CB, IDLE) \
+  tile_body<T, NI, NJ>(d, sa, sb, s0, s1, m0, n0, RB, CB, IDLE, mirror, Cb, pt, first, sx, sy, sz, smem, wave, lane)
+      if constexpr (T == 32) {
+        NT_BODY(1, 1, wm * 16, wn * 16, wm * 16 >= rv || wn * 16 >= cv || (diag2 && sub != 2 && wm < wn));
+      } else {
+        if (cv <= 16) NT_BODY(1, 1, wave * 16, 0, wave * 16 >= rv);
+        else if (cv <= 32) NT_BODY(1, 2, wave * 16, 0, wave * 16 >= rv);
+        else if (rv <= 16) NT_BODY(1, 1, 0, wave * 16, wave * 16 >= cv);
+        else if (rv <= 32) NT_BODY(2, 1, 0, wave * 16, wave * 16 >= cv);
+        else NT_BODY(2, 2, wm * 32, wn * 32, diag2 && wm < wn);
       }
-
-    for (int seg = 0; seg < d.nseg; ++seg) {
-      const char* As = Ab + (long long)seg * d.sA_seg * esz;
-      const char* Bs = Bb + (long long)seg * d.sB_seg * esz;
-      const int kcur = (seg == d.nseg - 1) ? d.Klast : d.Kseg;
-      u4 ra[4], rb[4];
-      load_tile<P, A_CONJ>(As, d.lda, d.a_plane, m0, d.M, 0, kcur, ra);
-      load_tile<P, B_CONJ>(Bs, d.ldb, d.b_plane, n0, d.N, 0, kcur, rb);
-      for (int k0 = 0; k0 < kcur; k0 += BK) {
-        __syncthreads();
-        store_tile<P>(sA, ra);
-        store_tile<P>(sB, rb);
-        __syncthreads();
-        if (k0 + BK < kcur) {   // prefetch the next k block while this one is multiplied
-          load_tile<P, A_CONJ>(As, d.lda, d.a_plane, m0, d.M, k0 + BK, kcur, ra);
-          load_tile<P, B_CONJ>(Bs, d.ldb, d.b_plane, n0, d.N, k0 + BK, kcur, rb);
-        }
-        if constexpr (P == 0) {
-          // lane k-set: 4*lk + s, s = 0..3 (two 16-byte loads per plane)
-          const double* a = (const double*)sA;
-          const double* bb = (const double*)sB;
-          double ar[2][4], ai[2][4], br[2][4], bi[2][4];
-#pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            const int ra_ = wm * 32 + i * 16 + lr, rb_ = wn * 32 + i * 16 + lr;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-              ar[i][s] = a[(0 * 64 + ra_) * PITCH + 4 * lk + s];
-              ai[i][s] = a[(1 * 64 + ra_) * PITCH + 4 * lk + s];
-              br[i][s] = bb[(0 * 64 + rb_) * PITCH + 4 * lk + s];
-              bi[i][s] = bb[(1 * 64 + rb_) * PITCH + 4 * lk + s];
-            }
-          }
-#pragma unroll
-          for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-              for (int j = 0; j < 2; ++j) {
-                acc_re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[i][s], br[j][s], acc_re[i][j], 0, 0, 0);
-                acc_re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai[i][s], bi[j][s], acc_re[i][j], 0, 0, 0);
-                acc_im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[i][s], bi[j][s], acc_im[i][j], 0, 0, 0);
-                acc_im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[i][s], br[j][s], acc_im[i][j], 0, 0, 0);
-              }
-        } else {
-          // lane k-set: 8*lk + s, s = 0..7
-          const float* a = (const float*)sA;
-          const float* bb = (const float*)sB;
-#pragma unroll
-          for (int half = 0; half < 2; ++half) {
-            float ar[2][4], ai[2][4], br[2][4], bi[2][4];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-              const int ra_ = wm * 32 + i * 16 + lr, rb_ = wn * 32 + i * 16 + lr;
-              const f4 x0 = *(const f4*)&a[(0 * 64 + ra_) * PITCH + 8 * lk + 4 * half];
-              const f4 x1 = *(const f4*)&a[(1 * 64 + ra_) * PITCH + 8 * lk + 4 * half];
-              const f4 y0 = *(const f4*)&bb[(0 * 64 + rb_) * PITCH + 8 * lk + 4 * half];
-              const f4 y1 = *(const f4*)&bb[(1 * 64 + rb_) * PITCH + 8 * lk + 4 * half];
-#pragma unroll
-              for (int s = 0; s < 4; ++s) {
-                ar[i][s] = x0[s];
-                ai[i][s] = x1[s];
-                br[i][s] = y0[s];
-                bi[i][s] = y1[s];
-              }
-            }
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-              for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                  c_re[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[i][s], br[j][s], c_re[i][j], 0, 0, 0);
-                  c_re[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(-ai[i][s], bi[j][s], c_re[i][j], 0, 0, 0);
-                  c_im[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[i][s], bi[j][s], c_im[i][j], 0, 0, 0);
-                  c_im[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[i][s], br[j][s], c_im[i][j], 0, 0, 0);
-                }
-          }
-        }
-      }
-      if constexpr (P != 0) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              acc_re[i][j][v] += (double)c_re[i][j][v];
-              acc_im[i][j][v] += (double)c_im[i][j][v];
-              c_re[i][j][v] = 0.f;
-              c_im[i][j][v] = 0.f;
-            }
-      }
+#undef NT_BODY
     }
-
-    // ---- epilogue ----
-    const bool mirror = (d.herm == 1) && (tm != tn);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int r = (P == 0) ? (4 * v + lk) : (4 * lk + v);
-          const int m = m0 + wm * 32 + i * 16 + r;
-          const int n = n0 + wn * 32 + j * 16 + lr;
-          if (m >= d.M) continue;
-          const double vr = acc_re[i][j][v], vi = acc_im[i][j][v];
-          if (d.epi == 3) {
-            // split store (format of P) with zero fill of the row padding
-            if (n >= (d.npad ? d.npad : d.ldc)) continue;
-            const bool in = n < d.N;
-            const long long o = (long long)b * d.sC_bat + (long long)m * d.ldc + n;
-            if constexpr (P == 1) {
-              float* c = (float*)d.C;
-              c[o] = in ? (float)vr : 0.f;
-              c[d.c_plane + o] = in ? (float)vi : 0.f;
-            }
-            continue;
-          }
-          if (n >= d.N) continue;
-          cplx* Cb = (cplx*)d.C + (long long)b * d.sC_bat;
-          cplx val = cmk(vr, vi);
-          if (d.epi == 2) {
-            const int nf = d.nf;
-            const long long nf2 = (long long)nf * nf;
-            const int s_ = n / nf, r_ = n - s_ * nf;
-            Cb[(long long)m * nf2 + (long long)r_ * nf + s_] = val;
-            if (mirror) {
-              const int p_ = m / nf, q_ = m - p_ * nf;
-              Cb[(long long)n * nf2 + (long long)q_ * nf + p_] = cconj(val);
-            }
-          } else {
-            const long long o = (long long)m * d.ldc + n;
-            if (d.epi == 1) val = cadd(Cb[o], val);
-            if (d.epi == 4) val = csub(Cb[o], val);
-            Cb[o] = val;
-            if (mirror) {
-              const long long o2 = (long long)n * d.ldc + m;
-              cplx v2 = cmk(vr, -vi);
-              if (d.epi == 1) v2 = cadd(Cb[o2], v2);
-              Cb[o2] = v2;
-            }
-          }
-        }
   }
 }
 
-template <int P, int KIND>
-hipError_t launch_nt(int conj, const NtDesc* descs, int ndesc, long long total, int blocks,
-                     hipStream_t s) {
+template <int T>
+hipError_t launch_kind(int kind, const NtDesc* descs, int ndesc, long long t0, long long nt, int nch, cplx* part,
+                       int conj, int blocks, hipStream_t s) {
   dim3 g(blocks), b(256);
-  switch (conj & 3) {
-    case 0: hipLaunchKernelGGL((zgemm_nt_kernel<P, false, false, KIND>), g, b, 0, s, descs, ndesc, total); break;
-    case 1: hipLaunchKernelGGL((zgemm_nt_kernel<P, true, false, KIND>), g, b, 0, s, descs, ndesc, total); break;
-    case 2: hipLaunchKernelGGL((zgemm_nt_kernel<P, false, true, KIND>), g, b, 0, s, descs, ndesc, total); break;
-    default: hipLaunchKernelGGL((zgemm_nt_kernel<P, true, true, KIND>), g, b, 0, s, descs, ndesc, total); break;
+  const size_t lds = 4 * T * ROW_B;
+  switch (kind) {
+    case 1: hipLaunchKernelGGL((zgemm_nt_kernel<T, 1>), g, b, lds, s, descs, ndesc, t0, nt, nch, part, conj); break;
+    case 2: hipLaunchKernelGGL((zgemm_nt_kernel<T, 2>), g, b, lds, s, descs, ndesc, t0, nt, nch, part, conj); break;
+    case 3: hipLaunchKernelGGL((zgemm_nt_kernel<T, 3>), g, b, lds, s, descs, ndesc, t0, nt, nch, part, conj); break;
+    default: hipLaunchKernelGGL((zgemm_nt_kernel<T, 0>), g, b, lds, s, descs, ndesc, t0, nt, nch, part, conj); break;
   }
   return hipGetLastError();
-}
-
-template <int P>
-hipError_t launch_kind(int kind, int conj, const NtDesc* descs, int ndesc, long long total, int blocks,
-                       hipStream_t s) {
-  switch (kind) {
-    case 1: return launch_nt<P, 1>(conj, descs, ndesc, total, blocks, s);
-    case 2: return launch_nt<P, 2>(conj, descs, ndesc, total, blocks, s);
-    case 3: return launch_nt<P, 3>(conj, descs, ndesc, total, blocks, s);
-    default: return launch_nt<P, 0>(conj, descs, ndesc, total, blocks, s);
-  }
 }
 
 }  // namespace
@@ -335,25 +320,27 @@ hipError_t launch_kind(int kind, int conj, const NtDesc* descs, int ndesc, long 
 long long nt_plan(NtDesc* d, int n) {
   long long acc = 0;
   for (int i = 0; i < n; ++i) {
-    d[i].tiles_m = ceil_div(d[i].M, TM);
-    d[i].tiles_n = ceil_div(d[i].N, TN);
+    d[i].tiles_m = ceil_div(d[i].M, MT);
+    d[i].tiles_n = ceil_div(d[i].N, MT);
     d[i].tiles_per_batch = d[i].herm ? d[i].tiles_m * (d[i].tiles_m + 1) / 2
                                      : d[i].tiles_m * d[i].tiles_n;
     if (d[i].Klast <= 0 || d[i].Klast > d[i].Kseg) d[i].Klast = d[i].Kseg;
+    if (d[i].cseg <= 0) d[i].cseg = d[i].nseg;
     d[i].tile_begin = acc;
     acc += (long long)d[i].tiles_per_batch * d[i].batch;
   }
   return acc;
 }
 
-hipError_t nt_launch(int prec, int conj, const NtDesc* descs_dev, int ndesc, long long total,
-                     int max_blocks, hipStream_t s, int kind) {
+hipError_t nt_launch(int conj, const NtDesc* descs_dev, int ndesc, long long total, int max_blocks, hipStream_t s,
+                     int kind) {
   if (total <= 0) return hipSuccess;
-  const long long t8 = (total + 7) / 8 * 8;
   max_blocks = max_blocks / 8 * 8;
-  const int blocks = (int)(t8 < max_blocks ? t8 : max_blocks);
-  // FP64 and FP32 operands; bf16 hi+lo operands go through x3_launch
-  if (prec == 0) return launch_kind<0>(kind, conj, descs_dev, ndesc, total, blocks, s);
-  if (prec == 1) return launch_kind<1>(kind, conj, descs_dev, ndesc, total, blocks, s);
-  return hipErrorInvalidValue;
+  // 32 x 32 tiles where 64 x 64 would leave CUs idle or half filled: below
+  // NT_SMALL_TILES tiles
+  const bool small = total < NT_SMALL_TILES;
+  const long long units = small ? 4 * total : total;
+  const long long u8 = (units + 7) / 8 * 8;
+  if (small) return launch_kind<32>(kind, descs_dev, ndesc, 0, total, 1, nullptr, conj, (int)(u8 < 2048 ? u8 : 2048), s);
+  return launch_kind<64>(kind, descs_dev, ndesc, 0, total, 1, nullptr, conj, (int)(u8 < max_blocks ? u8 : max_blocks), s);
 }

@@ -229,13 +229,13 @@ void run_gemm(Arena& ar, int prec, int layout, std::vector<GemmDesc>& d, hipStre
 // mark(true) / mark(false) bracket each kernel launch when given (kernel timing)
 typedef std::function<void(bool)> LaunchMark;
 
-void run_nt(Arena& ar, int prec, int conj, std::vector<NtDesc>& d, hipStream_t s, int kind = 0,
+void run_nt(Arena& ar, int conj, std::vector<NtDesc>& d, hipStream_t s, int kind = 0,
             const LaunchMark& mark = nullptr) {
   long long total = nt_plan(d.data(), (int)d.size());
   if (total == 0) return;
   NtDesc* dd = ar.put(d.data(), d.size(), s);
   if (mark) mark(true);
-  HIPCHK(nt_launch(prec, conj, dd, (int)d.size(), total, gemm_blocks(), s, kind));
+  HIPCHK(nt_launch(conj, dd, (int)d.size(), total, gemm_blocks(), s, kind));
   if (mark) mark(false);
 }
 
@@ -657,7 +657,7 @@ void chol_blocked(Arena& ar, const cplx* in, cplx* A, cplx* lt, int* perm, int* 
       d[0].sA_bat = d[0].sB_bat = d[0].sC_bat = nn;
       d[0].herm = 2;
       d[0].epi = 4;
-      run_nt(ar, 0, 2, d, s);
+      run_nt(ar, 2, d, s);
     }
   }
 }
@@ -784,7 +784,7 @@ void do_fit(isdf_ctx c, int prec) {
           g[0].batch = nh;
           g[0].sA_bat = g[0].sB_bat = nn;
           g[0].sC_bat = (long long)nip * 64;
-          run_nt(c->arena_aux, 0, 0, g, c->aux);
+          run_nt(c->arena_aux, 0, g, c->aux);
         }
         HIPCHK(tri_inv_diag_launch(Lrow, c->rank.as<int>(), A, Yd, nip, nh, jb, c->aux));
         if (jb > 0) {
@@ -796,7 +796,7 @@ void do_fit(isdf_ctx c, int prec) {
           g[0].sB_bat = 4096;
           g[0].sC_bat = nn;
           g[0].epi = 4;
-          run_nt(c->arena_aux, 0, 0, g, c->aux);
+          run_nt(c->arena_aux, 0, g, c->aux);
         }
       }
     }
@@ -806,7 +806,7 @@ void do_fit(isdf_ctx c, int prec) {
     d[0].sA_bat = d[0].sB_bat = d[0].sC_bat = nip2(c);
     d[0].herm = 1;
     // G[m][n] = sum_i conj(Yt[m][i]) Yt[n][i]
-    run_nt(c->arena_aux, 0, 1, d, c->aux);
+    run_nt(c->arena_aux, 1, d, c->aux);
   }
   c->timer.end("pinv", c->aux);
   HIPCHK(hipEventRecord(c->ev_pinv, c->aux));
@@ -953,7 +953,7 @@ void kernel_zeta_route(isdf_ctx c) {
     d[0].batch = nh;
     d[0].sC_bat = nip2(c);
     d[0].herm = 1;
-    run_nt(c->arena, ISDF_FP64, 2, d, s, 1);
+    run_nt(c->arena, 2, d, s, 1);
   }
   c->timer.end("w_gemm", s);
   c->kernel_pending = false;
@@ -1029,7 +1029,7 @@ void do_kernel(isdf_ctx c, int prec) {
       d[0].batch = nb;
       d[0].sC_bat = nip2(c);
       d[0].herm = 1;
-      run_nt(c->arena, ISDF_FP64, 2, d, s, 1);
+      run_nt(c->arena, 2, d, s, 1);
     }
     c->timer.end("v_gemm", s);
   }
@@ -1054,7 +1054,7 @@ void do_kernel(isdf_ctx c, int prec) {
         g.herm = herm;
         d.push_back(g);
       }
-      run_nt(c->arena, 0, conj, d, s);
+      run_nt(c->arena, conj, d, s);
     };
     // T1 = G V'  (V' Hermitian: V'[k][n] = conj(V'[n][k]))
     prod(c->work3.as<cplx>(), c->w.as<cplx>(), c->work1.as<cplx>(), 2, 0);
@@ -1389,7 +1389,7 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     d[0].sB_bat = (long long)nip * ld;
     d[0].epi = prec == 0 ? 0 : 3;
     d[0].npad = (int)ld;
-    if (prec == 0) run_nt(ws.arena, prec, 0, d, s, 2);
+    if (prec == 0) run_nt(ws.arena, 0, d, s, 2);
     else run_big(ws.arena, prec, 0, d, 1, s, 2);
   };
   // (pq|rs) = sum_q sum_J U^q_{(pq),J} conj(R^q_{(sr),J})  (eq. (19), R^{-q}_{rs} = conj R^q_{sr}).
@@ -1430,7 +1430,7 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
       else ws.timer.end("frag_eri_kernel", s);
     };
   auto eri_gemm = [&](std::vector<NtDesc>& d) {
-    if (prec == 0) run_nt(ws.arena, prec, 2, d, s, 3, mark);
+    if (prec == 0) run_nt(ws.arena, 2, d, s, 3, mark);
     else run_big(ws.arena, prec, 2, d, d[0].nseg, s, 3, mark);
   };
   if (p.nb == 1) {
@@ -2666,7 +2666,7 @@ isdf_status isdf_hf_jk(isdf_ctx ctx, const void* dm, void* j_out, void* k_out, u
       d[0].batch = nk;
       d[0].sA_bat = d[0].sB_bat = on;
       d[0].sC_bat = oo;
-      run_nt(c->arena, 0, 1, d, s);
+      run_nt(c->arena, 1, d, s);
       c->timer.end("hf_j", s);
     }
     if (K) {
@@ -2701,7 +2701,7 @@ isdf_status isdf_hf_jk(isdf_ctx ctx, const void* dm, void* j_out, void* k_out, u
         d[0].sA_bat = on;
         d[0].sB_bat = nn;
         d[0].sC_bat = on;
-        run_nt(c->arena, 0, 0, d, s);
+        run_nt(c->arena, 0, d, s);
       }
       {
         // K^k[mu][nu] = sum_I conj(X^k_{I mu}) Zt^k[nu][I]
@@ -2710,7 +2710,7 @@ isdf_status isdf_hf_jk(isdf_ctx ctx, const void* dm, void* j_out, void* k_out, u
         d[0].batch = nk;
         d[0].sA_bat = d[0].sB_bat = on;
         d[0].sC_bat = oo;
-        run_nt(c->arena, 0, 1, d, s);
+        run_nt(c->arena, 1, d, s);
       }
       c->timer.end("hf_k", s);
     }
@@ -2744,7 +2744,7 @@ static void tau_polarisabilities(isdf_ctx c, const cplx* y, const double* ed, in
     d[0].sA_bat = d[0].sB_bat = (long long)nip * kk;
     d[0].sC_bat = nn;
     d[0].herm = 1;
-    run_nt(c->arena, 0, 2, d, s);
+    run_nt(c->arena, 2, d, s);
   }
   c->timer.end("mp2_green", s);
   c->timer.begin("mp2_pconv", s);

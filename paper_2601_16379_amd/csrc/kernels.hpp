@@ -44,7 +44,8 @@ hipError_t gemm_launch(int prec, int layout_flags, const GemmDesc* descs_dev, in
 // Operand formats by precision: 0 complex128 rows (ld in complex elements);
 // 1 two float planes re|im; 2 four bf16 planes re_hi|re_lo|im_hi|im_lo (ld and
 // plane strides in scalar elements; rows zero-padded to a multiple of 8).
-// epi: 0 store c128, 1 accumulate c128, 2 ERI scatter c128, 3 store in the
+// epi: 0 store c128, 1 accumulate c128 over the K segments of a launch
+// sequence (FP64: over the chunks of cseg segments), 3 store in the
 // split format of the precision (plane stride c_plane), zero-filling columns
 // N..ldc-1, 4 subtract from c128.  herm: 1 lower tiles mirrored as conj to the
 // upper triangle; 2 lower tiles only, no mirror.
@@ -59,17 +60,19 @@ struct NtDesc {
   long long sA_bat, sB_bat, sC_bat;
   int M, N, Kseg, nseg, Klast, batch;
   int tiles_m, tiles_n, tiles_per_batch;
-  int herm, epi, nf;
+  int herm, epi;
+  int cseg;               // FP64: K segments per chunk (0 = all)
   int npad;               // epi 3: columns written (zeros from N on); 0 = ldc
   int ktri;               // B[n][k] = 0 for k < n: the mixed kernels start each column
                           // tile's K range at its first column (FP64 reads the zeros)
   long long tile_begin;
 };
 long long nt_plan(NtDesc* d, int n);
-// conj: bit 0 conjugates A, bit 1 conjugates B
+// FP64 products (gemm_nt.hip).  conj: bit 0 conjugates A, bit 1 conjugates B;
 // kind names the call site in profiles: 0 generic, 1 V^q, 2 U^q, 3 fragment contraction
-hipError_t nt_launch(int prec, int conj, const NtDesc* descs_dev, int ndesc, long long total,
-                     int max_blocks, hipStream_t s, int kind = 0);
+constexpr int NT_SMALL_TILES = 768;   // fewer 64 x 64 tiles than this run as 32 x 32 ones
+hipError_t nt_launch(int conj, const NtDesc* descs_dev, int ndesc, long long total, int max_blocks, hipStream_t s,
+                     int kind = 0);
 
 // Large-tile (128x128, 512 threads) NT GEMM for the mixed precisions (1, 2):
 // one K segment `seg` per launch; epi 1 accumulates the FP32 partials in an

@@ -1,0 +1,58 @@
+"""Edges of the fragment products' tiles, against the oracle.
+
+Given the GPU's own W^q, the fragment ERIs of eqs. (19)-(20) are products of
+sizes N_IP and n_f^2: interpolation-point counts and fragment sizes one below,
+at and one above the tile, strip and stage sizes (16, 32, 64, 128), with few
+tiles (small tiles) and with many (large ones).  Bars: the repository's own,
+1e-10 of the largest ERI in FP64 and 1e-6 Eh in FP32 and bf16x3."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import isdf_inputs as inp
+from oracle import kpoint as ko
+
+pytestmark = pytest.mark.gpu
+
+FEW = [1, 2, 3, 4, 5, 6, 8, 9, 11]                # n_f^2 = 1 .. 121
+MANY = [24, 25, 41, 46]                           # n_f^2 = 576 .. 2116: over a thousand 64 x 64 tiles
+
+
+def _context(n_ip):
+    import torch
+    import paper_2601_16379_amd as pkg
+    cfg = dataclasses.replace(inp.get_config("t_small_k2"), n_ip=n_ip)
+    d = inp.make_inputs(cfg)
+    ctx = pkg.Isdf(d.lattice, cfg.grid, cfg.kmesh, torch.from_numpy(d.orbitals).cuda(),
+                   torch.from_numpy(d.ip_index).cuda())
+    ctx.fit()
+    ctx.coulomb_kernel("fp64")
+    return cfg, ctx, ko.ip_values(d.orbitals, d.ip_index), np.stack([ctx.get_kernel(q) for q in range(cfg.n_k)])
+
+
+def _check(cfg, ctx, x, w, sizes, precs):
+    import torch
+    frags = [inp.make_fragment(cfg, f, n) for f, n in enumerate(sizes)]
+    dev = [torch.from_numpy(f).cuda() for f in frags]
+    out = {p: ctx.fragment_eri(dev, p) for p in precs}
+    for f, c in enumerate(frags):
+        ref = ko.fragment_eri(x, c, w, cfg.kmesh)
+        big = np.max(np.abs(ref))
+        for p in precs:
+            err = np.max(np.abs(out[p][f].cpu().numpy() - ref))
+            assert err <= (1e-10 * big if p == "fp64" else 1e-6), (sizes[f], p, err, big)
+
+
+@pytest.mark.parametrize("n_ip", [15, 16, 17, 31, 33, 48, 63, 64, 65, 97, 127, 129])
+def test_small_products(n_ip):
+    cfg, ctx, x, w = _context(n_ip)
+    _check(cfg, ctx, x, w, FEW, ["fp64", "fp32", "bf16x3"])
+    ctx.close()
+
+
+@pytest.mark.parametrize("n_ip", [72, 129])
+def test_many_tiles(n_ip):
+    cfg, ctx, x, w = _context(n_ip)
+    _check(cfg, ctx, x, w, MANY, ["fp64", "fp32", "bf16x3"])
+    ctx.close()
