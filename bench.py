@@ -152,29 +152,25 @@ def stage_work(stage, cfg, nfs, prec, passes=1, yform=False):
     return None
 
 
-KERNEL_OF_STAGE = {"frag_eri": ("zgemm_nt_kernel<0, false, true, 3>", "{x}false, true, 3"),
-                   "frag_u": ("zgemm_nt_kernel<0, false, false, 2>", "{x}false, false, 2"),
-                   "frag_pair": ("pair_kernel", "pair_kernel"),
-                   "v_gemm": ("zgemm_nt_kernel<0, false, true, 1>", "zgemm_nt_kernel<0, false, true, 1>"),
-                   "rhs_t": ("rhs_t_kernel<", "rhs_t_kernel<"),
-                   "rhs_kconv": ("kconv_", "kconv_"),
-                   "grid_fft": ("slab_kernel_c<", "slab_kernel_c<")}
+# main kernel of a stage as the profiler lists it (prefixes, by precision)
+GEMM_OF_STAGE = {"frag_eri": {"fp64": "zgemm_nt_kernel<0, 64, 3>", "fp32": "zgemm_nt_kernel<1, 64, 3>",
+                              "bf16x3": "zgemm_x3_kernel<3>", "bf16": "zgemm_c2b_kernel<3>"},
+                 "frag_u": {"fp64": "zgemm_nt_kernel<0, 64, 2>", "fp32": "zgemm_nt_kernel<1, 64, 2>",
+                            "bf16x3": "zgemm_x3_kernel<2>", "bf16": "zgemm_ring_kernel<3, 2>"}}
+KERNEL_OF_STAGE = {"frag_pair": "pair_", "v_gemm": "zgemm_nt_kernel<0, 64, 1>", "rhs_t": "rhs_t_kernel<",
+                   "rhs_kconv": "kconv_", "grid_fft": "slab_kernel_c<"}
 
 
 def kernel_name(stage, prec):
-    """Name (prefix) of a stage's main kernel as the profiler lists it: the
-    FP32 path runs the two-plane big-tile kernel, bf16x3 and bf16 their own
-    MFMA kernels."""
-    if stage not in KERNEL_OF_STAGE:
-        return stage
-    x = {"fp32": "zgemm_big_kernel<1, ", "bf16x3": "zgemm_x3_kernel<", "bf16": "zgemm_x1_kernel<"}.get(prec, "")
-    if stage == "frag_eri" and prec == "bf16":
-        return "zgemm_c2b_kernel<3>"
-    return KERNEL_OF_STAGE[stage][0 if prec == "fp64" else 1].format(x=x)
+    """Name (prefix) of a stage's main kernel as the profiler lists it."""
+    if stage in GEMM_OF_STAGE:
+        return GEMM_OF_STAGE[stage][prec]
+    return KERNEL_OF_STAGE.get(stage, stage)
 
 
 # other kernels of a stage (the contraction of launches with few tiles)
-KERNEL_ALT = {("frag_eri", "bf16x3"): "zgemm_c2b_kernel<2>"}
+KERNEL_ALT = {("frag_eri", "bf16x3"): "zgemm_c2b_kernel<2>", ("frag_eri", "fp64"): "zgemm_nt_kernel<0, 32, 3>",
+              ("frag_eri", "fp32"): "zgemm_nt_kernel<1, 32, 3>"}
 
 
 def counter_traffic(stage, workload, prec):
@@ -184,7 +180,7 @@ def counter_traffic(stage, workload, prec):
     taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "%s_%s_traffic.json" % (workload, prec))
-    if stage not in KERNEL_OF_STAGE or not os.path.exists(path):
+    if stage not in {**GEMM_OF_STAGE, **KERNEL_OF_STAGE} or not os.path.exists(path):
         return None
     prof = json.load(open(path))
     csrc = os.path.join(ROOT, "paper_2601_16379_amd", "csrc")

@@ -78,13 +78,6 @@ __device__ inline void wait_copies(int n) {
 // The ring pipeline: one workgroup a CU, RING LDS stage buffers
 constexpr int RING = 4;
 
-__device__ inline int isqrt_floor(long long x) {
-  long long r = (long long)sqrt((double)x);
-  while (r * r > x) --r;
-  while ((r + 1) * (r + 1) <= x) ++r;
-  return (int)r;
-}
-
 // Vectors that start at or past the end of the K segment are copied from
 // this zero block instead, so that LDS holds zeros there.
 __device__ __attribute__((aligned(16))) unsigned short kZeroVec[8];
@@ -272,7 +265,7 @@ __device__ inline void mma_single(const Frag<NI, NJ>& f, int j, f16v (&c_re)[NI]
 template <int F, int NI, int NJ>
 __device__ inline void tile_epilogue(const NtDesc& d, int b, int m0, int n0, int rb0, int cb0,
                                      const f16v (&c_re)[NI][NJ], const f16v (&c_im)[NI][NJ], char* smem, int wave,
-                                     int lane, bool first) {
+                                     int lane, bool first, cplx* part) {
   const int lr = lane & 31, lk = lane >> 5;
   if (d.epi == 3) {
     __syncthreads();                      // every wave is past its last stage reads
@@ -315,14 +308,30 @@ __device__ inline void tile_epilogue(const NtDesc& d, int b, int m0, int n0, int
       }
       __builtin_amdgcn_wave_barrier();
     }
+  } else if (part) {
+    // partial block of the tile, row-major; the offset is opaque so that the
+    // addresses are formed here and not held over the K loop
+    int o0 = (rb0 + 4 * lk) * XT + cb0 + lr;
+    asm volatile("" : "+v"(o0));
+    cplx* pp = part + o0;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          pp[(i * 32 + 8 * (v >> 2) + (v & 3)) * XT + j * 32] =
+              cmk((double)c_re[i][j][v], (double)c_im[i][j][v]);
   } else {
+    int mr = m0 + rb0 + 4 * lk;
+    asm volatile("" : "+v"(mr));
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int m = m0 + rb0 + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
+          const int m = mr + i * 32 + 8 * (v >> 2) + (v & 3);
           const int n = n0 + cb0 + j * 32 + lr;
           if (m >= d.M || n >= d.N) continue;
           cplx* cp = (cplx*)d.C + (long long)b * d.sC_bat + (long long)m * d.ldc + n;
@@ -381,7 +390,7 @@ template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ, bool TRI>
 __device__ inline void tile_body(const NtDesc& d, int b, int m0, int n0, int kcur,
                                  const unsigned short* const (&asrc)[NCOPY], const unsigned short* const (&bsrc)[NCOPY],
                                  const int (&gslot)[NCOPY], int rb0, int cb0, char* smem, int wave, int lane,
-                                 bool idle, bool first) {
+                                 bool idle, bool first, cplx* part) {
   const int lr = lane & 31, lk = lane >> 5;
   f16v c_re[NI][NJ], c_im[NI][NJ];
 #pragma unroll
@@ -423,7 +432,7 @@ __device__ inline void tile_body(const NtDesc& d, int b, int m0, int n0, int kcu
       if (!idle) stage_mma<F, NI, NJ, A_CONJ, B_CONJ>(f, c_re, c_im);
     }
   }
-  if (!idle) tile_epilogue<F, NI, NJ>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first);
+  if (!idle) tile_epilogue<F, NI, NJ>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first, part);
 }
 
 // One step of the ring pipeline: the MFMAs of stage s (fragments in `cur`)
@@ -474,7 +483,7 @@ template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ, bool TRI>
 __device__ inline void tile_body_ring(const NtDesc& d, int b, int m0, int n0, int kcur,
                                       const unsigned short* const (&asrc)[NCOPY],
                                       const unsigned short* const (&bsrc)[NCOPY], const int (&gslot)[NCOPY],
-                                      int rb0, int cb0, char* smem, int wave, int lane, bool idle, bool first) {
+                                      int rb0, int cb0, char* smem, int wave, int lane, bool idle, bool first, cplx* part) {
   const int lr = lane & 31, lk = lane >> 5;
   f16v c_re[NI][NJ], c_im[NI][NJ];
 #pragma unroll
@@ -511,7 +520,7 @@ __device__ inline void tile_body_ring(const NtDesc& d, int b, int m0, int n0, in
       ring_step<F, NI, NJ, A_CONJ, B_CONJ, TRI>(s + 1, nst, kcur, d.ktri != 0, f1, f0, c_re, c_im, asrc, bsrc, gslot,
                                                 rb0, cb0, smem, wave, lr, lk, idle);
   }
-  if (!idle) tile_epilogue<F, NI, NJ>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first);
+  if (!idle) tile_epilogue<F, NI, NJ>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first, part);
 }
 
 // The same K loop with two barriers a stage and the copies two stages
@@ -530,7 +539,7 @@ template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ, bool TRI>
 __device__ inline void tile_body_2b(const NtDesc& d, int b, int m0, int n0, int kcur,
                                  const unsigned short* const (&asrc)[NCOPY], const unsigned short* const (&bsrc)[NCOPY],
                                  const int (&gslot)[NCOPY], int rb0, int cb0, char* smem, int wave, int lane,
-                                 bool idle, bool first) {
+                                 bool idle, bool first, cplx* part) {
   const int lr = lane & 31, lk = lane >> 5;
   f16v c_re[NI][NJ], c_im[NI][NJ];
 #pragma unroll
@@ -583,39 +592,31 @@ __device__ inline void tile_body_2b(const NtDesc& d, int b, int m0, int n0, int 
       }
     }
   }
-  if (!idle) tile_epilogue<F, NI, NJ>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first);
+  if (!idle) tile_epilogue<F, NI, NJ>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first, part);
 }
 
 template <int F, bool A_CONJ, bool B_CONJ, int KIND, bool RINGP, bool TWOB = false>
-__device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, long long total_tiles, int seg) {
+__device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, long long t0, long long nt, int seg0,
+                                int nseg, cplx* part) {
   extern __shared__ __attribute__((aligned(16))) char smem[];   // NBUF (RING) stages x (A, B)
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
-  const long long t8 = (total_tiles + 7) / 8 * 8;
-  const long long per = t8 / 8;
-  for (long long it = blockIdx.x; it < t8; it += gridDim.x) {
-    const long long t = (it % 8) * per + it / 8;   // XCD-contiguous tile ranges
-    if (t >= total_tiles) continue;
-    int lo = 0, hi = ndesc - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (descs[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
-    }
-    const NtDesc d = descs[lo];
-    const long long local = t - d.tile_begin;
-    const int b = (int)(local / d.tiles_per_batch);
-    const int lt = (int)(local - (long long)b * d.tiles_per_batch);
-    int tm, tn;
-    if (d.herm) {
-      tm = (isqrt_floor(8LL * lt + 1) - 1) / 2;
-      tn = lt - tm * (tm + 1) / 2;
-    } else {
-      tm = lt / d.tiles_n;
-      tn = lt - tm * d.tiles_n;
-    }
+  // units: the tiles [t0, t0 + nt) of the K segment seg0, or with part those
+  // of each of nseg segments, segment by segment
+  const long long units = nt * nseg;
+  const long long u8 = (units + 7) / 8 * 8;
+  const long long per = u8 / 8;
+  for (long long it = blockIdx.x; it < u8; it += gridDim.x) {
+    const long long u = (it % 8) * per + it / 8;   // XCD-contiguous ranges
+    if (u >= units) continue;
+    const int seg = seg0 + (int)(u / nt);
+    const NtTile tl = nt_tile(descs, ndesc, t0 + u % nt);
+    const NtDesc d = descs[tl.desc];
+    const int b = tl.b, tm = tl.tm, tn = tl.tn;
+    cplx* pt = part ? part + u * (XT * XT) : nullptr;
     const int m0 = tm * XT, n0 = tn * XT;
     // interleaved formats: logical element e at u16 EU*e (e a multiple of 8)
     constexpr int EU = Fmt<F>::EU;
@@ -649,148 +650,106 @@ __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, lon
     if constexpr (RINGP) {
       if (d.M - m0 <= 32)
         tile_body_ring<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave,
-                                                lane, diag && wave > 0, first);
+                                                lane, diag && wave > 0, first, pt);
       else if (d.N - n0 <= 32)
         tile_body_ring<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wave * 32, 0, smem, wave,
-                                                lane, false, first);
+                                                lane, false, first, pt);
       else
         tile_body_ring<F, 2, 2, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 64, wn * 64, smem,
-                                                wave, lane, diag && wm < wn, first);
+                                                wave, lane, diag && wm < wn, first, pt);
     } else if constexpr (TWOB) {
       if (d.M - m0 <= 32)
         tile_body_2b<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave, lane,
-                                              diag && wave > 0, first);
+                                              diag && wave > 0, first, pt);
       else if (d.N - n0 <= 32)
         tile_body_2b<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wave * 32, 0, smem, wave, lane,
-                                              false, first);
+                                              false, first, pt);
       else
         tile_body_2b<F, 2, 2, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 64, wn * 64, smem, wave,
-                                              lane, diag && wm < wn, first);
+                                              lane, diag && wm < wn, first, pt);
     } else {
       if (d.M - m0 <= 32)
         tile_body<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave, lane,
-                                           diag && wave > 0, first);
+                                           diag && wave > 0, first, pt);
       else if (d.N - n0 <= 32)
         tile_body<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wave * 32, 0, smem, wave, lane,
-                                           false, first);
+                                           false, first, pt);
       else
         tile_body<F, 2, 2, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 64, wn * 64, smem, wave,
-                                           lane, diag && wm < wn, first);
+                                           lane, diag && wm < wn, first, pt);
     }
   }
 }
 
-template <bool A_CONJ, bool B_CONJ, int KIND>
-__global__ __launch_bounds__(XNT, 2) void zgemm_x3_kernel(const NtDesc* __restrict__ descs, int ndesc,
-                                                          long long total_tiles, int seg) {
-  x3_tiles<2, A_CONJ, B_CONJ, KIND, false>(descs, ndesc, total_tiles, seg);
-}
-
-template <bool A_CONJ, bool B_CONJ, int KIND>
-__global__ __launch_bounds__(XNT, 2) void zgemm_x1_kernel(const NtDesc* __restrict__ descs, int ndesc,
-                                                          long long total_tiles, int seg) {
-  x3_tiles<3, A_CONJ, B_CONJ, KIND, false>(descs, ndesc, total_tiles, seg);
-}
-
-// two barriers a stage: the fragment contraction (kind 3, B conjugated) of
-// launches with few tiles, both formats
-template <int F>
-__global__ __launch_bounds__(XNT, 2) void zgemm_c2b_kernel(const NtDesc* __restrict__ descs, int ndesc,
-                                                           long long total_tiles, int seg) {
-  x3_tiles<F, false, true, 3, false, true>(descs, ndesc, total_tiles, seg);
-}
-
-// ring pipeline (one workgroup a CU): the fragment GEMMs, both formats
-template <int F, bool A_CONJ, bool B_CONJ, int KIND>
-__global__ __launch_bounds__(XNT, 1) void zgemm_ring_kernel(const NtDesc* __restrict__ descs, int ndesc,
-                                                            long long total_tiles, int seg) {
-  x3_tiles<F, A_CONJ, B_CONJ, KIND, true>(descs, ndesc, total_tiles, seg);
-}
+// the two call sites of the path: U^q = R^q W^q (kind 2, no conjugation) and
+// the fragment contraction (kind 3, B conjugated)
+#define X3_ARGS const NtDesc *__restrict__ descs, int ndesc, long long t0, long long nt, int seg0, int nseg, cplx *part
 
 template <int KIND>
-hipError_t launch_x3(int conj, const NtDesc* descs, int ndesc, long long total, int blocks, int seg,
-                     hipStream_t s) {
-  dim3 g(blocks), b(XNT);
-  const size_t lds = NBUF * STAGE_B;
-  switch (conj & 3) {
-    case 0: hipLaunchKernelGGL((zgemm_x3_kernel<false, false, KIND>), g, b, lds, s, descs, ndesc, total, seg); break;
-    case 1: hipLaunchKernelGGL((zgemm_x3_kernel<true, false, KIND>), g, b, lds, s, descs, ndesc, total, seg); break;
-    case 2: hipLaunchKernelGGL((zgemm_x3_kernel<false, true, KIND>), g, b, lds, s, descs, ndesc, total, seg); break;
-    default: hipLaunchKernelGGL((zgemm_x3_kernel<true, true, KIND>), g, b, lds, s, descs, ndesc, total, seg); break;
-  }
-  return hipGetLastError();
+__global__ __launch_bounds__(XNT, 2) void zgemm_x3_kernel(X3_ARGS) {
+  x3_tiles<2, false, KIND == 3, KIND, false>(descs, ndesc, t0, nt, seg0, nseg, part);
 }
 
-// single-bf16 format: the two call sites of the path (U^q = R^q W^q, kind 2,
-// no conjugation; the fragment contraction, kind 3, B conjugated)
-hipError_t launch_x1(int conj, const NtDesc* descs, int ndesc, long long total, int blocks, int seg, int kind,
-                     hipStream_t s) {
-  dim3 g(blocks), b(XNT);
-  const size_t lds = NBUF * STAGE_B;
-  if (kind == 2 && (conj & 3) == 0)
-    hipLaunchKernelGGL((zgemm_x1_kernel<false, false, 2>), g, b, lds, s, descs, ndesc, total, seg);
-  else if (kind == 3 && (conj & 3) == 2)
-    hipLaunchKernelGGL((zgemm_x1_kernel<false, true, 3>), g, b, lds, s, descs, ndesc, total, seg);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
-// ring pipeline: the same two call sites, either format
+// two barriers a stage: the fragment contraction of launches with few tiles
+// (bf16x3), or always (single bf16)
 template <int F>
-hipError_t launch_ring(int conj, const NtDesc* descs, int ndesc, long long total, int blocks, int seg, int kind,
-                       hipStream_t s) {
-  dim3 g(blocks), b(XNT);
-  const size_t lds = RING * STAGE_B;
-  if (kind == 2 && (conj & 3) == 0)
-    hipLaunchKernelGGL((zgemm_ring_kernel<F, false, false, 2>), g, b, lds, s, descs, ndesc, total, seg);
-  else if (kind == 3 && (conj & 3) == 2)
-    hipLaunchKernelGGL((zgemm_ring_kernel<F, false, true, 3>), g, b, lds, s, descs, ndesc, total, seg);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+__global__ __launch_bounds__(XNT, 2) void zgemm_c2b_kernel(X3_ARGS) {
+  x3_tiles<F, false, true, 3, false, true>(descs, ndesc, t0, nt, seg0, nseg, part);
 }
+
+// ring pipeline (one workgroup a CU), both formats
+template <int F, int KIND>
+__global__ __launch_bounds__(XNT, 1) void zgemm_ring_kernel(X3_ARGS) {
+  x3_tiles<F, false, KIND == 3, KIND, true>(descs, ndesc, t0, nt, seg0, nseg, part);
+}
+#undef X3_ARGS
 
 }  // namespace
 
-bool ring_supported(int conj, int kind) {
-  return (kind == 2 && (conj & 3) == 0) || (kind == 3 && (conj & 3) == 2);
+long long x3_plan(NtDesc* d, int n) {
+  long long acc = 0;
+  for (int i = 0; i < n; ++i) {
+    d[i].tiles_m = ceil_div(d[i].M, XT);
+    d[i].tiles_n = ceil_div(d[i].N, XT);
+    d[i].tiles_per_batch = d[i].herm ? d[i].tiles_m * (d[i].tiles_m + 1) / 2
+                                     : d[i].tiles_m * d[i].tiles_n;
+    if (d[i].Klast <= 0 || d[i].Klast > d[i].Kseg) d[i].Klast = d[i].Kseg;
+    d[i].tile_begin = acc;
+    acc += (long long)d[i].tiles_per_batch * d[i].batch;
+  }
+  return acc;
 }
 
-hipError_t x1_launch(int conj, const NtDesc* descs_dev, int ndesc, long long total, int max_blocks, int seg,
-                     hipStream_t s, int kind, bool ring) {
-  if (total <= 0) return hipSuccess;
-  const long long t8 = (total + 7) / 8 * 8;
+hipError_t x3_launch(int fmt, const NtDesc* descs_dev, int ndesc, long long t0, long long nt, int seg0, int nseg,
+                     cplx* part, int max_blocks, hipStream_t s, int kind, bool ring) {
+  if (nt <= 0 || nseg <= 0) return hipSuccess;
+  if ((fmt != 2 && fmt != 3) || (kind != 2 && kind != 3) || (!part && nseg != 1)) return hipErrorInvalidValue;
+  const long long units = nt * nseg, u8 = (units + 7) / 8 * 8;
   max_blocks = max_blocks / 8 * 8;
-  const int blocks = (int)(t8 < max_blocks ? t8 : max_blocks);
-  if (ring) return launch_ring<3>(conj, descs_dev, ndesc, total, blocks, seg, kind, s);
-  // single bf16: 32 MFMAs a stage (against 48 in bf16x3) leave less time to
-  // cover a one-stage prefetch; the contraction always takes the two-barrier
-  // loop (0.378 against 0.354 of bf16 peak on the 120-orbital 1000-k shape)
-  if (kind == 3 && (conj & 3) == 2) {
-    hipLaunchKernelGGL((zgemm_c2b_kernel<3>), dim3(blocks), dim3(XNT), NBUF * STAGE_B, s, descs_dev, ndesc, total,
-                       seg);
-    return hipGetLastError();
+  const dim3 g((unsigned)(u8 < max_blocks ? u8 : max_blocks)), b(XNT);
+#define COMMA ,
+#define X3_GO(KERNEL, LDS) \
+  hipLaunchKernelGGL((KERNEL), g, b, LDS, s, descs_dev, ndesc, t0, nt, seg0, nseg, part)
+  if (ring) {
+    if (fmt == 2 && kind == 2) X3_GO(zgemm_ring_kernel<2 COMMA 2>, RING * STAGE_B);
+    else if (fmt == 2) X3_GO(zgemm_ring_kernel<2 COMMA 3>, RING * STAGE_B);
+    else if (kind == 2) X3_GO(zgemm_ring_kernel<3 COMMA 2>, RING * STAGE_B);
+    else X3_GO(zgemm_ring_kernel<3 COMMA 3>, RING * STAGE_B);
+  } else if (fmt == 3) {
+    // single bf16: 32 MFMAs a stage (against 48 in bf16x3) leave less time to
+    // cover a one-stage prefetch; the contraction always takes the two-barrier
+    // loop (0.378 against 0.354 of bf16 peak on the 120-orbital 1000-k shape),
+    // U^q the ring
+    if (kind == 2) return hipErrorInvalidValue;
+    X3_GO(zgemm_c2b_kernel<3>, NBUF * STAGE_B);
+  } else if (kind == 2) {
+    X3_GO(zgemm_x3_kernel<2>, NBUF * STAGE_B);
+  } else if (units < 2LL * g.x) {
+    X3_GO(zgemm_c2b_kernel<2>, NBUF * STAGE_B);
+  } else {
+    X3_GO(zgemm_x3_kernel<3>, NBUF * STAGE_B);
   }
-  return launch_x1(conj, descs_dev, ndesc, total, blocks, seg, kind, s);
-}
-
-hipError_t x3_launch(int conj, const NtDesc* descs_dev, int ndesc, long long total, int max_blocks, int seg,
-                     hipStream_t s, int kind, bool ring) {
-  if (total <= 0) return hipSuccess;
-  const long long t8 = (total + 7) / 8 * 8;
-  max_blocks = max_blocks / 8 * 8;
-  const int blocks = (int)(t8 < max_blocks ? t8 : max_blocks);
-  if (ring) return launch_ring<2>(conj, descs_dev, ndesc, total, blocks, seg, kind, s);
-  if (kind == 3 && (conj & 3) == 2 && total < 2LL * blocks) {
-    hipLaunchKernelGGL((zgemm_c2b_kernel<2>), dim3(blocks), dim3(XNT), NBUF * STAGE_B, s, descs_dev, ndesc, total,
-                       seg);
-    return hipGetLastError();
-  }
-  switch (kind) {
-    case 1: return launch_x3<1>(conj, descs_dev, ndesc, total, blocks, seg, s);
-    case 2: return launch_x3<2>(conj, descs_dev, ndesc, total, blocks, seg, s);
-    case 3: return launch_x3<3>(conj, descs_dev, ndesc, total, blocks, seg, s);
-    default: return launch_x3<0>(conj, descs_dev, ndesc, total, blocks, seg, s);
-  }
+#undef X3_GO
+#undef COMMA
+  return hipGetLastError();
 }

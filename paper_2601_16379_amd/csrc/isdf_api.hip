@@ -229,40 +229,100 @@ void run_gemm(Arena& ar, int prec, int layout, std::vector<GemmDesc>& d, hipStre
 // mark(true) / mark(false) bracket each kernel launch when given (kernel timing)
 typedef std::function<void(bool)> LaunchMark;
 
-void run_nt(Arena& ar, int conj, std::vector<NtDesc>& d, hipStream_t s, int kind = 0,
-            const LaunchMark& mark = nullptr) {
-  long long total = nt_plan(d.data(), (int)d.size());
+// FP64 products (and FP32 U^q, prec 1).
+void run_nt(Arena& ar, int conj, std::vector<NtDesc>& d, hipStream_t s, int kind = 0, int prec = 0) {
+  const long long total = nt_plan(d.data(), (int)d.size());
   if (total == 0) return;
   NtDesc* dd = ar.put(d.data(), d.size(), s);
-  if (mark) mark(true);
-  HIPCHK(nt_launch(conj, dd, (int)d.size(), total, gemm_blocks(), s, kind));
-  if (mark) mark(false);
+  HIPCHK(nt_launch(prec, conj, dd, (int)d.size(), 0, total, 0, 1, nullptr, gemm_blocks(), s, kind));
 }
 
-// Upload big-tile descriptors once and launch them for each K segment.
-void run_big(Arena& ar, int prec, int conj, std::vector<NtDesc>& d, int nseg, hipStream_t s, int kind,
-             const LaunchMark& mark = nullptr) {
-  long long total = big_plan(d.data(), (int)d.size());
+// U^q = R^q W^q on bf16 operands.  The single-bf16 product runs the ring
+// pipeline (one workgroup a CU), the bf16x3 one the two-stage pipeline with
+// two workgroups a CU, whatever the tiling (1000-k shape, 14400 pair rows:
+// single bf16 0.274 of bf16 peak on the ring against 0.255; bf16x3 0.127
+// against 0.119 for the triangular factor product, 0.146 against 0.141 for
+// the full one).
+void run_u16(Arena& ar, int prec, std::vector<NtDesc>& d, hipStream_t s) {
+  const long long total = x3_plan(d.data(), (int)d.size());
   if (total == 0) return;
   NtDesc* dd = ar.put(d.data(), d.size(), s);
-  for (int seg = 0; seg < nseg; ++seg) {
-    if (mark) mark(true);
-    // the ring pipeline of the bf16 kernels (one workgroup a CU): for U^q =
-    // R^q W^q (kind 2) in single bf16, for the contraction when the tiling
-    // asks for one workgroup a CU.  bf16x3 U^q runs the two-stage pipeline
-    // with two workgroups a CU whatever the tiling (1000-k shape, 14400 pair
-    // rows: 0.127 against 0.119 of bf16 peak for the triangular factor
-    // product, 0.146 against 0.141 for the full one; single bf16 0.274 on
-    // the ring against 0.255).
-    const bool ring = (prec == 2 || prec == 3) && ring_supported(conj, kind) &&
-                      ((kind == 2 && prec == 3) || (kind == 3 && t_wg_per_cu == 1));
-    const int blocks = ring ? max_gemm_blocks() / 8
-                            : (prec == 2 && kind == 2 ? max_gemm_blocks() / 8 * 2 : gemm_blocks());
-    HIPCHK(prec == 2   ? x3_launch(conj, dd, (int)d.size(), total, blocks, seg, s, kind, ring)
-           : prec == 3 ? x1_launch(conj, dd, (int)d.size(), total, blocks, seg, s, kind, ring)
-                       : big_launch(prec, conj, dd, (int)d.size(), total, gemm_blocks(), seg, s, kind));
-    if (mark) mark(false);
+  const bool ring = prec == 3;
+  const int cu = max_gemm_blocks() / 8;
+  HIPCHK(x3_launch(prec, dd, (int)d.size(), 0, total, 0, 1, nullptr, ring ? cu : 2 * cu, s, 2, ring));
+}
+
+// How the tiles of a fragment contraction of `total` tiles and nch chunks of
+// its K range are launched: the first `whole` tiles (a whole number of rounds
+// of two workgroups a CU) by one workgroup each, chunk after chunk; the rest,
+// which would leave the last round nearly empty for every chunk, one unit a
+// tile and chunk, each with a partial block of its own that the fold adds to C
+// in chunk order (the same sums in the same order).  part_bytes: room for
+// partial blocks; a rest that fills three quarters of a round, or no room for
+// the blocks of two chunks, keeps every tile whole.
+struct Split {
+  long long whole = 0, rest = 0;
+  int per = 0;                            // chunks of the rest per launch
+};
+Split plan_split(long long total, int nch, long long tile_bytes, int blocks, long long part_bytes) {
+  Split p;
+  const long long round = std::min<long long>(blocks, max_gemm_blocks() / 8 * 2);
+  p.whole = total / round * round;
+  p.rest = total - p.whole;
+  const long long fit = p.rest > 0 ? part_bytes / (p.rest * tile_bytes) : 0;
+  if (nch < 2 || p.rest * 4 >= round * 3 || fit < 2) {
+    p.whole = total;
+    p.rest = 0;
+    return p;
   }
+  const int passes = (int)((nch + fit - 1) / fit);
+  p.per = (nch + passes - 1) / passes;
+  return p;
+}
+// Partial blocks are worth at most this much room.
+constexpr long long PART_BYTES_MAX = 512LL << 20;
+// Room the partial blocks of such a contraction would take (0: none needed).
+long long part_bytes_wanted(long long total, int nch, long long tile_bytes, int blocks) {
+  const Split p = plan_split(total, nch, tile_bytes, blocks, PART_BYTES_MAX);
+  return p.rest * p.per * tile_bytes;
+}
+
+// The fragment contraction (eq. (19)): nch chunks of the K range, d.cseg
+// segments each (mixed: one).  mark brackets every GEMM launch.
+void run_contraction(Arena& ar, int prec, std::vector<NtDesc>& d, int nch, hipStream_t s, char* part,
+                     long long part_bytes, const LaunchMark& mark) {
+  const bool bf = prec >= 2;
+  const int tile = bf ? X3_TILE : NT_TILE;
+  const long long total = bf ? x3_plan(d.data(), (int)d.size()) : nt_plan(d.data(), (int)d.size());
+  if (total == 0) return;
+  NtDesc* dd = ar.put(d.data(), d.size(), s);
+  const int nd = (int)d.size();
+  // the ring pipeline of the bf16 kernels when the tiling asks for one
+  // workgroup a CU
+  const bool ring = bf && t_wg_per_cu == 1;
+  const int blocks = ring ? max_gemm_blocks() / 8 : gemm_blocks();
+  const long long tb = (long long)tile * tile * sizeof(cplx);
+  const Split sp = plan_split(total, nch, tb, blocks, part ? part_bytes : 0);
+  auto go = [&](long long t0, long long nt, int c0, int nc, cplx* pt) {
+    if (mark) mark(true);
+    HIPCHK(bf ? x3_launch(prec, dd, nd, t0, nt, c0, nc, pt, blocks, s, 3, ring)
+              : nt_launch(prec, 2, dd, nd, t0, nt, c0, nc, pt, blocks, s, 3));
+    if (mark) mark(false);
+  };
+  if (sp.whole) {
+    // FP64: every chunk in one launch; mixed: a launch per chunk, so that the
+    // tiles that run together stay on the same K range
+    if (prec == 0) go(0, sp.whole, 0, nch, nullptr);
+    else
+      for (int c = 0; c < nch; ++c) go(0, sp.whole, c, 1, nullptr);
+  }
+  if (sp.rest)
+    for (int c = 0; c < nch; c += sp.per) {
+      const int nc = std::min(sp.per, nch - c);
+      go(sp.whole, sp.rest, c, nc, (cplx*)part);
+      HIPCHK(nt_fold_launch(dd, nd, tile, bf ? X3_TILE : nt_part_tile(sp.rest, nc), sp.whole, sp.rest, c, nc,
+                            (const cplx*)part, s));
+    }
 }
 
 NtDesc mknt(const void* A, long long lda, const void* B, long long ldb, void* C, long long ldc,
@@ -1173,6 +1233,37 @@ size_t request_bytes(isdf_ctx c, int nf, bool host_out, int prec) {
   return batch_bytes(c, one, prec, (int)std::min<long long>(MAX_PAIR_BLOCKS, np));
 }
 
+// Chunks of the contraction's K range (the classes): n chunks of `per` classes
+// (the last may have fewer).  A function of the context and the precision
+// alone, because the sums over the chunks' partial sums (FP64) follow them.
+// Mixed: the groups of eri_qgroup classes whose FP32 sums stay separate, in
+// balanced groups.  FP64: at most 8, of at least 512 values of K, so that a
+// contraction of few tiles has work for every CU.
+struct EriChunks {
+  int n, per;
+};
+EriChunks eri_chunks(isdf_ctx c, int prec) {
+  const int nh = c->nh;
+  int n;
+  if (prec == 0) n = (int)std::max<long long>(1, std::min<long long>(std::min(8, nh), (long long)nh * c->nip / 512));
+  else n = (nh + c->eri_qgroup - 1) / c->eri_qgroup;
+  const int per = (nh + n - 1) / n;
+  return {(nh + per - 1) / per, per};
+}
+
+// Room that partial blocks of the (unblocked) contraction of these fragments
+// are worth.
+long long part_wanted(isdf_ctx c, const std::vector<FragIn>& fr, int prec) {
+  const int tile = prec >= 2 ? X3_TILE : NT_TILE;
+  long long total = 0;
+  for (const FragIn& f : fr) {
+    const long long t = ((long long)f.nf * f.nf + tile - 1) / tile;
+    total += t * (t + 1) / 2;
+  }
+  const int blocks = prec >= 2 && t_wg_per_cu == 1 ? max_gemm_blocks() / 8 : gemm_blocks();
+  return part_bytes_wanted(total, eri_chunks(c, prec).n, (long long)tile * tile * sizeof(cplx), blocks);
+}
+
 // Device tables of one pair transform over pair range [p0, p0 + np) of each
 // fragment of the batch (np = all pairs when the batch is unblocked).
 struct PairTables {
@@ -1188,7 +1279,9 @@ struct PairTables {
 // Enqueue the whole fragment pipeline of one batch on ws.stream.  capture:
 // the stream is being captured into a graph (no synchronisation; the
 // workspace and arena were sized by an eager pass).
-void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn>& fr, bool timed,
+// cap: workspace bytes the batch may use (its plan fits; partial blocks of the
+// contraction may take more of it).
+void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn>& fr, bool timed, size_t cap,
                    int nb = 1, bool capture = false) {
   if (!c->kernel_ready) throw Fail{ISDF_E_STATE, "isdf_coulomb_kernel must run before fragment ERIs"};
   if (nb > 1 && fr.size() != 1) throw Fail{ISDF_E_INVALID, "pair blocking applies to one fragment"};
@@ -1197,14 +1290,24 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
   const int nk = c->nk, norb = c->norb, nip = c->nip;
   const long long ld = c->ld_ip;
   BatchPlan p = plan_batch(c, fr, prec, nb);
+  // room behind the plan's regions for partial blocks of the contraction
+  const long long want = p.nb == 1 ? part_wanted(c, fr, prec) : 0;
   if (!capture) {
     ws.arena.reset(s);
     ws.arena.reserve(p.arena_bytes);
+    if (!ws.mem.fixed && p.bytes + want > ws.mem.bytes && p.bytes + want <= cap) {
+      try {
+        ws.mem.ensure(p.bytes + want);
+      } catch (const Fail&) {
+        // the plan alone, below
+      }
+    }
     ws.mem.ensure(p.bytes);
   } else {
     if (p.bytes > ws.mem.bytes) throw Fail{ISDF_E_INVALID, "captured batch larger than its workspace"};
     ws.arena.used = 0;
   }
+  const long long part_bytes = want > 0 ? std::min<long long>(want, (long long)(ws.mem.bytes - p.bytes)) : 0;
   char* base = ws.mem.as<char>();
   cplx* Call = (cplx*)(base + p.off_c);
   cplx* Tf = (cplx*)(base + p.off_tf);
@@ -1389,36 +1492,36 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     d[0].sB_bat = (long long)nip * ld;
     d[0].epi = prec == 0 ? 0 : 3;
     d[0].npad = (int)ld;
-    if (prec == 0) run_nt(ws.arena, 0, d, s, 2);
-    else run_big(ws.arena, prec, 0, d, 1, s, 2);
+    if (prec < 2) run_nt(ws.arena, 0, d, s, 2, prec);
+    else run_u16(ws.arena, prec, d, s);
   };
   // (pq|rs) = sum_q sum_J U^q_{(pq),J} conj(R^q_{(sr),J})  (eq. (19), R^{-q}_{rs} = conj R^q_{sr}).
   // The term of -q is the conjugate of that of q with (pq) -> (qp) and
   // (sr) -> (rs) (R^{-q}_{pq} = conj R^q_{qp}, W^{-q} = conj W^q), so the
   // contraction runs over one q per class {q, -q} (weight 1/2 where q = -q,
   // folded into W):  G_f[(pq)][(sr)] = sum_{h, J} U^h_{(pq),J} conj(R^h_{(sr),J})
-  // in FP64 (lower triangle; one grouped persistent launch over all
-  // fragments, or one per block pair), then (pq|rs) = G[(pq)][(sr)] +
-  // conj(G[(qp)][(rs)]) by the scatter.  FP64 path: FP64 sum over the
-  // classes inside the kernel; mixed: one launch per group of classes (one
-  // contiguous K range per row, FP32 sums inside), FP64 sum over the groups.
+  // in FP64 (lower triangle; grouped persistent launches over all
+  // fragments, or per block pair), then (pq|rs) = G[(pq)][(sr)] +
+  // conj(G[(qp)][(rs)]) by the scatter.  The classes are summed in chunks
+  // (eri_chunks): FP64 inside a chunk in FP64, FP32 in the mixed precisions (one
+  // contiguous K range per row), FP64 over the chunks in every precision.
   const size_t sc = fmt_scalar(prec);
-  const int ngroup = (nh + c->eri_qgroup - 1) / c->eri_qgroup;
-  const int qgroup = (nh + ngroup - 1) / ngroup;       // balanced groups
+  const EriChunks ec = eri_chunks(c, prec);
   auto eri_desc = [&](const void* A, const void* B, cplx* C, long long ldc, int M, int N, int herm) {
     NtDesc g = mknt(A, (long long)nh * ld, B, (long long)nh * ld, C, ldc, M, N, nip);
     g.a_plane = g.b_plane = mplane;
     g.herm = herm;
+    g.epi = 1;
     if (prec == 0) {
       g.nseg = nh;
+      g.cseg = ec.per;
       g.sA_seg = g.sB_seg = ld;
-      g.epi = 0;
     } else {
-      g.Kseg = (int)(qgroup * ld);
-      g.nseg = (nh + qgroup - 1) / qgroup;
-      g.Klast = (int)((nh - (long long)(g.nseg - 1) * qgroup) * ld);
-      g.sA_seg = g.sB_seg = qgroup * ld;
-      g.epi = 1;
+      g.Kseg = (int)(ec.per * ld);
+      g.nseg = ec.n;
+      g.cseg = 1;
+      g.Klast = (int)((nh - (long long)(ec.n - 1) * ec.per) * ld);
+      g.sA_seg = g.sB_seg = ec.per * ld;
     }
     return g;
   };
@@ -1430,8 +1533,7 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
       else ws.timer.end("frag_eri_kernel", s);
     };
   auto eri_gemm = [&](std::vector<NtDesc>& d) {
-    if (prec == 0) run_nt(ws.arena, 2, d, s, 3, mark);
-    else run_big(ws.arena, prec, 2, d, d[0].nseg, s, 3, mark);
+    run_contraction(ws.arena, prec, d, ec.n, s, part_bytes > 0 ? base + p.bytes : nullptr, part_bytes, mark);
   };
   if (p.nb == 1) {
     if (timed) ws.timer.begin("frag_pair", s);
@@ -1552,7 +1654,7 @@ void enqueue_fragments(isdf_ctx c, Workspace& ws, int prec, const std::vector<Fr
         }
         ++j;
       }
-    enqueue_batch(c, ws, prec, sub, timed, nb);
+    enqueue_batch(c, ws, prec, sub, timed, cap, nb);
     i = j;
   }
 }
@@ -2186,7 +2288,7 @@ isdf_status isdf_fragment_eri(isdf_ctx ctx, isdf_precision prec, int32_t n_frag,
     const int forced = (int)((flags >> 8) & 0xFFu);
     if (forced > 1) {
       for (const FragIn& f : fr)
-        enqueue_batch(ctx, ctx->sync_ws, prec, std::vector<FragIn>(1, f), true,
+        enqueue_batch(ctx, ctx->sync_ws, prec, std::vector<FragIn>(1, f), true, sync_cap(ctx->sync_ws),
                       (int)std::min<long long>(forced, (long long)f.nf * f.nf));
     } else {
       enqueue_fragments(ctx, ctx->sync_ws, prec, fr, true, sync_cap(ctx->sync_ws));
@@ -2263,11 +2365,12 @@ isdf_status isdf_graph_create(isdf_ctx ctx, isdf_precision prec, int32_t n_frag,
     HIPCHK(hipStreamWaitEvent(g->ws.stream, g->after, 0));
     // eager pass: sizes the workspace and descriptor arena (no allocation may
     // happen under capture) and runs every launch once
-    enqueue_batch(ctx, g->ws, prec, fr, false);
+    const size_t cap = sync_cap(g->ws);
+    enqueue_batch(ctx, g->ws, prec, fr, false, cap);
     HIPCHK(hipStreamSynchronize(g->ws.stream));
     HIPCHK(hipStreamBeginCapture(g->ws.stream, hipStreamCaptureModeThreadLocal));
     try {
-      enqueue_batch(ctx, g->ws, prec, fr, false, 1, true);
+      enqueue_batch(ctx, g->ws, prec, fr, false, cap, 1, true);
     } catch (...) {
       hipGraph_t part = nullptr;
       (void)hipStreamEndCapture(g->ws.stream, &part);
@@ -2342,11 +2445,12 @@ isdf_status isdf_autotune(isdf_ctx ctx, isdf_precision prec, int32_t n_frag, con
         for (int w : wgs) {
           ctx->eri_qgroup = g;
           ctx->frag_wg_per_cu = w;
-          enqueue_batch(ctx, ctx->sync_ws, prec, fr, false);     // warm-up (sizes the workspace)
+          const size_t cap = sync_cap(ctx->sync_ws);
+          enqueue_batch(ctx, ctx->sync_ws, prec, fr, false, cap);     // warm-up (sizes the workspace)
           double ms = 1e300;
           for (int rep = 0; rep < 2; ++rep) {
             HIPCHK(hipEventRecord(e0, ctx->stream));
-            enqueue_batch(ctx, ctx->sync_ws, prec, fr, false);
+            enqueue_batch(ctx, ctx->sync_ws, prec, fr, false, cap);
             HIPCHK(hipEventRecord(e1, ctx->stream));
             HIPCHK(hipEventSynchronize(e1));
             float t = 0.f;

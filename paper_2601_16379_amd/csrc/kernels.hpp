@@ -61,49 +61,84 @@ struct NtDesc {
   int M, N, Kseg, nseg, Klast, batch;
   int tiles_m, tiles_n, tiles_per_batch;
   int herm, epi;
-  int cseg;               // FP64: K segments per chunk (0 = all)
+  int cseg;               // K segments per chunk (0 = all)
   int npad;               // epi 3: columns written (zeros from N on); 0 = ldc
   int ktri;               // B[n][k] = 0 for k < n: the mixed kernels start each column
                           // tile's K range at its first column (FP64 reads the zeros)
   long long tile_begin;
 };
 long long nt_plan(NtDesc* d, int n);
-// FP64 products (gemm_nt.hip).  conj: bit 0 conjugates A, bit 1 conjugates B;
-// kind names the call site in profiles: 0 generic, 1 V^q, 2 U^q, 3 fragment contraction
-constexpr int NT_SMALL_TILES = 768;   // fewer 64 x 64 tiles than this run as 32 x 32 ones
-hipError_t nt_launch(int conj, const NtDesc* descs_dev, int ndesc, long long total, int max_blocks, hipStream_t s,
-                     int kind = 0);
+// One tile of a descriptor list: descriptor, batch, tile row and column.
+struct NtTile {
+  int desc, b, tm, tn;
+};
+__device__ inline int isqrt_floor(long long x) {
+  long long r = (long long)sqrt((double)x);
+  while (r * r > x) --r;
+  while ((r + 1) * (r + 1) <= x) ++r;
+  return (int)r;
+}
+__device__ inline NtTile nt_tile(const NtDesc* descs, int ndesc, long long t) {
+  int lo = 0, hi = ndesc - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (descs[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
+  }
+  const long long local = t - descs[lo].tile_begin;
+  const int per = descs[lo].tiles_per_batch;
+  NtTile r;
+  r.desc = lo;
+  r.b = (int)(local / per);
+  const int lt = (int)(local - (long long)r.b * per);
+  if (descs[lo].herm) {
+    r.tm = (isqrt_floor(8LL * lt + 1) - 1) / 2;
+    r.tn = lt - r.tm * (r.tm + 1) / 2;
+  } else {
+    r.tm = lt / descs[lo].tiles_n;
+    r.tn = lt - r.tm * descs[lo].tiles_n;
+  }
+  return r;
+}
+// FP64 and FP32 products (gemm_nt.hip, prec 0 and 1; FP32: kinds 2 and 3),
+// planned with nt_plan (64 x 64 tiles): tiles [t0, t0 + nt) of the list,
+// chunks [c0, c0 + nc) of the K segments.  part: null, or room for nt * nc
+// partial tiles (64 x 64 c128 each), one per tile and chunk, which the
+// launch leaves there instead of updating C (nt_fold_launch adds them).
+// conj: bit 0 conjugates A, bit 1 conjugates B; kind names the call site in
+// profiles: 0 generic, 1 V^q, 2 U^q, 3 fragment contraction
+constexpr int NT_TILE = 64;
+constexpr int NT_SMALL_TILES = 768;   // fewer tiles than this run as 32 x 32 ones
+hipError_t nt_launch(int prec, int conj, const NtDesc* descs_dev, int ndesc, long long t0, long long nt, int c0,
+                     int nc, cplx* part, int max_blocks, hipStream_t s, int kind = 0);
+// Edge of the partial blocks such a launch with part leaves (64 or 32).
+int nt_part_tile(long long nt, int nc);
+// C (epi 1, FP64) += the partial blocks of tiles [t0, t0 + nt), chunk after
+// chunk from c0 on (chunk 0 stores): the same sums in the same order as a
+// launch without part.  tile: edge of the list's tiles (64 or 128), edge:
+// of the partial blocks.
+hipError_t nt_fold_launch(const NtDesc* descs_dev, int ndesc, int tile, int edge, long long t0, long long nt, int c0,
+                          int nc, const cplx* part, hipStream_t s);
 
-// Large-tile (128x128, 512 threads) NT GEMM for the mixed precisions (1, 2):
-// one K segment `seg` per launch; epi 1 accumulates the FP32 partials in an
-// FP64 c128 output (segment 0 stores, later segments add), epi 3 stores the
-// split format; herm 2 computes lower tiles only (entries above the diagonal
-// inside diagonal tiles are left unwritten).
-long long big_plan(NtDesc* d, int n);
-hipError_t big_launch(int prec, int conj, const NtDesc* descs_dev, int ndesc, long long total,
-                      int max_blocks, int seg, hipStream_t s, int kind = 0);
-// Fill the upper triangles of nbat Hermitian n x n matrices (pitch ld,
-// batch stride bat) from their computed lower triangles.
-hipError_t herm_fill_launch(cplx* c, int n, long long ld, long long bat, int nbat, hipStream_t s);
+// Tile counts of the bf16 products (128 x 128 tiles)
+constexpr int X3_TILE = 128;
+long long x3_plan(NtDesc* d, int n);
 // G[(pq)][(sr)] (Hermitian, lower triangle computed; the contraction over the
 // classes {q, -q}) -> eri[p][q][r][s] = G[(pq)][(sr)] + conj(G[(qp)][(rs)])
 // for n fragments in one launch: fragment f reads e + eoff[f] and writes
 // eri[f]; nf, eoff, eri are device arrays
 hipError_t eri_scatter_batch_launch(const cplx* e, const long long* eoff, cplx* const* eri, const int* nf,
                                     int n, int maxnf, hipStream_t s);
-// bf16x3 NT GEMM on the 32x32x16 matrix cores (128 x 128 tiles, 256
-// threads, direct-to-LDS operand copies): same descriptors and epilogues as
-// big_launch for precision 2; plan with big_plan.
+// NT GEMM on bf16 operands with the 32x32x16 matrix cores (128 x 128 tiles,
+// direct-to-LDS operand copies): F = 2 the hi+lo format (bf16x3), F = 3 single
+// bf16; plan with x3_plan.  Kind 2 without conjugation (U^q) and kind 3 with
+// B conjugated (the contraction) only.  Tiles [t0, t0 + nt), K segments
+// [seg0, seg0 + nseg); part: null (nseg = 1: epi 1 accumulates the FP32
+// partial sums of the segment in C, epi 3 stores the operand format), or room
+// for nt * nseg partial tiles (128 x 128 c128 each), as in nt_launch.
 // ring: the ring pipeline (four LDS stages, one workgroup a CU, the next
-// stage's fragments read during the MFMAs; same results bit for bit), for
-// the call sites ring_supported accepts.
-hipError_t x3_launch(int conj, const NtDesc* descs_dev, int ndesc, long long total, int max_blocks, int seg,
-                     hipStream_t s, int kind, bool ring = false);
-// The same kernel on the single-bf16 operand format (fmt 3): kind 2 without
-// conjugation (U^q) and kind 3 with B conjugated (the contraction) only.
-hipError_t x1_launch(int conj, const NtDesc* descs_dev, int ndesc, long long total, int max_blocks, int seg,
-                     hipStream_t s, int kind, bool ring = false);
-bool ring_supported(int conj, int kind);
+// stage's fragments read during the MFMAs; same results bit for bit).
+hipError_t x3_launch(int fmt, const NtDesc* descs_dev, int ndesc, long long t0, long long nt, int seg0, int nseg,
+                     cplx* part, int max_blocks, hipStream_t s, int kind, bool ring = false);
 // mixed-precision fragment contraction: classes {q, -q} summed in FP32 per
 // launch (one contiguous K range of the classes of a group, the classes
 // split into balanced groups), FP64 across launches.  The initial tiling of
