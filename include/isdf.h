@@ -139,8 +139,9 @@ isdf_status isdf_create(isdf_ctx* out, const double* lattice, const int32_t grid
  * pivots: start from the residual d(x) = M(x, x) = rho(x)^2; at each step take
  * the point p of largest residual (lowest index among equals), form the
  * factor column L(x) = (M(x, p) - sum of the previous columns' L(x) L(p)) /
- * sqrt(d(p)), lower d by L(x)^2 and set d(p) = 0.  M is never formed: a step
- * reads the orbitals once.  FP64.
+ * sqrt(d(p)), lower d by L(x)^2 and set d(p) = 0.  M is never formed: a pass
+ * over the orbitals forms the columns of a pivot and of the points next in
+ * line, which serve later steps.  FP64.
  *   grid, kmesh, n_orb  as isdf_create (n_ip <= N_g).
  *   orbitals   c128 [N_k][n_orb][N_g], host or device (ISDF_INPUT_DEVICE),
  *              the layout isdf_create takes.
@@ -151,8 +152,8 @@ isdf_status isdf_create(isdf_ctx* out, const double* lattice, const int32_t grid
  *              its decay measures how well the first i points span the pair
  *              products).
  *   hip_stream  stream of the launches (0 = null stream).
- * Synchronous; device workspace n_ip N_g 8 bytes plus a few grid-sized
- * vectors (and a copy of host orbitals), freed on return.  Errors
+ * Synchronous; device workspace n_ip N_g 8 bytes plus a few tens of
+ * grid-sized vectors (and a copy of host orbitals), freed on return.  Errors
  * (message from isdf_last_error(NULL)): ISDF_E_INVALID for bad sizes or
  * pointers; ISDF_E_NUMERIC when a step's largest residual is not positive
  * (the products span fewer than n_ip grid columns, or the orbitals are not

@@ -2090,25 +2090,32 @@ isdf_status isdf_select_points(const int32_t grid[3], const int32_t kmesh[3], in
       }
     }
     const SelPlan pl = sel_plan(nrows, ng);
-    DevBuf phi, part, lf, d, bv, bi, piv, dmax;
+    DevBuf phi, part, lf, d, bv, bi, piv, dmax, state;
     const cplx* ph = (const cplx*)orbitals;
     if (!(flags & ISDF_INPUT_DEVICE)) {
       phi.alloc(sizeof(cplx) * nrows * ng);
       HIPCHK(hipMemcpyAsync(phi.p, orbitals, sizeof(cplx) * nrows * ng, hipMemcpyHostToDevice, s));
       ph = phi.as<cplx>();
     }
-    part.alloc(sizeof(cplx) * pl.nslice * ng);
     lf.alloc(sizeof(double) * n_ip * ng);
     d.alloc(sizeof(double) * ng);
-    bv.alloc(sizeof(double) * pl.xblocks);
-    bi.alloc(sizeof(long long) * pl.xblocks);
+    bv.alloc(sizeof(double) * pl.ublocks);
+    bi.alloc(sizeof(long long) * pl.ublocks);
     piv.alloc(sizeof(int) * n_ip);
     dmax.alloc(sizeof(double) * n_ip);
-    HIPCHK(sel_start_launch(pl, ph, nrows, ng, part.as<cplx>(), d.as<double>(), bv.as<double>(),
-                            bi.as<long long>(), piv.as<int>(), dmax.as<double>(), s));
-    for (int i = 0; i < n_ip; ++i)
-      HIPCHK(sel_step_launch(pl, ph, nrows, ng, part.as<cplx>(), lf.as<double>(), d.as<double>(), bv.as<double>(),
-                             bi.as<long long>(), piv.as<int>(), dmax.as<double>(), i, i + 1 < n_ip, s));
+    state.alloc(SEL_STATE_BYTES);
+    // several columns a pass where there is room for their partial sums
+    int ncols = SEL_COLS;
+    try {
+      part.alloc(sizeof(cplx) * pl.nslice * ng * ncols);
+    } catch (const Fail&) {
+      ncols = 1;
+      part.alloc(sizeof(cplx) * pl.nslice * ng);
+    }
+    const SelBufs sb{part.as<cplx>(), lf.as<double>(), d.as<double>(), bv.as<double>(), bi.as<long long>(),
+                     piv.as<int>(), dmax.as<double>(), state.p};
+    HIPCHK(sel_start_launch(pl, ph, nrows, ng, sb, s));
+    for (int i = 0; i < n_ip; ++i) HIPCHK(sel_step_launch(pl, ph, nrows, ng, sb, ncols, i, s));
     std::vector<int32_t> ph_piv(n_ip);
     std::vector<double> ph_dmax(n_ip);
     HIPCHK(hipMemcpyAsync(ph_piv.data(), piv.p, sizeof(int) * n_ip, hipMemcpyDeviceToHost, s));

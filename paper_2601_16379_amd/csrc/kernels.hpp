@@ -350,23 +350,36 @@ hipError_t nonfinite_launch(const cplx* x, long long n, int* flag, hipStream_t s
 // ---------------------------------------------------------------------------
 // interpolation-point selection (pivoted Cholesky of the pair products)
 // ---------------------------------------------------------------------------
-// Launch shape of one step: xblocks workgroups of 256 grid points, each of
-// the nslice row slices rows_per rows long.
+// Launch shapes: a pass over the orbitals, xblocks workgroups of 512 grid
+// points, each of the nslice row slices rows_per rows long; an update,
+// ublocks workgroups of 64 grid points.
 struct SelPlan {
   int xblocks = 0;
+  int ublocks = 0;
   int nslice = 0;
   long long rows_per = 0;
 };
 SelPlan sel_plan(long long nrows, long long ng);
-// phi [nrows][ng]; part [nslice][ng]; d [ng]; bv, bi [xblocks]; piv, dmax
-// [n_ip].  Start: d = rho^2, piv[0] / dmax[0] = first pivot and its residual.
-hipError_t sel_start_launch(const SelPlan& pl, const cplx* phi, long long nrows, long long ng, cplx* part, double* d,
-                            double* bv, long long* bi, int* piv, double* dmax, hipStream_t s);
-// Step `step`: column lf[step][ng] and residual update; with pick_next the
-// pivot of step + 1 into piv / dmax.
-hipError_t sel_step_launch(const SelPlan& pl, const cplx* phi, long long nrows, long long ng, cplx* part, double* lf,
-                           double* d, double* bv, long long* bi, int* piv, double* dmax, int step, bool pick_next,
-                           hipStream_t s);
+// Columns of G formed by one pass (or 1).
+constexpr int SEL_COLS = 8;
+constexpr long long SEL_STATE_BYTES = 256;
+// part [ncols][nslice][ng]; lf [n_ip][ng]; d [ng]; bv, bi [ublocks]; piv,
+// dmax [n_ip]; state SEL_STATE_BYTES.
+struct SelBufs {
+  cplx* part;
+  double *lf, *d, *bv;
+  long long* bi;
+  int* piv;
+  double* dmax;
+  void* state;
+};
+// Start: d = rho^2 and its block maxima.
+hipError_t sel_start_launch(const SelPlan& pl, const cplx* phi, long long nrows, long long ng, const SelBufs& b,
+                            hipStream_t s);
+// Step `step`: its pivot and residual into piv / dmax, column lf[step][ng],
+// residual update.  ncols: SEL_COLS or 1, the same for all steps.
+hipError_t sel_step_launch(const SelPlan& pl, const cplx* phi, long long nrows, long long ng, const SelBufs& b,
+                           int ncols, int step, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // k-point Hartree-Fock Coulomb matrix helpers
