@@ -23,7 +23,7 @@
 //   sel_update -- sums the slices of the pivot's column, forms the column of
 //                 the factor and the residual, writes L_i and d, and reduces
 //                 its block's d to (max, argmax).
-// Bound: a pass reads the orbitals once (N_k N_orb N_g 16 bytes), and is
+// Bound: a pass reads the orbitals once (N_k N_orb N_g 16 bytes); one
 // with 8 columns takes 184 us against 152 for one (872 MB).  A greedy
 // step takes the largest residual; the point next in line is usually taken
 // soon, so a pass serves several steps: 8 columns leave about one pass in five

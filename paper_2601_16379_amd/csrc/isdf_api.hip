@@ -160,6 +160,8 @@ struct Arena {
   void reset(hipStream_t s) {
     HIPCHK(hipStreamSynchronize(s));
     used = 0;
+    deferring = false;
+    todo.clear();
   }
   // Capacity for `bytes` of puts (each put adds at most 255 bytes of
   // alignment); the stream has drained (reset) and nothing was put yet.
@@ -175,6 +177,30 @@ struct Arena {
     if (host.bytes < cap) host.ensure(cap);
     if (dev.bytes < cap) dev.ensure(cap);
   }
+  // Deferred passes: between defer() and run() puts only fill the host copy
+  // and launch() keeps its functions; run() copies the whole pass's
+  // descriptors at once and then calls the functions in order.  A fragment
+  // batch puts 15 small tables: one copy instead of 15 (about 4 us of GPU time
+  // and a gap each) between its kernels.
+  bool deferring = false;
+  size_t first = 0;
+  std::vector<std::function<void()>> todo;
+  void defer() {
+    deferring = true;
+    first = used;
+    todo.clear();
+  }
+  template <class F> void launch(F f) {
+    if (deferring) todo.emplace_back(std::move(f));
+    else f();
+  }
+  void run(hipStream_t s) {
+    deferring = false;
+    if (used > first)
+      HIPCHK(hipMemcpyAsync((char*)dev.p + first, host_ptr() + first, used - first, hipMemcpyHostToDevice, s));
+    for (auto& f : todo) f();
+    todo.clear();
+  }
   template <class T> T* put(const T* src, size_t n, hipStream_t s) {
     size_t bytes = n * sizeof(T);
     size_t off = (used + 255) & ~size_t(255);
@@ -186,7 +212,7 @@ struct Arena {
       off = 0;
     }
     memcpy(host_ptr() + off, src, bytes);
-    HIPCHK(hipMemcpyAsync((char*)dev.p + off, host_ptr() + off, bytes, hipMemcpyHostToDevice, s));
+    if (!deferring) HIPCHK(hipMemcpyAsync((char*)dev.p + off, host_ptr() + off, bytes, hipMemcpyHostToDevice, s));
     used = off + bytes;
     return reinterpret_cast<T*>((char*)dev.p + off);
   }
@@ -223,7 +249,8 @@ void run_gemm(Arena& ar, int prec, int layout, std::vector<GemmDesc>& d, hipStre
   long long total = gemm_plan(d.data(), (int)d.size());
   if (total == 0) return;
   GemmDesc* dd = ar.put(d.data(), d.size(), s);
-  HIPCHK(gemm_launch(prec, layout, dd, (int)d.size(), total, gemm_blocks(), s));
+  const int n = (int)d.size(), blocks = gemm_blocks();
+  ar.launch([=] { HIPCHK(gemm_launch(prec, layout, dd, n, total, blocks, s)); });
 }
 
 // mark(true) / mark(false) bracket each kernel launch when given (kernel timing)
@@ -234,7 +261,8 @@ void run_nt(Arena& ar, int conj, std::vector<NtDesc>& d, hipStream_t s, int kind
   const long long total = nt_plan(d.data(), (int)d.size());
   if (total == 0) return;
   NtDesc* dd = ar.put(d.data(), d.size(), s);
-  HIPCHK(nt_launch(prec, conj, dd, (int)d.size(), 0, total, 0, 1, nullptr, gemm_blocks(), s, kind));
+  const int n = (int)d.size(), blocks = gemm_blocks();
+  ar.launch([=] { HIPCHK(nt_launch(prec, conj, dd, n, 0, total, 0, 1, nullptr, blocks, s, kind)); });
 }
 
 // U^q = R^q W^q on bf16 operands.  The single-bf16 product runs the ring
@@ -249,7 +277,8 @@ void run_u16(Arena& ar, int prec, std::vector<NtDesc>& d, hipStream_t s) {
   NtDesc* dd = ar.put(d.data(), d.size(), s);
   const bool ring = prec == 3;
   const int cu = max_gemm_blocks() / 8;
-  HIPCHK(x3_launch(prec, dd, (int)d.size(), 0, total, 0, 1, nullptr, ring ? cu : 2 * cu, s, 2, ring));
+  const int n = (int)d.size();
+  ar.launch([=] { HIPCHK(x3_launch(prec, dd, n, 0, total, 0, 1, nullptr, ring ? cu : 2 * cu, s, 2, ring)); });
 }
 
 // How the tiles of a fragment contraction of `total` tiles and nch chunks of
@@ -303,26 +332,28 @@ void run_contraction(Arena& ar, int prec, std::vector<NtDesc>& d, int nch, hipSt
   const int blocks = ring ? max_gemm_blocks() / 8 : gemm_blocks();
   const long long tb = (long long)tile * tile * sizeof(cplx);
   const Split sp = plan_split(total, nch, tb, blocks, part ? part_bytes : 0);
-  auto go = [&](long long t0, long long nt, int c0, int nc, cplx* pt) {
-    if (mark) mark(true);
-    HIPCHK(bf ? x3_launch(prec, dd, nd, t0, nt, c0, nc, pt, blocks, s, 3, ring)
-              : nt_launch(prec, 2, dd, nd, t0, nt, c0, nc, pt, blocks, s, 3));
-    if (mark) mark(false);
-  };
-  if (sp.whole) {
-    // FP64: every chunk in one launch; mixed: a launch per chunk, so that the
-    // tiles that run together stay on the same K range
-    if (prec == 0) go(0, sp.whole, 0, nch, nullptr);
-    else
-      for (int c = 0; c < nch; ++c) go(0, sp.whole, c, 1, nullptr);
-  }
-  if (sp.rest)
-    for (int c = 0; c < nch; c += sp.per) {
-      const int nc = std::min(sp.per, nch - c);
-      go(sp.whole, sp.rest, c, nc, (cplx*)part);
-      HIPCHK(nt_fold_launch(dd, nd, tile, bf ? X3_TILE : nt_part_tile(sp.rest, nc), sp.whole, sp.rest, c, nc,
-                            (const cplx*)part, s));
+  ar.launch([=] {
+    auto go = [&](long long t0, long long nt, int c0, int nc, cplx* pt) {
+      if (mark) mark(true);
+      HIPCHK(bf ? x3_launch(prec, dd, nd, t0, nt, c0, nc, pt, blocks, s, 3, ring)
+                : nt_launch(prec, 2, dd, nd, t0, nt, c0, nc, pt, blocks, s, 3));
+      if (mark) mark(false);
+    };
+    if (sp.whole) {
+      // FP64: every chunk in one launch; mixed: a launch per chunk, so that the
+      // tiles that run together stay on the same K range
+      if (prec == 0) go(0, sp.whole, 0, nch, nullptr);
+      else
+        for (int c = 0; c < nch; ++c) go(0, sp.whole, c, 1, nullptr);
     }
+    if (sp.rest)
+      for (int c = 0; c < nch; c += sp.per) {
+        const int nc = std::min(sp.per, nch - c);
+        go(sp.whole, sp.rest, c, nc, (cplx*)part);
+        HIPCHK(nt_fold_launch(dd, nd, tile, bf ? X3_TILE : nt_part_tile(sp.rest, nc), sp.whole, sp.rest, c, nc,
+                              (const cplx*)part, s));
+      }
+  });
 }
 
 NtDesc mknt(const void* A, long long lda, const void* B, long long ldb, void* C, long long ldc,
@@ -1307,6 +1338,11 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     if (p.bytes > ws.mem.bytes) throw Fail{ISDF_E_INVALID, "captured batch larger than its workspace"};
     ws.arena.used = 0;
   }
+  ws.arena.defer();
+  auto tick = [&](const char* name, bool on) {
+    if (timed)
+      ws.arena.launch([&ws, s, name, on] { on ? ws.timer.begin(name, s) : ws.timer.end(name, s); });
+  };
   const long long part_bytes = want > 0 ? std::min<long long>(want, (long long)(ws.mem.bytes - p.bytes)) : 0;
   char* base = ws.mem.as<char>();
   cplx* Call = (cplx*)(base + p.off_c);
@@ -1338,10 +1374,14 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     }
     maxnf = std::max(maxnf, f.nf);
   }
-  HIPCHK(copy_cols_batch_launch(ws.arena.put(srcs.data(), srcs.size(), s), Call, nk, norb,
-                                ws.arena.put(p.nf.data(), p.nf.size(), s),
-                                ws.arena.put(p.col.data(), p.col.size(), s), (int)fr.size(), maxnf, p.ncol, s));
-  if (timed) ws.timer.begin("frag_t", s);
+  const cplx* const* d_src = ws.arena.put(srcs.data(), srcs.size(), s);
+  const int* d_nf = ws.arena.put(p.nf.data(), p.nf.size(), s);
+  const int* d_col = ws.arena.put(p.col.data(), p.col.size(), s);
+  const int nfrag = (int)fr.size(), ncol = p.ncol;
+  ws.arena.launch([=] {
+    HIPCHK(copy_cols_batch_launch(d_src, Call, nk, norb, d_nf, d_col, nfrag, maxnf, ncol, s));
+  });
+  tick("frag_t", true);
   // T^k_{pI} = sum_mu C^k_{mu p} X^k_{I mu}   (Algorithm 2, stored [k][p][I])
   {
     std::vector<GemmDesc> d(1);
@@ -1368,9 +1408,9 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     // the register pair transform of the mixed precisions reads psi as
     // complex FP32 (in the U region while it is free, or its own region)
     if (p.psi32) a.out32 = psi32;
-    HIPCHK(kconv_launch(a, s));
+    ws.arena.launch([=] { HIPCHK(kconv_launch(a, s)); });
   }
-  if (timed) ws.timer.end("frag_t", s);
+  tick("frag_t", false);
   const int nh = c->nh;
   const long long rows = p.nb == 1 ? p.ptot : p.pb;            // pair rows of the M / U regions
   const long long mplane = (long long)nh * rows * ld;
@@ -1434,8 +1474,6 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     t.nitems = ioff.back();
     return t;
   };
-  const int* d_nf = ws.arena.put(p.nf.data(), p.nf.size(), s);
-  const int* d_col = ws.arena.put(p.col.data(), p.col.size(), s);
   // R^q_{I,pq} = N_k^{-1/2} sum_R exp(-iq.R) conj(psi_p) psi_q   (eq. (20)),
   // in the GEMM operand format of the precision, pair-major: row (pair) holds
   // the nh blocks of ld columns (class of q, I), so that the contraction over
@@ -1473,7 +1511,7 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
       a.nfrag = (int)fr.size();
       a.nitems = t.nitems;
     }
-    HIPCHK(pair_launch(a, s));
+    ws.arena.launch([=] { HIPCHK(pair_launch(a, s)); });
   };
   // U^q_{P,J} = sum_I R^q_{P,I} W^q_{IJ}   (eq. (19), first contraction)
   // With the factor (wfac, mixed precisions) the same product with W^T
@@ -1536,13 +1574,13 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     run_contraction(ws.arena, prec, d, ec.n, s, part_bytes > 0 ? base + p.bytes : nullptr, part_bytes, mark);
   };
   if (p.nb == 1) {
-    if (timed) ws.timer.begin("frag_pair", s);
+    tick("frag_pair", true);
     pair_transform(make_tables(0, 0), Mq);
-    if (timed) ws.timer.end("frag_pair", s);
-    if (timed) ws.timer.begin("frag_u", s);
+    tick("frag_pair", false);
+    tick("frag_u", true);
     u_gemm(Mq, p.ptot, Uq);
-    if (timed) ws.timer.end("frag_u", s);
-    if (timed) ws.timer.begin("frag_eri", s);
+    tick("frag_u", false);
+    tick("frag_eri", true);
     std::vector<NtDesc> d;
     for (size_t f = 0; f < fr.size(); ++f) {
       const int nf2 = p.nf[f] * p.nf[f];
@@ -1566,45 +1604,47 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     }
     for (int i = 0; i < p.nb; ++i) {
       const long long i0 = (long long)i * p.pb, ni = std::min<long long>(p.pb, nf2 - i0);
-      if (timed) ws.timer.begin("frag_pair", s);
+      tick("frag_pair", true);
       pair_transform(tabs[i], Mq);
-      if (timed) ws.timer.end("frag_pair", s);
-      if (timed) ws.timer.begin("frag_u", s);
+      tick("frag_pair", false);
+      tick("frag_u", true);
       u_gemm(Mq, ni, Uq);
-      if (timed) ws.timer.end("frag_u", s);
+      tick("frag_u", false);
       for (int j = 0; j <= i; ++j) {
         const long long j0 = (long long)j * p.pb, nj = std::min<long long>(p.pb, nf2 - j0);
         // column operand: R_j, or with the factor Y_j (Y_i for j == i; else
         // Y_j = R_j L into the first R region, whose R_i is no longer read)
         const char* rj = yform ? Uq : Mq;
         if (j != i) {
-          if (timed) ws.timer.begin("frag_pair", s);
+          tick("frag_pair", true);
           pair_transform(tabs[j], Mq2);
-          if (timed) ws.timer.end("frag_pair", s);
+          tick("frag_pair", false);
           rj = Mq2;
           if (yform) {
-            if (timed) ws.timer.begin("frag_u", s);
+            tick("frag_u", true);
             u_gemm(Mq2, nj, Mq);
-            if (timed) ws.timer.end("frag_u", s);
+            tick("frag_u", false);
             rj = Mq;
           }
         }
-        if (timed) ws.timer.begin("frag_eri", s);
+        tick("frag_eri", true);
         std::vector<NtDesc> d(1, eri_desc(Uq, rj, acc + i0 * nf2 + j0, nf2, (int)ni, (int)nj, j == i ? 2 : 0));
         eri_gemm(d);
-        if (timed) ws.timer.end("frag_eri", s);
+        tick("frag_eri", false);
       }
     }
-    if (timed) ws.timer.begin("frag_eri", s);
+    tick("frag_eri", true);
   }
   {
     std::vector<cplx*> outs(fr.size());
     for (size_t f = 0; f < fr.size(); ++f)
       outs[f] = (fr[f].flags & ISDF_FRAG_DEVICE) ? (cplx*)fr[f].eri : Est + p.eoff[f];
-    HIPCHK(eri_scatter_batch_launch(acc, ws.arena.put(p.aoff.data(), p.aoff.size(), s),
-                                    ws.arena.put(outs.data(), outs.size(), s), d_nf, (int)fr.size(), maxnf, s));
+    const long long* d_off = ws.arena.put(p.aoff.data(), p.aoff.size(), s);
+    cplx* const* d_out = ws.arena.put(outs.data(), outs.size(), s);
+    ws.arena.launch([=] { HIPCHK(eri_scatter_batch_launch(acc, d_off, d_out, d_nf, nfrag, maxnf, s)); });
   }
-  if (timed) ws.timer.end("frag_eri", s);
+  tick("frag_eri", false);
+  ws.arena.run(s);
   for (size_t f = 0; f < fr.size(); ++f) {
     if (fr[f].flags & ISDF_FRAG_DEVICE) continue;
     const long long e4 = (long long)p.nf[f] * p.nf[f] * p.nf[f] * p.nf[f];

@@ -107,7 +107,7 @@ __device__ inline NtTile nt_tile(const NtDesc* descs, int ndesc, long long t) {
 // conj: bit 0 conjugates A, bit 1 conjugates B; kind names the call site in
 // profiles: 0 generic, 1 V^q, 2 U^q, 3 fragment contraction
 constexpr int NT_TILE = 64;
-constexpr int NT_SMALL_TILES = 768;   // fewer tiles than this run as 32 x 32 ones
+constexpr int NT_SMALL_TILES = 512;   // fewer tiles than this (two a CU) run as 32 x 32 ones
 hipError_t nt_launch(int prec, int conj, const NtDesc* descs_dev, int ndesc, long long t0, long long nt, int c0,
                      int nc, cplx* part, int max_blocks, hipStream_t s, int kind = 0);
 // Edge of the partial blocks such a launch with part leaves (64 or 32).
