@@ -167,103 +167,167 @@ __global__ void bchol_setup_kernel(const cplx* __restrict__ pi, cplx* a, int* pe
   }
 }
 
-// Unblocked Cholesky of the diagonal block A[jb:jb+nb, jb:jb+nb] in LDS.
+// Unblocked Cholesky of the diagonal block A[jb:jb+nb, jb:jb+nb].
+// Bound: the chain of 64 columns, each a square root, a reciprocal and an
+// update.  The block is held in registers, lane i of every wave its row i, wave
+// w the columns w + 4 e; a column goes through LDS to the other waves, one
+// barrier a column (two buffers in turn).  Each entry takes the same updates in
+// the same order as in LDS with three barriers a column: 93 -> 35 us a block.
+template <int J>
+__device__ inline bool diag_steps(cplx (&d)[16], cplx (&col)[2][CHOL_NB], int* bad, double tol, int nb, int lane,
+                                  int w) {
+  if constexpr (J < CHOL_NB) {
+    if (J >= nb) return true;
+    constexpr int EJ = J / 4, WJ = J % 4;
+    cplx* cj = col[J & 1];
+    if (w == WJ) {
+      const double djj = __shfl(d[EJ].x, J);
+      if (!(djj > tol) || !(djj > 0.0)) {      // the same for the whole wave
+        if (lane == 0) *bad = 1;
+      } else {
+        const double r = sqrt(djj);
+        d[EJ] = lane == J ? cmk(r, 0.0) : cscale(d[EJ], 1.0 / r);
+        cj[lane] = d[EJ];
+      }
+    }
+    __syncthreads();
+    if (*bad) return false;
+    const cplx li = cj[lane];
+#pragma unroll
+    for (int e = EJ; e < 16; ++e) {
+      if (e == EJ && w <= WJ) continue;
+      const cplx lc = cj[4 * e + w];
+      d[e].x -= fma(li.x, lc.x, li.y * lc.y);
+      d[e].y -= fma(li.y, lc.x, -(li.x * lc.y));
+    }
+    return diag_steps<J + 1>(d, col, bad, tol, nb, lane, w);
+  }
+  return true;
+}
+
 __global__ __launch_bounds__(256) void bchol_diag_kernel(cplx* a, cplx* lt, const double* dmax, int* flag,
                                                          int n, int jb, double rtol) {
-  constexpr int NB = CHOL_NB;
-  __shared__ cplx D[NB][NB + 1];
+  __shared__ cplx col[2][CHOL_NB];
   __shared__ int s_bad;
   const int q = blockIdx.x;
   if (flag[q]) return;
   const long long nn = (long long)n * n;
   cplx* A = a + q * nn;
   cplx* L = lt + q * nn;
-  const int nb = (n - jb) < NB ? (n - jb) : NB;
-  for (int idx = threadIdx.x; idx < nb * nb; idx += blockDim.x) {
-    const int i = idx / nb, j = idx - (idx / nb) * nb;
-    D[i][j] = A[(long long)(jb + i) * n + jb + j];
+  const int nb = (n - jb) < CHOL_NB ? (n - jb) : CHOL_NB;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  cplx d[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int c = 4 * e + w;
+    d[e] = (lane < nb && c <= lane) ? A[(long long)(jb + lane) * n + jb + c] : cmk(0.0, 0.0);
   }
   if (threadIdx.x == 0) s_bad = 0;
   __syncthreads();
-  const double tol = rtol * dmax[q];
-  for (int j = 0; j < nb; ++j) {
-    const double djj = D[j][j].x;
-    if (!(djj > tol) || !(djj > 0.0)) {   // uniform: every thread reads the same value
-      if (threadIdx.x == 0) s_bad = 1;
-      break;
-    }
-    const double d = sqrt(djj);
-    __syncthreads();
-    for (int i = j + threadIdx.x; i < nb; i += blockDim.x) D[i][j] = (i == j) ? cmk(d, 0.0) : cscale(D[i][j], 1.0 / d);
-    __syncthreads();
-    const int w = nb - j - 1;
-    for (int idx = threadIdx.x; idx < w * w; idx += blockDim.x) {
-      const int i = j + 1 + idx / w, c = j + 1 + idx - (idx / w) * w;
-      if (c > i) continue;
-      const cplx li = D[i][j], lc = D[c][j];
-      D[i][c].x -= li.x * lc.x + li.y * lc.y;
-      D[i][c].y -= li.y * lc.x - li.x * lc.y;
-    }
-    __syncthreads();
-  }
-  __syncthreads();
-  if (s_bad) {
+  if (!diag_steps<0>(d, col, &s_bad, rtol * dmax[q], nb, lane, w)) {
     if (threadIdx.x == 0) flag[q] = 1;
     return;
   }
-  for (int idx = threadIdx.x; idx < nb * nb; idx += blockDim.x) {
-    const int i = idx / nb, j = idx - (idx / nb) * nb;
-    if (j > i) continue;
-    A[(long long)(jb + i) * n + jb + j] = D[i][j];
-    L[(long long)(jb + j) * n + jb + i] = D[i][j];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int c = 4 * e + w;
+    if (lane >= nb || c > lane) continue;
+    A[(long long)(jb + lane) * n + jb + c] = d[e];
+    L[(long long)(jb + c) * n + jb + lane] = d[e];
   }
 }
 
-// L21 = A21 L11^{-H}: row i solves x L11^H = a, x_c = (a_c - sum_{d<c} x_d conj(L11[c][d])) / L11[c][c].
-__global__ __launch_bounds__(64) void bchol_panel_kernel(cplx* a, cplx* lt, const int* flag, int n, int jb) {
-  constexpr int NB = CHOL_NB;
-  __shared__ cplx L11[NB][NB + 1];
-  __shared__ cplx X[64][NB + 1];
+// Forward substitution with a 64 x 64 lower triangle for 64 right hand sides,
+//   x_c = (a_c - sum_{d<c} op(L[c][d]) x_d) / L[c][c],  d ascending,
+// op the conjugate for CJ; unknowns at or past rb are zero.  Bound: the chain of
+// 64 unknowns.  256 threads, four lanes (a quad) a right hand side, 8 unknowns
+// at a time, two a lane in registers: the earlier unknowns' products first
+// (T[d][c] = L[c][d], X and the reciprocals of the diagonal in LDS, the reads of
+// several d in flight), then the 8 in turn, each sent through the quad by DPP.
+// A block of the factor's panel 112-220 -> 35 us, a diagonal block's inverse
+// 152-250 -> 29 us (one lane a right hand side, one unknown at a time).
+struct Tri64 {
+  cplx T[CHOL_NB][CHOL_NB];
+  cplx X[64][CHOL_NB + 1];
+  double rinv[CHOL_NB];
+};
+// the triangle at jb from lt (L transposed); nb rows and columns of it
+__device__ inline void load_tri(Tri64& t, const cplx* lt, int n, int jb, int nb) {
+  const int c = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+  for (int d = w; d < CHOL_NB; d += 4)
+    t.T[d][c] = d <= c && c < nb ? lt[(long long)(jb + d) * n + jb + c] : cmk(0.0, 0.0);
+  if (w == 0) t.rinv[c] = c < nb ? 1.0 / lt[(long long)(jb + c) * (n + 1)].x : 0.0;
+}
+template <int K> __device__ inline cplx quad_bcast(cplx v) {
+  auto one = [](double x) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, K * 0x55, 0xf, 0xf, true);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), K * 0x55, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (unsigned long long)lo | ((unsigned long long)hi << 32));
+  };
+  return cmk(one(v.x), one(v.y));
+}
+// s -= op(l) x, the roundings written out so that every caller has the same
+template <bool CJ>
+__device__ inline void tri_sub(cplx& s, const cplx l, const cplx x) {
+  if (CJ) {
+    s.x -= fma(x.x, l.x, x.y * l.y);
+    s.y -= fma(x.y, l.x, -(x.x * l.y));
+  } else {
+    s.x -= fma(l.x, x.x, -(l.y * x.y));
+    s.y -= fma(l.y, x.x, l.x * x.y);
+  }
+}
+template <bool CJ, int V>
+__device__ inline void tri_step(Tri64& t, cplx (&acc)[2], int c0, int rb, int row, int g) {
+  if constexpr (V < 8) {
+    const cplx x = quad_bcast<V / 2>(c0 + V < rb ? cscale(acc[V & 1], t.rinv[c0 + V]) : cmk(0.0, 0.0));
+    if (g == V / 2) t.X[row][c0 + V] = x;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (2 * g + u > V) tri_sub<CJ>(acc[u], t.T[c0 + V][c0 + 2 * g + u], x);
+    tri_step<CJ, V + 1>(t, acc, c0, rb, row, g);
+  }
+}
+template <bool CJ>
+__device__ inline void tri_solve64(Tri64& t, int rb) {
+  const int row = threadIdx.x >> 2, g = threadIdx.x & 3;
+  for (int c0 = 0; c0 < rb; c0 += 8) {
+    cplx acc[2] = {t.X[row][c0 + 2 * g], t.X[row][c0 + 2 * g + 1]};
+#pragma unroll 8
+    for (int d = 0; d < c0; ++d) {
+      const cplx x = t.X[row][d];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) tri_sub<CJ>(acc[u], t.T[d][c0 + 2 * g + u], x);
+    }
+    tri_step<CJ, 0>(t, acc, c0, rb, row, g);
+  }
+}
+
+// L21 = A21 L11^{-H}: row i solves x L11^H = a.
+__global__ __launch_bounds__(256) void bchol_panel_kernel(cplx* a, cplx* lt, const int* flag, int n, int jb) {
+  __shared__ Tri64 s;
   const int q = blockIdx.y;
   if (flag[q]) return;
   const long long nn = (long long)n * n;
   cplx* A = a + q * nn;
   cplx* L = lt + q * nn;
-  const int nb = (n - jb) < NB ? (n - jb) : NB;
-  const int r0 = jb + nb + blockIdx.x * 64;
-  if (r0 >= n) return;
+  const int r0 = jb + CHOL_NB + blockIdx.x * 64;       // the panel's blocks are whole
   const int nr = (n - r0) < 64 ? (n - r0) : 64;
-  for (int idx = threadIdx.x; idx < nb * nb; idx += blockDim.x) {
-    const int i = idx / nb, j = idx - (idx / nb) * nb;
-    L11[i][j] = A[(long long)(jb + i) * n + jb + j];
-  }
-  for (int idx = threadIdx.x; idx < nr * nb; idx += blockDim.x) {
-    const int i = idx / nb, j = idx - (idx / nb) * nb;
-    X[i][j] = A[(long long)(r0 + i) * n + jb + j];
-  }
+  const int t = threadIdx.x & 63, w = threadIdx.x >> 6;
+  load_tri(s, L, n, jb, CHOL_NB);
+#pragma unroll
+  for (int i = w; i < 64; i += 4) s.X[i][t] = i < nr ? A[(long long)(r0 + i) * n + jb + t] : cmk(0.0, 0.0);
   __syncthreads();
-  const int t = threadIdx.x;
-  if (t < nr) {
-    for (int c = 0; c < nb; ++c) {
-      cplx acc = X[t][c];
-      for (int d = 0; d < c; ++d) {
-        const cplx x = X[t][d], l = L11[c][d];
-        // acc -= x * conj(l)
-        acc.x -= x.x * l.x + x.y * l.y;
-        acc.y -= x.y * l.x - x.x * l.y;
-      }
-      X[t][c] = cscale(acc, 1.0 / L11[c][c].x);
-    }
-  }
+  tri_solve64<true>(s, CHOL_NB);
   __syncthreads();
-  for (int idx = threadIdx.x; idx < nr * nb; idx += blockDim.x) {
-    const int i = idx / nb, j = idx - (idx / nb) * nb;
-    A[(long long)(r0 + i) * n + jb + j] = X[i][j];
-  }
-  for (int idx = threadIdx.x; idx < nr * nb; idx += blockDim.x) {
-    const int j = idx / nr, i = idx - (idx / nr) * nr;   // coalesced along i for lt rows
-    L[(long long)(jb + j) * n + r0 + i] = X[i][j];
-  }
+#pragma unroll
+  for (int i = w; i < 64; i += 4)
+    if (i < nr) A[(long long)(r0 + i) * n + jb + t] = s.X[i][t];
+#pragma unroll
+  for (int j = w; j < CHOL_NB; j += 4)
+    if (t < nr) L[(long long)(jb + j) * n + r0 + t] = s.X[t][j];   // coalesced along the rows
 }
 
 __global__ void zero_kernel(cplx* x, long long n) {
@@ -312,7 +376,7 @@ hipError_t bchol_panel_launch(cplx* a, cplx* lt, const int* flag, int n, int nq,
   const int nb = (n - jb) < CHOL_NB ? (n - jb) : CHOL_NB;
   const int rows = n - jb - nb;
   if (rows <= 0) return hipSuccess;
-  hipLaunchKernelGGL(bchol_panel_kernel, dim3((rows + 63) / 64, nq), dim3(64), 0, s, a, lt, flag, n, jb);
+  hipLaunchKernelGGL(bchol_panel_kernel, dim3((rows + 63) / 64, nq), dim3(256), 0, s, a, lt, flag, n, jb);
   return hipGetLastError();
 }
 
@@ -350,36 +414,32 @@ __global__ __launch_bounds__(256) void tri_setup_kernel(const cplx* __restrict__
   }
 }
 
-// Diagonal block at jb: Y_bb = L_bb^{-1} by forward substitution, one thread
-// per column, the block in LDS.  Written transposed into yt
-// (yt[jb+c][jb+i] = Y_bb[i][c]) and row-major into yd[q] (64 x 64).
-__global__ __launch_bounds__(64) void tri_inv_diag_kernel(const cplx* __restrict__ lrow,
-                                                          const int* __restrict__ rank, cplx* yt,
-                                                          cplx* yd, int n, int jb) {
-  __shared__ cplx Ls[64][65];
-  __shared__ cplx Ys[64][65];
-  const int q = blockIdx.x;
+// Diagonal blocks: Y_bb = L_bb^{-1}, one right hand side per column, every
+// block of every matrix at once.  Written transposed into yt
+// (yt[jb+c][jb+i] = Y_bb[i][c]) and row-major over the diagonal block of
+// lrow (which nothing reads any more).
+__global__ __launch_bounds__(256) void tri_inv_diag_kernel(const cplx* __restrict__ lt, const int* __restrict__ rank,
+                                                           cplx* lrow, cplx* yt, int n) {
+  __shared__ Tri64 s;
+  const int q = blockIdx.y, jb = blockIdx.x * CHOL_NB;
   const long long nn = (long long)n * n;
-  const int nb = (n - jb) < 64 ? (n - jb) : 64;
+  const int nb = (n - jb) < CHOL_NB ? (n - jb) : CHOL_NB;
   int rb = rank[q] - jb;
   rb = rb < 0 ? 0 : (rb > nb ? nb : rb);
-  const int c = threadIdx.x;
-  for (int i = 0; i < 64; ++i)
-    Ls[i][c] = (i < nb && c < nb) ? lrow[q * nn + (long long)(jb + i) * n + jb + c] : cmk(0.0, 0.0);
+  const int t = threadIdx.x & 63, w = threadIdx.x >> 6;
+  load_tri(s, lt + q * nn, n, jb, nb);
+#pragma unroll
+  for (int i = w; i < 64; i += 4) s.X[i][t] = cmk(i == t ? 1.0 : 0.0, 0.0);
   __syncthreads();
-  for (int i = 0; i < 64; ++i) {
-    cplx s = cmk(i == c ? 1.0 : 0.0, 0.0);
-    for (int k = c; k < i; ++k) {
-      const cplx l = Ls[i][k], y = Ys[k][c];
-      s.x -= l.x * y.x - l.y * y.y;
-      s.y -= l.x * y.y + l.y * y.x;
-    }
-    Ys[i][c] = (i < rb && c < rb && i >= c) ? cscale(s, 1.0 / Ls[i][i].x) : cmk(0.0, 0.0);
-  }
+  tri_solve64<false>(s, rb);
   __syncthreads();
-  for (int i = 0; i < 64; ++i) {
-    yd[(long long)q * 4096 + i * 64 + c] = Ys[i][c];
-    if (i < nb && c < nb) yt[q * nn + (long long)(jb + c) * n + jb + i] = Ys[i][c];
+  // X[c][i] = Y_bb[i][c]
+#pragma unroll
+  for (int k = w; k < CHOL_NB; k += 4) {
+    if (k >= nb || t >= nb) continue;
+    const bool in = k < rb && t < rb;
+    lrow[q * nn + (long long)(jb + k) * n + jb + t] = in && k >= t ? s.X[t][k] : cmk(0.0, 0.0);
+    yt[q * nn + (long long)(jb + k) * n + jb + t] = in && t >= k ? s.X[k][t] : cmk(0.0, 0.0);
   }
 }
 
@@ -393,9 +453,9 @@ hipError_t tri_setup_launch(const cplx* lt, const int* rank, cplx* lrow, cplx* y
   return hipGetLastError();
 }
 
-hipError_t tri_inv_diag_launch(const cplx* lrow, const int* rank, cplx* yt, cplx* yd, int n, int nq, int jb,
-                               hipStream_t s) {
+hipError_t tri_inv_diag_launch(const cplx* lt, const int* rank, cplx* lrow, cplx* yt, int n, int nq, hipStream_t s) {
   if (nq <= 0) return hipSuccess;
-  hipLaunchKernelGGL(tri_inv_diag_kernel, dim3(nq), dim3(64), 0, s, lrow, rank, yt, yd, n, jb);
+  hipLaunchKernelGGL(tri_inv_diag_kernel, dim3((n + CHOL_NB - 1) / CHOL_NB, nq), dim3(256), 0, s, lt, rank, lrow, yt,
+                     n);
   return hipGetLastError();
 }

@@ -735,10 +735,13 @@ void release_workspaces(isdf_ctx c) {
 void chol_blocked(Arena& ar, const cplx* in, cplx* A, cplx* lt, int* perm, int* rank, double* dmax, int* flag, int n,
                   int nq, double rtol, hipStream_t s) {
   const long long nn = (long long)n * n;
-  HIPCHK(bchol_setup_launch(in, A, perm, rank, dmax, flag, n, nq, s));
+  ar.defer();                            // one upload of the updates' descriptors
+  ar.launch([=] { HIPCHK(bchol_setup_launch(in, A, perm, rank, dmax, flag, n, nq, s)); });
   for (int jb = 0; jb < n; jb += CHOL_NB) {
-    HIPCHK(bchol_diag_launch(A, lt, dmax, flag, n, nq, jb, rtol, s));
-    HIPCHK(bchol_panel_launch(A, lt, flag, n, nq, jb, s));
+    ar.launch([=] {
+      HIPCHK(bchol_diag_launch(A, lt, dmax, flag, n, nq, jb, rtol, s));
+      HIPCHK(bchol_panel_launch(A, lt, flag, n, nq, jb, s));
+    });
     const int rest = n - jb - CHOL_NB;
     if (rest > 0) {
       std::vector<NtDesc> d(1);
@@ -751,6 +754,7 @@ void chol_blocked(Arena& ar, const cplx* in, cplx* A, cplx* lt, int* perm, int* 
       run_nt(ar, 2, d, s);
     }
   }
+  ar.run(s);
 }
 
 void do_fit(isdf_ctx c, int prec) {
@@ -858,38 +862,38 @@ void do_fit(isdf_ctx c, int prec) {
     // Y = L^{-1} by 64-row block rows (zero outside the rank block; stored
     // transposed in A = work2), G = Y^H Y (into work3), so that
     // P^T Pi^+ P = G on the rank block.  Scratch: the row-major factor in
-    // work3 (overwritten by G at the end), the block-row partials St [n][64]
-    // and the diagonal inverses in pinv_ws.
+    // work3 (the diagonal inverses take its diagonal blocks; overwritten by G at
+    // the end) and the block-row partials St [n][64] in pinv_ws.
     {
       cplx* Lrow = c->work3.as<cplx>();
       cplx* St = c->pinv_ws.as<cplx>();
-      cplx* Yd = St + (long long)nh * nip * 64;
       const long long nn = nip2(c);
-      HIPCHK(tri_setup_launch(c->lt.as<cplx>(), c->rank.as<int>(), Lrow, A, nip, nh, c->aux));
-      for (int jb = 0; jb < nip; jb += 64) {
+      const cplx* lt = c->lt.as<cplx>();
+      const int* rank = c->rank.as<int>();
+      hipStream_t aux = c->aux;
+      c->arena_aux.defer();
+      c->arena_aux.launch([=] {
+        HIPCHK(tri_setup_launch(lt, rank, Lrow, A, nip, nh, aux));
+        HIPCHK(tri_inv_diag_launch(lt, rank, Lrow, A, nip, nh, aux));
+      });
+      for (int jb = 64; jb < nip; jb += 64) {
         const int nb = std::min(64, nip - jb);
-        if (jb > 0) {
-          // St[n][m] = sum_{k < jb} Yt[n][k] L[jb+m][k]
-          std::vector<NtDesc> g(1);
-          g[0] = mknt(A, nip, Lrow + (long long)jb * nip, nip, St, 64, jb, nb, jb);
-          g[0].batch = nh;
-          g[0].sA_bat = g[0].sB_bat = nn;
-          g[0].sC_bat = (long long)nip * 64;
-          run_nt(c->arena_aux, 0, g, c->aux);
-        }
-        HIPCHK(tri_inv_diag_launch(Lrow, c->rank.as<int>(), A, Yd, nip, nh, jb, c->aux));
-        if (jb > 0) {
-          // Yt[n][jb+m] = Y[jb+m][n] = -sum_k St[n][k] Y_bb[m][k]
-          std::vector<NtDesc> g(1);
-          g[0] = mknt(St, 64, Yd, 64, A + jb, nip, jb, nb, nb);
-          g[0].batch = nh;
-          g[0].sA_bat = (long long)nip * 64;
-          g[0].sB_bat = 4096;
-          g[0].sC_bat = nn;
-          g[0].epi = 4;
-          run_nt(c->arena_aux, 0, g, c->aux);
-        }
+        // St[n][m] = sum_{k < jb} Yt[n][k] L[jb+m][k]
+        std::vector<NtDesc> g(1);
+        g[0] = mknt(A, nip, Lrow + (long long)jb * nip, nip, St, 64, jb, nb, jb);
+        g[0].batch = nh;
+        g[0].sA_bat = g[0].sB_bat = nn;
+        g[0].sC_bat = (long long)nip * 64;
+        run_nt(c->arena_aux, 0, g, c->aux);
+        // Yt[n][jb+m] = Y[jb+m][n] = -sum_k St[n][k] Y_bb[m][k]
+        g[0] = mknt(St, 64, Lrow + (long long)jb * (nip + 1), nip, A + jb, nip, jb, nb, nb);
+        g[0].batch = nh;
+        g[0].sA_bat = (long long)nip * 64;
+        g[0].sB_bat = g[0].sC_bat = nn;
+        g[0].epi = 4;
+        run_nt(c->arena_aux, 0, g, c->aux);
       }
+      c->arena_aux.run(c->aux);
     }
     std::vector<NtDesc> d(1);
     d[0] = mknt(A, nip, A, nip, c->work3.as<cplx>(), nip, nip, nip, nip);
