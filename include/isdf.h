@@ -448,7 +448,9 @@ isdf_status isdf_load(isdf_ctx* out, const char* path, void* hip_stream);
  *   j_out, k_out  c128 [N_k][n_orb][n_orb], either may be NULL (not computed).
  *   flags  ISDF_HF_DEVICE: dm, j_out, k_out are device pointers (else host).
  * Device workspace N_k N_IP^2 + N_k n_orb N_IP complex numbers (17.3 + 0.9 GB
- * at N_k = 1000, N_IP = 1040), freed on return; the idle workspace of
+ * at N_k = 1000, N_IP = 1040), kept by the context for the next such call up
+ * to 24 GiB and handed back when a device allocation of the library needs it,
+ * with the next isdf_create and with the context; the idle workspace of
  * isdf_fragment_eri is handed back first when the device is full.
  * Synchronous.  Errors: ISDF_E_STATE before isdf_coulomb_kernel,
  * ISDF_E_INVALID for null or (with ISDF_HF_DEVICE) non-device pointers and
@@ -482,7 +484,7 @@ isdf_status isdf_hf_jk(isdf_ctx ctx, const void* dm, void* j_out, void* k_out, u
  *   e_os_out    float64: E_OS.
  * Device workspace 2 N_k N_IP^2 + nh N_IP^2 complex numbers plus
  * N_k N_IP n_mo x 2 (34.6 + 8.7 + 1.7 GB at N_k = 1000, N_IP = 1040),
- * freed on return.  Synchronous.  Errors: ISDF_E_STATE before
+ * kept as isdf_hf_jk's.  Synchronous.  Errors: ISDF_E_STATE before
  * isdf_coulomb_kernel; ISDF_E_INVALID for null pointers, bad counts, energies
  * without a gap, negative or non-finite tau, more than 2048 k points;
  * ISDF_E_NOMEM, ISDF_E_DEVICE.
@@ -508,8 +510,8 @@ isdf_status isdf_sos_mp2(isdf_ctx ctx, const void* mo_coeff, const double* mo_en
  * chi^q(-iw) = chi^q(iw)^H), and its second-order term
  * (pi N_k)^-1 sum_q -1/2 Re tr[(chi W)^2], which is the opposite-spin MP2
  * energy.  chi^q(iw) is not Hermitian without time-reversal symmetry, so
- * Re ln det(1 - P) is taken as 1/2 ln det(A^H A), A = 1 - P, from a blocked
- * FP64 Cholesky factor; P, A^H A and the time convolutions are FP64 (MFMA for
+ * Re ln det(1 - P) is taken as 1/2 ln det(A A^H), A = 1 - P, from a blocked
+ * FP64 Cholesky factor; P, A A^H and the time convolutions are FP64 (MFMA for
  * the products).  One q per class {q, -q} (the -q term is the conjugate).
  * The frequencies are processed in batches that fit the device memory (the
  * time loop runs once per batch).
@@ -525,7 +527,7 @@ isdf_status isdf_sos_mp2(isdf_ctx ctx, const void* mo_coeff, const double* mo_en
  *   e_drpa_out  float64: E_dRPA;  e_second_out  float64 or NULL: the
  *               second-order term on the same grids.
  * Device workspace as isdf_sos_mp2 plus 3 nh N_IP^2 and, per frequency of a
- * batch, nh N_IP^2 complex numbers; freed on return.  Synchronous.  Errors:
+ * batch, nh N_IP^2 complex numbers; kept as isdf_hf_jk's.  Synchronous.  Errors:
  * as isdf_sos_mp2 (non-finite transform or weights: ISDF_E_INVALID);
  * ISDF_E_NUMERIC when 1 - chi W is singular; ISDF_E_NOMEM when not even one
  * frequency fits.

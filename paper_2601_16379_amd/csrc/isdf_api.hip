@@ -76,6 +76,85 @@ void* scratch_ptr(int device) {
   return ptr;
 }
 
+// Idle device buffers of the calls that take their workspace per call
+// (isdf_hf_jk, isdf_sos_mp2, isdf_drpa), kept by their context between calls:
+// allocating and freeing them cost more than the call (a device allocation of
+// memory that was freed shortly before waits while it is cleared, at about 10
+// GB/s: 0.1 to 0.9 s for the 2.9 GB of a Coulomb-exchange build on a 1000-k
+// mesh whose kernels take 7 ms).  At most POOL_BYTES_MAX a context; all pools
+// are handed back when a device allocation of this library fails, before a
+// context plans its buffers, and with their context.  Buffers in a pool are
+// not in use: a call returns its buffers after its stream has drained.
+constexpr size_t POOL_BYTES_MAX = (size_t)24 << 30;
+class IdlePool {
+ public:
+  IdlePool() {
+    std::lock_guard<std::mutex> lk(registry_mu());
+    registry().insert(this);
+  }
+  ~IdlePool() {
+    std::lock_guard<std::mutex> lk(registry_mu());
+    registry().erase(this);
+    drain();
+  }
+  // A buffer of at least `bytes` (and at most twice that), or null.
+  void* take(size_t bytes, size_t* got) {
+    std::lock_guard<std::mutex> lk(mu_);
+    size_t best = idle_.size();
+    for (size_t i = 0; i < idle_.size(); ++i)
+      if (idle_[i].second >= bytes && idle_[i].second <= 2 * bytes &&
+          (best == idle_.size() || idle_[i].second < idle_[best].second))
+        best = i;
+    if (best == idle_.size()) return nullptr;
+    void* p = idle_[best].first;
+    *got = idle_[best].second;
+    total_ -= *got;
+    idle_.erase(idle_.begin() + best);
+    return p;
+  }
+  // Keeps a buffer (false: no room for it).
+  bool give(void* p, size_t bytes) {
+    std::lock_guard<std::mutex> lk(mu_);
+    if (total_ + bytes > POOL_BYTES_MAX) return false;
+    idle_.emplace_back(p, bytes);
+    total_ += bytes;
+    return true;
+  }
+  void drain() {
+    std::lock_guard<std::mutex> lk(mu_);
+    for (auto& b : idle_) (void)hipFree(b.first);
+    idle_.clear();
+    total_ = 0;
+  }
+  size_t bytes() {
+    std::lock_guard<std::mutex> lk(mu_);
+    return total_;
+  }
+  // Hands back every context's idle buffers; true when there were any.
+  static bool drain_all() {
+    std::lock_guard<std::mutex> lk(registry_mu());
+    bool any = false;
+    for (IdlePool* p : registry()) {
+      any = any || p->bytes() > 0;
+      p->drain();
+    }
+    return any;
+  }
+
+ private:
+  static std::mutex& registry_mu() {
+    static std::mutex* m = new std::mutex();       // outlives every context
+    return *m;
+  }
+  static std::set<IdlePool*>& registry() {
+    static std::set<IdlePool*>* r = new std::set<IdlePool*>();
+    return *r;
+  }
+  std::mutex mu_;
+  std::vector<std::pair<void*, size_t>> idle_;
+  size_t total_ = 0;
+};
+
 // Device allocation that is freed with its owner.
 // A buffer attached to caller-provided memory (attach) never allocates or
 // frees: asking it for more than it holds is ISDF_E_NOMEM.
@@ -96,6 +175,10 @@ struct DevBuf {
     release();
     if (b == 0) return;
     hipError_t e = hipMalloc(&p, b);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      if (IdlePool::drain_all()) e = hipMalloc(&p, b);
+    }
     if (e != hipSuccess) {
       p = nullptr;
       (void)hipGetLastError();
@@ -540,6 +623,7 @@ struct isdf_ctx_s {
   Arena arena_aux;                      // descriptors of the second stream (chol, pinv)
   StageTimer timer;
   std::string err;
+  IdlePool pool;                        // workspace of hf_jk, sos_mp2 and drpa between calls
   // fragment workspace of the synchronous call
   Workspace sync_ws;
   // workspace of isdf_fragment_eri_static: attached to this device's copy of
@@ -620,6 +704,40 @@ struct Exclusive {
     c->cv.notify_all();
   }
 };
+
+// Workspace buffer of a synchronous call: from the context's idle buffers, to
+// which it returns (in order on the context's stream, like every later use).
+// When the device is full, the idle workspace of synchronous fragment calls is
+// handed back and the allocation tried once more.
+struct PoolBuf {
+  isdf_ctx c = nullptr;
+  void* p = nullptr;
+  size_t bytes = 0;
+  PoolBuf() = default;
+  PoolBuf(const PoolBuf&) = delete;
+  PoolBuf& operator=(const PoolBuf&) = delete;
+  ~PoolBuf() {
+    if (p && !c->pool.give(p, bytes)) (void)hipFree(p);
+  }
+  template <class T> T* as() const { return reinterpret_cast<T*>(p); }
+};
+void alloc_reclaim(isdf_ctx c, PoolBuf& b, size_t bytes) {
+  b.c = c;
+  if (bytes == 0) return;
+  if ((b.p = c->pool.take(bytes, &b.bytes)) != nullptr) return;
+  DevBuf d;
+  try {
+    d.alloc(bytes);
+  } catch (const Fail& f) {
+    if (f.st != ISDF_E_NOMEM) throw;
+    HIPCHK(hipStreamSynchronize(c->stream));
+    c->sync_ws.mem.release();
+    d.alloc(bytes);
+  }
+  b.p = d.p;
+  b.bytes = bytes;
+  d.p = nullptr;                         // now the pool buffer's
+}
 
 bool good_grid(int n) {
   if (n < 2 || n > 64) return false;
@@ -1657,14 +1775,15 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
 }
 
 // Memory a synchronous fragment call may use: what is free on the device
-// plus what the workspace already holds, less a margin.
-size_t sync_cap(const Workspace& ws) {
+// plus what the workspace already holds and the context's idle buffers (handed
+// back when the workspace cannot grow beside them), less a margin.
+size_t sync_cap(isdf_ctx c, const Workspace& ws) {
   size_t fr = 0, tot = 0;
   if (hipMemGetInfo(&fr, &tot) != hipSuccess) {
     (void)hipGetLastError();
     return ws.mem.bytes;
   }
-  const size_t avail = fr + ws.mem.bytes;
+  const size_t avail = fr + ws.mem.bytes + c->pool.bytes();
   const size_t margin = std::max<size_t>((size_t)1 << 28, avail / 16);
   return avail > margin ? avail - margin : 0;
 }
@@ -1932,6 +2051,7 @@ void setup_context(isdf_ctx c, const double* lattice, const int32_t grid[3], con
     const size_t per_class = (size_t)n_ip * ng * e;
     const size_t transient = 3 * m2 + (size_t)nk * n_ip * n_ip * e +
                              (size_t)nh * ((size_t)n_ip * 64 + 4096) * e + 2 * (size_t)nk * c->ri * c->rc * e;
+    IdlePool::drain_all();               // plan with all the memory there is
     size_t fr = 0, tot = 0;
     HIPCHK(hipMemGetInfo(&fr, &tot));
     const double avail = fr > transient ? (double)(fr - transient) : 0.0;
@@ -2339,10 +2459,10 @@ isdf_status isdf_fragment_eri(isdf_ctx ctx, isdf_precision prec, int32_t n_frag,
     const int forced = (int)((flags >> 8) & 0xFFu);
     if (forced > 1) {
       for (const FragIn& f : fr)
-        enqueue_batch(ctx, ctx->sync_ws, prec, std::vector<FragIn>(1, f), true, sync_cap(ctx->sync_ws),
+        enqueue_batch(ctx, ctx->sync_ws, prec, std::vector<FragIn>(1, f), true, sync_cap(ctx, ctx->sync_ws),
                       (int)std::min<long long>(forced, (long long)f.nf * f.nf));
     } else {
-      enqueue_fragments(ctx, ctx->sync_ws, prec, fr, true, sync_cap(ctx->sync_ws));
+      enqueue_fragments(ctx, ctx->sync_ws, prec, fr, true, sync_cap(ctx, ctx->sync_ws));
     }
     HIPCHK(hipStreamSynchronize(ctx->stream));
     std::lock_guard<std::mutex> lk(ctx->mu);
@@ -2416,7 +2536,7 @@ isdf_status isdf_graph_create(isdf_ctx ctx, isdf_precision prec, int32_t n_frag,
     HIPCHK(hipStreamWaitEvent(g->ws.stream, g->after, 0));
     // eager pass: sizes the workspace and descriptor arena (no allocation may
     // happen under capture) and runs every launch once
-    const size_t cap = sync_cap(g->ws);
+    const size_t cap = sync_cap(ctx, g->ws);
     enqueue_batch(ctx, g->ws, prec, fr, false, cap);
     HIPCHK(hipStreamSynchronize(g->ws.stream));
     HIPCHK(hipStreamBeginCapture(g->ws.stream, hipStreamCaptureModeThreadLocal));
@@ -2496,7 +2616,7 @@ isdf_status isdf_autotune(isdf_ctx ctx, isdf_precision prec, int32_t n_frag, con
         for (int w : wgs) {
           ctx->eri_qgroup = g;
           ctx->frag_wg_per_cu = w;
-          const size_t cap = sync_cap(ctx->sync_ws);
+          const size_t cap = sync_cap(ctx, ctx->sync_ws);
           enqueue_batch(ctx, ctx->sync_ws, prec, fr, false, cap);     // warm-up (sizes the workspace)
           double ms = 1e300;
           for (int rep = 0; rep < 2; ++rep) {
@@ -2732,20 +2852,6 @@ isdf_status isdf_destroy(isdf_ctx ctx) {
   return ISDF_OK;
 }
 
-// Device buffer for a synchronous call; when the device is full, the idle
-// workspace of synchronous fragment calls is handed back and the allocation
-// tried once more.
-static void alloc_reclaim(isdf_ctx c, DevBuf& b, size_t bytes) {
-  try {
-    b.alloc(bytes);
-  } catch (const Fail& f) {
-    if (f.st != ISDF_E_NOMEM) throw;
-    HIPCHK(hipStreamSynchronize(c->stream));
-    c->sync_ws.mem.release();
-    b.alloc(bytes);
-  }
-}
-
 isdf_status isdf_hf_jk(isdf_ctx ctx, const void* dm, void* j_out, void* k_out, uint32_t flags) {
   return guarded(ctx, [&] {
     if (!dm || (!j_out && !k_out)) throw Fail{ISDF_E_INVALID, "null density matrix or no output"};
@@ -2768,7 +2874,7 @@ isdf_status isdf_hf_jk(isdf_ctx ctx, const void* dm, void* j_out, void* k_out, u
     }
     const size_t mb = (size_t)nk * norb * norb * sizeof(cplx);
     const long long nn = (long long)nip * nip, on = (long long)norb * nip, oo = (long long)norb * norb;
-    DevBuf dmd, jd, kd, rho, zb, nv, vv;
+    PoolBuf dmd, jd, kd, rho, zb, nv, vv;
     const cplx* P = (const cplx*)dm;
     cplx* J = (cplx*)j_out;
     cplx* K = (cplx*)k_out;
@@ -2965,7 +3071,7 @@ isdf_status isdf_sos_mp2(isdf_ctx ctx, const void* mo_coeff, const double* mo_en
     hipStream_t s = c->stream;
     const long long nn = (long long)nip * nip;
     const int nblk = std::max(1, std::min(64, (2048 + nh - 1) / nh));
-    DevBuf cd, ed, y, yo, yv, bo, bv, t1, part;
+    PoolBuf cd, ed, y, yo, yv, bo, bv, t1, part;
     const cplx* C = (const cplx*)mo_coeff;
     if (!dev) {
       alloc_reclaim(c, cd, sizeof(cplx) * (size_t)nk * norb * n_mo);
@@ -3004,16 +3110,16 @@ isdf_status isdf_sos_mp2(isdf_ctx ctx, const void* mo_coeff, const double* mo_en
       // T1 = W chi, T2 = chit W (FP64 MFMA), tr[W chi W chit] = sum T1 o conj(T2)
       c->timer.begin("mp2_wchi", s);
       {
-        std::vector<GemmDesc> d(1);
-        d[0] = mkdesc(c->w.as<cplx>(), nip, bv.as<cplx>(), nip, t1.as<cplx>(), nip, nip, nip, nip);
+        // chi and W Hermitian: a right operand's column k is the conjugate of its row k
+        std::vector<NtDesc> d(1);
+        d[0] = mknt(c->w.p, nip, bv.p, nip, t1.p, nip, nip, nip, nip);
         d[0].batch = nh;
         d[0].sA_bat = d[0].sB_bat = d[0].sC_bat = nn;
-        run_gemm(c->arena, 0, GEMM_B_KN, d, s);
-        std::vector<GemmDesc> d2(1);
-        d2[0] = mkdesc(bo.as<cplx>(), nip, c->w.as<cplx>(), nip, bv.as<cplx>(), nip, nip, nip, nip);
-        d2[0].batch = nh;
-        d2[0].sA_bat = d2[0].sB_bat = d2[0].sC_bat = nn;
-        run_gemm(c->arena, 0, GEMM_B_KN, d2, s);
+        run_nt(c->arena, 2, d, s);
+        d[0] = mknt(bo.p, nip, c->w.p, nip, bv.p, nip, nip, nip, nip);
+        d[0].batch = nh;
+        d[0].sA_bat = d[0].sB_bat = d[0].sC_bat = nn;
+        run_nt(c->arena, 2, d, s);
       }
       c->timer.end("mp2_wchi", s);
       c->timer.begin("mp2_trace", s);
@@ -3061,7 +3167,7 @@ isdf_status isdf_drpa(isdf_ctx ctx, const void* mo_coeff, const double* mo_energ
     hipStream_t s = c->stream;
     const long long nn = (long long)nip * nip, hn = (long long)nh * nn;
     const int ntile = drpa_trace2_tiles(nip);
-    DevBuf cd, ed, y, yo, yv, bo, bv, pm, gm, lt, perm, rank, dmax, flag, tr, tr2, ld, ph, chiw;
+    PoolBuf cd, ed, y, yo, yv, bo, bv, pm, gm, lt, perm, rank, dmax, flag, tr, tr2, ld, ph, chiw;
     const cplx* C = (const cplx*)mo_coeff;
     if (!dev) {
       alloc_reclaim(c, cd, sizeof(cplx) * (size_t)nk * norb * n_mo);
@@ -3091,10 +3197,11 @@ isdf_status isdf_drpa(isdf_ctx ctx, const void* mo_coeff, const double* mo_energ
     size_t fr = 0, tot = 0;
     HIPCHK(hipMemGetInfo(&fr, &tot));
     const long long per_w = hn * (long long)sizeof(cplx);
-    int nbw = (int)std::min<long long>(n_omega, (long long)(0.9 * (double)fr) / per_w);
+    int nbw = (int)std::min<long long>(n_omega, (long long)(0.9 * (double)(fr + c->pool.bytes())) / per_w);
     if (nbw < 1) {
       HIPCHK(hipStreamSynchronize(s));
       c->sync_ws.mem.release();
+      c->pool.drain();
       HIPCHK(hipMemGetInfo(&fr, &tot));
       nbw = (int)std::min<long long>(n_omega, (long long)(0.9 * (double)fr) / per_w);
     }
@@ -3135,14 +3242,15 @@ isdf_status isdf_drpa(isdf_ctx ctx, const void* mo_coeff, const double* mo_energ
         c->arena.reset(s);
         c->arena.reserve((size_t)1 << 20);
         cplx* chi = chiw.as<cplx>() + (long long)m * hn;
-        // P = chi W; tr P, tr P^2; A = 1 - P; G = A^H A = L L^H; ln|det A|^2 = ln det G
+        // P = chi W; tr P, tr P^2; A = 1 - P; G = A A^H = L L^H; ln|det A|^2 = ln det G
         c->timer.begin("drpa_p", s);
         {
-          std::vector<GemmDesc> d(1);
-          d[0] = mkdesc(chi, nip, c->w.as<cplx>(), nip, pm.as<cplx>(), nip, nip, nip, nip);
+          // W Hermitian: P[m][n] = sum_k chi[m][k] conj(W[n][k])
+          std::vector<NtDesc> d(1);
+          d[0] = mknt(chi, nip, c->w.p, nip, pm.p, nip, nip, nip, nip);
           d[0].batch = nh;
           d[0].sA_bat = d[0].sB_bat = d[0].sC_bat = nn;
-          run_gemm(c->arena, 0, GEMM_B_KN, d, s);
+          run_nt(c->arena, 2, d, s);
         }
         HIPCHK(drpa_trace_launch(pm.as<cplx>(), nip, nh, tr.as<cplx>(), s));
         HIPCHK(drpa_trace2_launch(pm.as<cplx>(), nip, nh, tr2.as<cplx>(), s));
@@ -3150,12 +3258,12 @@ isdf_status isdf_drpa(isdf_ctx ctx, const void* mo_coeff, const double* mo_energ
         c->timer.end("drpa_p", s);
         c->timer.begin("drpa_logdet", s);
         {
-          std::vector<GemmDesc> d(1);
-          d[0] = mkdesc(pm.as<cplx>(), nip, pm.as<cplx>(), nip, gm.as<cplx>(), nip, nip, nip, nip);
+          std::vector<NtDesc> d(1);
+          d[0] = mknt(pm.p, nip, pm.p, nip, gm.p, nip, nip, nip, nip);
           d[0].batch = nh;
           d[0].sA_bat = d[0].sB_bat = d[0].sC_bat = nn;
           d[0].herm = 1;
-          run_gemm(c->arena, 0, GEMM_A_KM | GEMM_B_KN | GEMM_A_CONJ, d, s);
+          run_nt(c->arena, 2, d, s);
         }
         chol_blocked(c->arena, gm.as<cplx>(), pm.as<cplx>(), lt.as<cplx>(), perm.as<int>(), rank.as<int>(),
                      dmax.as<double>(), flag.as<int>(), nip, nh, 0.0, s);
