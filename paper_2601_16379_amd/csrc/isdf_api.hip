@@ -1544,7 +1544,8 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
   int tp = 1;   // power of two (the LDS transform needs tp * ti to be one)
   while (tp < 8 && (long long)nk * ti * tp * 2 <= tile_cap) tp *= 2;
   int ipair = 0;
-  if (pair_lines_supported(prec, c->m[0], c->m[1], c->m[2])) {
+  const bool lines = pair_lines_supported(prec, c->m[0], c->m[1], c->m[2]);
+  if (lines) {
     // the line transform: one value a thread an axis pass.  A tile whose LDS
     // would leave one workgroup a CU (the 10^3 mesh: 129 KB at 16 points) is
     // halved, the halves of each 16-point range run by neighbouring
@@ -1557,7 +1558,18 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     }
   }
   const bool reg = pair_reg_supported(prec, c->m[0], c->m[1], c->m[2]);
-  const long long nchunk = (ld + 63) / 64;
+  const int rpts = pair_reg_points(c->m[0], c->m[1], c->m[2]);
+  const long long nchunk = (ld + rpts - 1) / rpts;
+  // consecutive q a workgroup takes with one psi_p (register and line paths):
+  // long runs halve the loads, but keep about 4096 workgroups
+  int qrun = 1;
+  {
+    long long pairs = 0;
+    for (int n : p.nf) pairs += p.nb == 1 ? (long long)n * n : p.pb;
+    const long long tiles = reg ? nchunk : (ld + ti - 1) / ti;
+    qrun = (int)std::max<long long>(1, std::min<long long>(reg ? 32 : 8, pairs * tiles / 4096));
+    if (reg && qrun < 4) qrun = 4;       // one q a wave
+  }
   // tables of the pair transform over pairs [pbeg, pbeg + pcnt) of every
   // fragment (unblocked: all pairs, output rows at the fragment's pair offset;
   // blocked: the block's pairs, output rows from 0)
@@ -1573,19 +1585,23 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
       fp0[f] = (int)b0;
       fnp[f] = (int)np;
       fpair[f] = p.nb == 1 ? p.poff[f] : -b0;
-      if (p.nb == 1 && tp == 1) {
-        // single pairs of a whole fragment in windows of 8 rows p: for each
-        // q, the pairs (p, q) of the window, so that consecutive blocks (run
-        // together on one XCD) need 8 + a few orbitals of the point tile
-        const int nfr = p.nf[f];
-        for (int p0 = 0; p0 < nfr; p0 += 8)
-          for (int q = 0; q < nfr; ++q)
-            for (int pp = p0; pp < std::min(p0 + 8, nfr); ++pp) blocks.push_back(PairBlock{(int)f, pp * nfr + q, 1});
+      if (lines) {
+        // runs of a row's pairs, in windows of 8 rows p: for each run of q the
+        // rows of the window, so that consecutive blocks (run together on one
+        // XCD) need 8 + a few orbitals of the point tile
+        const long long nfr = p.nf[f];
+        for (long long p0 = b0 / nfr; p0 * nfr < b0 + np; p0 += 8)
+          for (long long q0 = 0; q0 < nfr; q0 += qrun)
+            for (long long pp = p0; pp < p0 + 8; ++pp) {
+              const long long lo = std::max(b0, pp * nfr + q0), hi = std::min({b0 + np, (pp + 1) * nfr, pp * nfr + q0 + qrun});
+              if (lo < hi) blocks.push_back(PairBlock{(int)f, (int)lo, (int)(hi - lo)});
+            }
       } else {
         for (long long q0 = 0; q0 < np; q0 += tp)
           blocks.push_back(PairBlock{(int)f, (int)(b0 + q0), (int)std::min<long long>(tp, np - q0)});
       }
-      ioff[f + 1] = ioff[f] + nchunk * np;
+      const long long nfr = p.nf[f], nrow = (b0 + np - 1) / nfr + 1 - b0 / nfr;
+      ioff[f + 1] = ioff[f] + nchunk * nrow * ((nfr + qrun - 1) / qrun);
     }
     t.nblocks = (int)blocks.size();
     t.blocks = ws.arena.put(blocks.data(), blocks.size(), s);
@@ -1630,7 +1646,8 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     a.ipair = ipair;
     if (reg) {
       a.item_off = t.item_off;
-      a.nfrag = (int)fr.size();
+      a.nfrag = nfrag;
+      a.qrun = qrun;
       a.nitems = t.nitems;
     }
     ws.arena.launch([=] { HIPCHK(pair_launch(a, s)); });

@@ -232,16 +232,17 @@ struct PairArgs {
   long long ld, plane, q_stride, p_stride;
   int fmt;
   const int* qslot;        // device: output block of each q (rows q with qslot < 0 are not written)
-  // register path (mixed precisions, mesh axes <= 4): one wave per (pair,
-  // 64 interpolation points); items ordered (fragment, I chunk, pair),
-  // item_off[f] = first item of fragment f (nfrag + 1 entries, device).
+  // register path (mixed precisions, mesh axes <= 4): one workgroup per (row
+  // p, run of qrun q, 64 or 32 interpolation points); items ordered (fragment, I chunk,
+  // run, row), item_off[f] = first item of fragment f (nfrag + 1 entries, device).
   // A fragment's pairs may be a range: pairs frag_p0[f] .. frag_p0[f] +
-  // frag_np[f] - 1 (device arrays; null = all nf^2 pairs from 0); the output
-  // row of pair P is frag_pair[f] + P in both paths.
+  // frag_np[f] - 1 (device arrays); the output row of pair P is
+  // frag_pair[f] + P in both paths.
   const long long* item_off;
   const int* frag_p0;
   const int* frag_np;
   int nfrag;
+  int qrun;
   long long nitems;
   int m1, m2, m3;
   double scale;
@@ -262,12 +263,15 @@ hipError_t rhs_t_launch(const cplx* xt, const cplx* phi, cplx* out, int nk, int 
                         long long r0, int rcur, int i0, int icur, hipStream_t s);
 // true when pair_launch takes the register path (needs item_off / nitems)
 bool pair_reg_supported(int fmt, int m1, int m2, int m3);
+// points of one item of the register path: 32 where a point's values go to two lanes
+constexpr int pair_reg_points(int m1, int m2, int m3) { return m1 == 4 && m2 * m3 >= 8 && m2 * m3 % 2 == 0 ? 32 : 64; }
 // true when pair_launch takes the FP32 LDS path (mixed formats, a mesh axis
 // longer than 4): psi32 required, tp * ti * N_k <= 8192
 bool pair32_supported(int fmt, int m1, int m2, int m3);
 // the line pair transform (mixed formats, 6^3, 8^3 and 10^3 meshes) and the
-// largest tile (tp * ti, a power of two) it takes: at most 2048 lines an
-// axis pass (two a thread) and 160 KB of LDS
+// largest tile (points, a power of two): at most 2048 lines an axis pass and
+// 160 KB of LDS (the caller halves a tile of more than 80 KB, after which every
+// line has its own thread)
 bool pair_lines_supported(int fmt, int m1, int m2, int m3);
 constexpr int pair_lines_wmax(int m1, int m2, int m3) {
   int w = 1;

@@ -7,6 +7,8 @@
 // time inside LDS (each thread owns one length-m line in registers), applies
 // the pointwise step, transforms back and stores: one HBM read and one HBM
 // write per element, however many mesh axes there are.
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "dft_small.hpp"
 
@@ -807,6 +809,78 @@ __global__ __launch_bounds__(256) void pair32_kernel(PairArgs a) {
   }
 }
 
+// ---- 16-bit operand stores of four consecutive points by the lanes of a quad ----
+// Each lane holds the values of one point (the quad's four are consecutive, the
+// first a multiple of four); the quad exchanges them by DPP so that each lane
+// stores one whole part: 8 bytes (4 points of one of the four planes) in bf16
+// hi+lo, 4 bytes (2 points of one of the two) in single bf16, against four
+// (two) 2-byte stores a lane.
+template <int CTRL> __device__ inline unsigned quad_mov(unsigned v) {
+  return (unsigned)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
+}
+// quad_part: u16 offset of the part this lane stores, for its point's element
+// offset off; output rows further on add a multiple of 8 elements.
+template <int FMT> __device__ inline long long quad_part(long long off) {
+  const int t = threadIdx.x & 3;
+  return FMT == 2 ? (off >> 3) * 32 + t * 8 + (off & 4) : (off >> 3) * 16 + (t >> 1) * 8 + (off & 4) + 2 * (t & 1);
+}
+template <int FMT> __device__ inline void quad_store(char* o, float re, float im) {
+  constexpr int X1 = 0xB1, X2 = 0x4E, SWAP12 = 0xD8;   // quad_perm [1,0,3,2], [2,3,0,1], [0,2,1,3]
+  const int t = threadIdx.x & 3;
+  const unsigned rh = bf16_bits_of(re), ih = bf16_bits_of(im);
+  // byte selectors of v_perm (s0, s1): even lanes (own.lo, other.lo), odd (other.hi, own.hi)
+  const unsigned sel = (t & 1) ? 0x07060302u : 0x01000504u;
+  if constexpr (FMT == 2) {
+    const unsigned rl = bf16_bits_of(re - bf16_value((unsigned short)rh));
+    const unsigned il = bf16_bits_of(im - bf16_value((unsigned short)ih));
+    const unsigned d0 = rh | (rl << 16), d1 = ih | (il << 16);
+    // points (2i, 2i + 1) of planes t & 1 (n0) and 2 + (t & 1) (n1)
+    const unsigned n0 = __builtin_amdgcn_perm(d0, quad_mov<X1>(d0), sel);
+    const unsigned n1 = __builtin_amdgcn_perm(d1, quad_mov<X1>(d1), sel);
+    const unsigned r = quad_mov<X2>(t < 2 ? n1 : n0);
+    *(uint2*)o = t < 2 ? make_uint2(n0, r) : make_uint2(r, n1);
+  } else {
+    const unsigned d = rh | (ih << 16);
+    const unsigned n = __builtin_amdgcn_perm(d, quad_mov<X1>(d), sel);   // lanes: re01, im01, re23, im23
+    *(unsigned*)o = quad_mov<SWAP12>(n);
+  }
+}
+
+// The last axis of the line transform: dft_any_f with the roundings of the
+// length-3 halves of a length-6 line written out (one output of each contracted,
+// the other not), so that they do not hang on which outputs are kept.
+template <int R> __device__ inline void dft_last_f(const float2 (&x)[R], float2 (&y)[R]) {
+  if constexpr (R == 6) {
+    constexpr TwF<3> t3{};
+    constexpr TwF<6> tw{};
+    constexpr float sn = -t3.s[1];
+    float2 h[2][3];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float2 x0 = x[i], x1 = x[2 + i], x2 = x[4 + i];
+      const float2 a = make_float2(x1.x + x2.x, x1.y + x2.y), b = make_float2(x1.x - x2.x, x1.y - x2.y);
+      const float2 t = make_float2(fmaf(-0.5f, a.x, x0.x), fmaf(-0.5f, a.y, x0.y));
+      h[i][0] = make_float2(x0.x + a.x, x0.y + a.y);
+      h[i][1] = make_float2(fmaf(-sn, b.y, t.x), fmaf(sn, b.x, t.y));
+      {
+#pragma clang fp contract(off)
+        const float2 u = make_float2(sn * b.x, sn * b.y);
+        h[i][2] = make_float2(t.x + u.y, t.y - u.x);
+      }
+    }
+    y[0] = make_float2(h[0][0].x + h[1][0].x, h[0][0].y + h[1][0].y);
+    y[3] = make_float2(h[0][0].x - h[1][0].x, h[0][0].y - h[1][0].y);
+#pragma unroll
+    for (int k = 1; k < 3; ++k) {
+      const float2 t = rot_f(h[1][k], tw.c[k], tw.s[k]);
+      y[k] = make_float2(h[0][k].x + t.x, h[0][k].y + t.y);
+      y[k + 3] = make_float2(h[0][k].x - t.x, h[0][k].y - t.y);
+    }
+  } else {
+    dft_any_f<R>(x, y);
+  }
+}
+
 // ---- pair transform of the mixed formats on the 6^3, 8^3 and 10^3 meshes,
 // one line a thread ----
 // The tile of pair_kernel (tp pairs x ti interpolation points for every R)
@@ -821,10 +895,20 @@ __global__ __launch_bounds__(256) void pair32_kernel(PairArgs a) {
 // neighbours in that order): half tiles, whose LDS lets two workgroups
 // share a CU, still read and write whole cache lines between two
 // workgroups that run together.
-template <int M1, int M2, int M3>
+// Bound: the vector units (about 0.9 busy on the 6^3 mesh with the addresses
+// formed per value; FP32 operations take 4 cycles a wave).  So addresses are a
+// uniform base and one 32-bit offset a line, output blocks a table of
+// offsets in LDS,  quads store whole parts: 5.50 -> LN6 ms
+// at 216 k (22779 pairs, single bf16), 10.2 -> LN10 ms at 1000 k (7205 pairs,
+// bf16x3).  WIDE: psi of 4 GiB and more (64-bit
+// offsets).
+template <int M1, int M2, int M3, int FMT, bool WIDE>
 __global__ __launch_bounds__(1024) void pair_lines_kernel(PairArgs a, int ntot) {
   extern __shared__ float2 pl[];
-  constexpr int NK = M1 * M2 * M3;
+  constexpr int NK = M1 * M2 * M3, NQ = (M1 / 2 + 1) * M2 * M3;
+  constexpr int ESZ = FMT == 2 ? 8 : 4;   // bytes per element of a row (FP32: per plane)
+  typedef typename std::conditional<WIDE, size_t, unsigned>::type Off;
+  __shared__ unsigned blk_off[NQ];     // output block of q in units of 16 elements, or all ones
   const int per = (ntot + 7) >> 3;
   const int v = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
   if (v >= ntot) return;
@@ -841,68 +925,85 @@ __global__ __launch_bounds__(1024) void pair_lines_kernel(PairArgs a, int ntot) 
   const int nf = a.frag_nf[pb.frag];
   const int col = a.frag_col[pb.frag];
   const long long poff = a.frag_pair[pb.frag];
-  const int w = a.tp * a.ti;           // power of two
-  const int wshift = __builtin_ctz(w), tshift = __builtin_ctz(a.ti);
-  const int I0 = it * a.ti;
+  const int w = a.ti;                  // points of the tile (a power of two)
+  const int wshift = __builtin_ctz(w);
+  const int I0 = it * w;
   const int rs = M3 * w + 1;           // LDS row of one (R1, R2)
   const long long rstride = (long long)a.ncol * a.n_ip;   // psi32 between consecutive R
-  const int tid = threadIdx.x, nt = blockDim.x;
-  // axis 3 from HBM: line (R1, R2, e)
-  for (int l = tid; l < (NK / M3) << wshift; l += nt) {
-    const int e = l & (w - 1), r12 = l >> wshift;
-    const int j = e >> tshift, I = I0 + (e & (a.ti - 1));
-    float2 x[M3];
-    if (j < pb.npair && I < a.n_ip) {
-      const int P = pb.pair0 + j, pp = P / nf, qq = P - pp * nf;
-      const float2* bp = a.psi32 + ((long long)r12 * M3 * a.ncol + col + pp) * a.n_ip + I;
-      const float2* bq = a.psi32 + ((long long)r12 * M3 * a.ncol + col + qq) * a.n_ip + I;
-#pragma unroll
-      for (int t = 0; t < M3; ++t) {
-        const float2 xp = bp[t * rstride], xq = bq[t * rstride];
-        // conj(psi_p) psi_q
-        x[t] = make_float2(fmaf(xp.x, xq.x, xp.y * xq.y), fmaf(xp.x, xq.y, -(xp.y * xq.x)));
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < M3; ++t) x[t] = make_float2(0.f, 0.f);
-    }
-    float2 y[M3];
-    dft_any_f<M3>(x, y);
-    float2* p = pl + r12 * rs + e;
-#pragma unroll
-    for (int t = 0; t < M3; ++t) p[t * w] = y[t];
-  }
-  __syncthreads();
-  // axis 2: line (R1, R3, e)
-  for (int l = tid; l < (NK / M2) << wshift; l += nt) {
-    const int e = l & (w - 1), r = l >> wshift;
-    float2* p = pl + (r / M3) * M2 * rs + (r % M3) * w + e;
-    float2 x[M2], y[M2];
-#pragma unroll
-    for (int t = 0; t < M2; ++t) x[t] = p[t * rs];
-    dft_any_f<M2>(x, y);
-#pragma unroll
-    for (int t = 0; t < M2; ++t) p[t * rs] = y[t];
-  }
-  __syncthreads();
-  // axis 1 to the output: line (Q2, Q3, e)
+  const int l = threadIdx.x, e = l & (w - 1), r = l >> wshift;
+  for (int q = l; q < NQ; q += blockDim.x) blk_off[q] = a.qslot[q] < 0 ? ~0u : (unsigned)(a.qslot[q] * (a.q_stride >> 4));
   const float sc = (float)a.scale;
-  for (int l = tid; l < (NK / M1) << wshift; l += nt) {
-    const int e = l & (w - 1), r = l >> wshift;
-    const int j = e >> tshift, I = I0 + (e & (a.ti - 1));
-    if (j >= pb.npair || I >= a.ld) continue;
-    const float2* p = pl + (r / M3) * rs + (r % M3) * w + e;
-    float2 x[M1], y[M1];
+  const Off o = (Off)r * (Off)(M3 * rstride * 8) + (Off)e * 8;   // line (R1, R2) = r of an orbital's values
+  const bool l3 = l < (NK / M3) << wshift, l2 = l < (NK / M2) << wshift, l1 = l < (NK / M1) << wshift;
+  const bool in = l3 && I0 + e < a.n_ip;
+  auto load = [&](int orb, float2 (&d)[M3]) {
+    const char* b = (const char*)(a.psi32 + (long long)(col + orb) * a.n_ip + I0);
 #pragma unroll
-    for (int t = 0; t < M1; ++t) x[t] = p[t * M2 * rs];
-    dft_any_f<M1>(x, y);
-    const long long row = (poff + pb.pair0 + j) * a.p_stride + I;
+    for (int t = 0; t < M3; ++t) d[t] = *(const float2*)(b + (long long)t * rstride * 8 + o);
+  };
+  float2 xp[M3];
+  int pl_ = -1;                        // the row whose psi_p line xp holds
+  for (int j = 0; j < pb.npair; ++j) {
+    const int P = pb.pair0 + j, pp = P / nf, qq = P - pp * nf;
+    // axis 3 from HBM: line (R1, R2, e); the last pair's lines have been read
+    __syncthreads();
+    if (l3) {
+      float2 x[M3], y[M3];
+      if (in) {
+        if (pp != pl_) load(pp, xp);
+        load(qq, x);
 #pragma unroll
-    for (int t = 0; t < M1; ++t) {
-      const int slot = a.qslot[t * M2 * M3 + r];
-      if (slot < 0) continue;
-      store_fmt(a.out, (long long)slot * a.q_stride + row, a.plane, a.fmt,
-                cmk((double)(y[t].x * sc), (double)(y[t].y * sc)));
+        for (int t = 0; t < M3; ++t)   // conj(psi_p) psi_q
+          x[t] = make_float2(fmaf(xp[t].x, x[t].x, xp[t].y * x[t].y), fmaf(xp[t].x, x[t].y, -(xp[t].y * x[t].x)));
+      } else {
+#pragma unroll
+        for (int t = 0; t < M3; ++t) x[t] = make_float2(0.f, 0.f);
+      }
+      dft_any_f<M3>(x, y);
+      float2* p = pl + r * rs + e;
+#pragma unroll
+      for (int t = 0; t < M3; ++t) p[t * w] = y[t];
+    }
+    pl_ = pp;
+    __syncthreads();
+    // axis 2: line (R1, R3, e)
+    if (l2) {
+      float2* p = pl + (r / M3) * M2 * rs + (r % M3) * w + e;
+      float2 x[M2], y[M2];
+#pragma unroll
+      for (int t = 0; t < M2; ++t) x[t] = p[t * rs];
+      dft_any_f<M2>(x, y);
+#pragma unroll
+      for (int t = 0; t < M2; ++t) p[t * rs] = y[t];
+    }
+    __syncthreads();
+    // axis 1 to the output: line (Q2, Q3, e); the four lanes of a quad hold
+    // consecutive points of one line (w is a multiple of 4)
+    if (l1 && I0 + e < a.ld) {
+      const float2* p = pl + (r / M3) * rs + (r % M3) * w + e;
+      float2 x[M1], y[M1];
+#pragma unroll
+      for (int t = 0; t < M1; ++t) x[t] = p[t * M2 * rs];
+      dft_last_f<M1>(x, y);
+      // with outputs dropped the compiler would contract the others' last sums
+#pragma unroll
+      for (int t = M1 / 2 + 1; t < M1; ++t) asm volatile("" ::"v"(y[t].x), "v"(y[t].y));
+      const long long row = (poff + P) * a.p_stride + I0 + e;
+      char* out = (char*)a.out + (FMT == 1 ? row * 4 : 2 * quad_part<FMT>(row));
+#pragma unroll
+      for (int t = 0; t <= M1 / 2; ++t) {
+        const unsigned bo = blk_off[t * M2 * M3 + r];
+        if (bo == ~0u) continue;
+        char* o = out + (size_t)bo * (16 * ESZ);
+        float re = y[t].x * sc, im = y[t].y * sc;
+        asm volatile("" : "+v"(re), "+v"(im));       // rounded: not contracted into the low part
+        if constexpr (FMT == 1) {
+          *(float*)o = re;
+          *(float*)(o + a.plane * 4) = im;
+        } else {
+          quad_store<FMT>(o, re, im);
+        }
+      }
     }
   }
 }
@@ -916,10 +1017,22 @@ hipError_t pair_lines_launch(const PairArgs& a, hipStream_t s) {
   if (ntot <= 0) return hipSuccess;
   if (ntot > (1LL << 30) || w > pair_lines_wmax(M1, M2, M3)) return hipErrorInvalidValue;
   const int lmax = NK / (M1 < M2 ? (M1 < M3 ? M1 : M3) : (M2 < M3 ? M2 : M3)) * w;
-  const int threads = lmax <= 1024 ? (lmax + 63) / 64 * 64 : ((lmax + 1) / 2 + 63) / 64 * 64;   // <= 1024
+  const int threads = (lmax + 63) / 64 * 64;
   const size_t lds = (size_t)M1 * M2 * (M3 * w + 1) * sizeof(float2);
   const long long blocks = (ntot + 7) / 8 * 8;
-  hipLaunchKernelGGL((pair_lines_kernel<M1, M2, M3>), dim3((unsigned)blocks), dim3(threads), lds, s, a, (int)ntot);
+  // one pair at a time, one line a thread, whole quads of points
+  if (a.tp != 1 || w < 4 || lmax > 1024 || a.q_stride % 16 || NK * (a.q_stride >> 4) >= (1LL << 32))
+    return hipErrorInvalidValue;
+  const dim3 g((unsigned)blocks), b(threads);
+  const bool wide = (long long)NK * a.ncol * a.n_ip * 8 >= (1LL << 32);
+#define LINES(F)                                                                                                   \
+  if (wide) hipLaunchKernelGGL((pair_lines_kernel<M1, M2, M3, F, true>), g, b, lds, s, a, (int)ntot);              \
+  else hipLaunchKernelGGL((pair_lines_kernel<M1, M2, M3, F, false>), g, b, lds, s, a, (int)ntot)
+  if (a.fmt == 1) { LINES(1); }
+  else if (a.fmt == 2) { LINES(2); }
+  else if (a.fmt == 3) { LINES(3); }
+  else return hipErrorInvalidValue;
+#undef LINES
   return hipGetLastError();
 }
 
@@ -1148,25 +1261,45 @@ __device__ inline void mesh_dft_reg(float2 (&x)[M1 * M2 * M3]) {
   }
 }
 
-// One wave per (pair (p, q) of a fragment, 64 consecutive interpolation
-// points): lane I loads psi_p(r_I + R) and psi_q(r_I + R) for every R from the
-// complex FP32 copy of psi (each load instruction reads 64 consecutive I),
-// forms conj(psi_p) psi_q in FP32, transforms R -> q in registers and writes
-// the N_k outputs of its I (each store instruction covers 64 consecutive I
-// of one row).  Workgroups are mapped XCD-contiguously so the psi rows of
-// one fragment and I chunk stay in one L2 while all its pairs use them.
-constexpr int PAIR_RB = 8;   // lattice vectors whose loads are issued together
-template <int M1, int M2, int M3>
-__global__ __launch_bounds__(256, 2) void pair_reg_kernel(PairArgs a, int nblocks) {
-  constexpr int NK = M1 * M2 * M3;
-  // output staging: per wave 8 rows (q) of 64 points in the operand format
-  __shared__ __attribute__((aligned(16))) unsigned short stage[4][8][256];
+// Lane half h's columns of a pair of values held as (column 0, column 1): the
+// value of column h that half `from` holds, for both halves' lanes.
+__device__ inline float2 half_cols(float2 c0, float2 c1, int from) {
+  const auto re = __builtin_amdgcn_permlane32_swap(__float_as_uint(c0.x), __float_as_uint(c1.x), false, false);
+  const auto im = __builtin_amdgcn_permlane32_swap(__float_as_uint(c0.y), __float_as_uint(c1.y), false, false);
+  return make_float2(__uint_as_float(re[from]), __uint_as_float(im[from]));
+}
+
+// One workgroup per (row p of a fragment, run of qrun consecutive q, 64 or 32
+// consecutive interpolation points): psi_p(r_I + R) of every R (complex FP32)
+// goes to LDS once, and each of the four waves takes every fourth q of the run:
+// lane I loads psi_q for every R, forms conj(psi_p) psi_q in FP32, transforms
+// R -> q in registers and writes the stored outputs of its I, whole parts of a
+// row (quad_store).  Meshes of four along axis 1 and 8 or more (an even number)
+// across it give a point to two lanes (l and l + 32): lane half h holds axis-1
+// places h and h + 2, forms their sums and differences, and v_permlane32_swap
+// brings both halves' of a column together, one column of two to each half for
+// the last butterfly; half the registers, so twice the waves.
+// Workgroups are mapped XCD-contiguously so the psi rows of one fragment and I
+// chunk stay in one L2 while all its pairs use them.
+// Bound: the latency of the psi loads and of the stores before them (vmcnt
+// counts both in order) at the waves that the registers allow.  4x4x4 mesh, 47.5 k
+// pairs of 520 points, bf16x3: 4.28 ms with a wave a pair of 64 points, both orbitals
+// loaded for every pair and outputs staged through LDS; 4.6 ms as now but one lane a
+// point (two waves a SIMD); REGMS ms with two.
+constexpr int PAIR_RB = 8;   // loads of psi_q issued together
+template <int M1, int M2, int M3, int FMT>
+__global__ __launch_bounds__(256, pair_reg_points(M1, M2, M3) == 32 ? 4 : 2) void pair_reg_kernel(PairArgs a, int nblocks) {
+  constexpr int NK = M1 * M2 * M3, M23 = M2 * M3, W = pair_reg_points(M1, M2, M3);
+  constexpr bool SPLIT = W == 32;
+  constexpr int NX = SPLIT ? 2 * M23 : NK;           // values a lane
+  constexpr int ESZ = FMT == 2 ? 8 : 4;              // bytes per element of a row (FP32: per plane)
+  __shared__ float2 pu[NX][64];
+  __shared__ unsigned blk_off[NK];                   // output block of q in units of 16 elements, or all ones
   const int g8 = gridDim.x >> 3;
-  const int blk = (int)(blockIdx.x & 7) * g8 + (int)(blockIdx.x >> 3);
-  if (blk >= nblocks) return;
-  const long long item = (long long)blk * 4 + (threadIdx.x >> 6);
-  if (item >= a.nitems) return;                      // whole wave
-  const int lane = threadIdx.x & 63;
+  const long long item = (long long)(blockIdx.x & 7) * g8 + (blockIdx.x >> 3);
+  if (item >= nblocks) return;                       // the whole workgroup
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = SPLIT ? lane >> 5 : 0;
   int lo = 0, hi = a.nfrag - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -1174,129 +1307,115 @@ __global__ __launch_bounds__(256, 2) void pair_reg_kernel(PairArgs a, int nblock
   }
   const int f = lo;
   const int nf = a.frag_nf[f];
-  const int np = a.frag_np ? a.frag_np[f] : nf * nf;     // pairs of this fragment in the launch
-  const int pbeg = a.frag_p0 ? a.frag_p0[f] : 0;
+  const int pbeg = a.frag_p0[f], pend = pbeg + a.frag_np[f];   // pairs of this fragment in the launch
+  const int row0 = pbeg / nf, nrow = (pend - 1) / nf + 1 - row0;
+  const int nseg = (nf + a.qrun - 1) / a.qrun;
   const long long local = item - a.item_off[f];
-  const int chunk = (int)(local / np);
-  const int pp = pbeg + (int)(local - (long long)chunk * np);
-  const int p = pp / nf, q = pp - (pp / nf) * nf;
-  const int I = chunk * 64 + lane;
+  const int p = row0 + (int)(local % nrow);
+  const int cs = (int)(local / nrow), seg = cs % nseg, chunk = cs / nseg;
+  // the q of this item: its run, within the pair range
+  const int q0 = max(seg * a.qrun, pbeg - p * nf), q1 = min(min(nf, (seg + 1) * a.qrun), pend - p * nf);
+  if (q0 >= q1) return;                              // the whole workgroup
+  const int I = chunk * W + (lane & (W - 1));
   const bool in = I < a.n_ip;
   const int col = a.frag_col[f];
   const long long rstride = (long long)a.ncol * a.n_ip;
-  float2 x[NK];
-  // loads in batches of RB lattice vectors, all issued before the first use
-  // (left to itself the compiler waits for every pair of loads in turn)
-  // complex FP32 psi (the register path serves the mixed precisions only)
-  const float2* fp = a.psi32 + (long long)(col + p) * a.n_ip + (in ? I : 0);
-  const float2* fq = a.psi32 + (long long)(col + q) * a.n_ip + (in ? I : 0);
-  constexpr int RB = NK < PAIR_RB ? NK : PAIR_RB;
-#pragma unroll
-  for (int R0 = 0; R0 < NK; R0 += RB) {
-    float2 u[RB], v[RB];
-#pragma unroll
-    for (int j = 0; j < RB; ++j) {
-      if (R0 + j < NK) {
-        u[j] = fp[(R0 + j) * rstride];
-        v[j] = fq[(R0 + j) * rstride];
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int j = 0; j < RB; ++j) {
-      if (R0 + j < NK) {
-        // conj(u) v
-        const float re = fmaf(u[j].x, v[j].x, u[j].y * v[j].y), im = fmaf(u[j].x, v[j].y, -(u[j].y * v[j].x));
-        x[R0 + j] = in ? make_float2(re, im) : make_float2(0.f, 0.f);
-      }
-    }
-  }
-  mesh_dft_reg<M1, M2, M3>(x);
+  // place i of this lane: R = (i / M23, and in halves half + 2 (i / M23)) M23 + i % M23
+  const long long lane_off = (long long)(half * M23) * rstride + (in ? I : 0);
+  auto psi = [&](int orb, int i) {
+    const int R = SPLIT ? (i / M23) * 2 * M23 + i % M23 : i;
+    return a.psi32[(long long)(col + orb) * a.n_ip + R * rstride + lane_off];
+  };
+  if (threadIdx.x < NK)
+    blk_off[threadIdx.x] = a.qslot[threadIdx.x] < 0 ? ~0u : (unsigned)(a.qslot[threadIdx.x] * (a.q_stride >> 4));
+#pragma unroll 4
+  for (int i = wave; i < NX; i += 4) pu[i][lane] = psi(p, i);
+  __syncthreads();
   const float sc = (float)a.scale;
-  const long long base = (a.frag_pair[f] + pp) * a.p_stride + chunk * 64;   // row start of this chunk
-  const int nI = (a.ld - chunk * 64) < 64 ? (int)(a.ld - chunk * 64) : 64;  // a multiple of 16
-  if (a.fmt == 1) {
-    if (I >= a.ld) return;
-    float* o = (float*)a.out;
+  constexpr int RB = NX < PAIR_RB ? NX : PAIR_RB, NB = (NX + RB - 1) / RB;
+  float2 v[2][RB];
+  auto load = [&](int q, int b) {
 #pragma unroll
-    for (int Q = 0; Q < NK; ++Q) {
-      const int slot = a.qslot[Q];
-      if (slot < 0) continue;
-      const long long off = base + lane + slot * a.q_stride;
-      o[off] = x[Q].x * sc;
-      o[a.plane + off] = x[Q].y * sc;
+    for (int j = 0; j < RB; ++j)
+      if (b * RB + j < NX) v[b & 1][j] = psi(q, b * RB + j);
+  };
+  auto store = [&](char* out, int Q, float re, float im) {
+    const unsigned bo = blk_off[Q];
+    if (bo == ~0u) return;                           // the class is kept at -q
+    char* o = out + (size_t)bo * (16 * ESZ);
+    if constexpr (FMT == 1) {
+      *(float*)o = re * sc;
+      *(float*)(o + a.plane * 4) = im * sc;
+    } else {
+      quad_store<FMT>(o, re * sc, im * sc);
     }
-    return;
-  }
-  if (a.fmt == 3) {
-    // single bf16: each row (q) of the chunk is 64 points x 4 bytes = 256
-    // contiguous bytes; rows assembled in LDS, 8 at a time, written with
-    // 16-byte stores (four rows per wave instruction)
-    unsigned short (*st3)[256] = stage[threadIdx.x >> 6];
-    const int e3 = (lane >> 3) * 16 + (lane & 7);
+  };
+  if (q0 + wave < q1) load(q0 + wave, 0);
+  for (int q = q0 + wave; q < q1; q += 4) {
+    float2 x[NX];
+    int pl = lane;                                   // opaque: psi_p stays in LDS over the loop
+    asm volatile("" : "+v"(pl));
 #pragma unroll
-    for (int Q0 = 0; Q0 < NK; Q0 += 8) {
+    for (int b = 0; b < NB; ++b) {
+      if (b + 1 < NB) load(q, b + 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (Q0 + u >= NK) break;
-        st3[u][e3] = bf16_bits_of(x[Q0 + u].x * sc);
-        st3[u][e3 + 8] = bf16_bits_of(x[Q0 + u].y * sc);
-      }
-      __builtin_amdgcn_wave_barrier();
+      for (int j = 0; j < RB; ++j)
+        if (b * RB + j < NX) {
+          // conj(u) v
+          const float2 u = pu[b * RB + j][pl], w = v[b & 1][j];
+          const float re = fmaf(u.x, w.x, u.y * w.y), im = fmaf(u.x, w.y, -(u.y * w.x));
+          x[b * RB + j] = in ? make_float2(re, im) : make_float2(0.f, 0.f);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // batch 0 of the next q, in flight over the transform and the stores
+    load(min(q + 4, q1 - 1), 0);
+    // in halves: sums (i < M23) and differences of axis-1 places half and half + 2
+    mesh_dft_reg<SPLIT ? 2 : M1, M2, M3>(x);
+    // all formed here (sunk into the conditional stores below, their operands
+    // outgrow the registers)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int u = 4 * h + (lane >> 4), part = lane & 15;   // row u, 16-byte part
-        const int sq = Q0 + u < NK ? a.qslot[Q0 + u] : -1;
-        if (sq >= 0 && (part >> 1) * 8 < nI) {
-          const uint4 v = *(const uint4*)&st3[u][part * 8];
-          *(uint4*)((unsigned short*)a.out + 2 * (base + (long long)sq * a.q_stride) + part * 8) = v;
+    for (int i = 0; i < NX; ++i) asm volatile("" : "+v"(x[i].x), "+v"(x[i].y));
+    // this lane's place in the pair's row
+    const long long o0 = (a.frag_pair[f] + (long long)p * nf + q) * a.p_stride + I;
+    char* out = (char*)a.out + (FMT == 1 ? o0 * 4 : 2 * quad_part<FMT>(o0));
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int j = 0; j < M23; j += 2) {
+        // column j + half: A, B = x0 +- x2 and C, D = x1 +- x3 of axis 1
+        const float2 A = half_cols(x[j], x[j + 1], 0), C = half_cols(x[j], x[j + 1], 1);
+        const float2 B = half_cols(x[M23 + j], x[M23 + j + 1], 0), D = half_cols(x[M23 + j], x[M23 + j + 1], 1);
+        if (I < a.ld) {
+          const int Q = j + half;
+          store(out, Q, A.x + C.x, A.y + C.y);
+          store(out, M23 + Q, B.x + D.y, B.y - D.x);
+          store(out, 2 * M23 + Q, A.x - C.x, A.y - C.y);
+          store(out, 3 * M23 + Q, B.x - D.y, B.y + D.x);
         }
       }
-      __builtin_amdgcn_wave_barrier();
-    }
-    return;
-  }
-  // bf16 hi/lo: each row (q) of the chunk is 64 points x 8 bytes = 512
-  // contiguous bytes; rows are assembled in LDS, 8 at a time, and written
-  // with 16-byte stores (two rows per wave instruction)
-  unsigned short (*st)[256] = stage[threadIdx.x >> 6];
-  const int e = (lane >> 3) * 32 + (lane & 7);
+    } else if (I < a.ld) {
 #pragma unroll
-  for (int Q0 = 0; Q0 < NK; Q0 += 8) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (Q0 + u >= NK) break;
-      const float re = x[Q0 + u].x * sc, im = x[Q0 + u].y * sc;
-      const unsigned short rh = bf16_bits_of(re), ih = bf16_bits_of(im);
-      st[u][e] = rh;
-      st[u][e + 8] = bf16_bits_of(re - bf16_value(rh));
-      st[u][e + 16] = ih;
-      st[u][e + 24] = bf16_bits_of(im - bf16_value(ih));
+      for (int Q = 0; Q < NK; ++Q) store(out, Q, x[Q].x, x[Q].y);
     }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const int u = 2 * h + (lane >> 5), part = lane & 31;   // row u, 16-byte part
-      // output block of row u (uniform loads, one per half wave)
-      const int s0 = Q0 + 2 * h < NK ? a.qslot[Q0 + 2 * h] : -1;
-      const int s1 = Q0 + 2 * h + 1 < NK ? a.qslot[Q0 + 2 * h + 1] : -1;
-      const int slot = (lane >> 5) ? s1 : s0;
-      if (slot >= 0 && part * 2 < nI) {
-        const uint4 v = *(const uint4*)&st[u][part * 8];
-        *(uint4*)((unsigned short*)a.out + 4 * (base + (long long)slot * a.q_stride) + part * 8) = v;
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
   }
 }
 
 template <int M1, int M2, int M3>
 hipError_t launch_pair_reg(const PairArgs& a, hipStream_t s) {
-  const long long nb = (a.nitems + 3) / 4;
+  const long long nb = a.nitems;
   if (nb <= 0) return hipSuccess;
-  if (nb > (1LL << 30)) return hipErrorInvalidValue;
+  if (nb > (1LL << 30) || a.q_stride % 16 || a.qrun < 1 || !a.frag_p0 || !a.frag_np ||
+      M1 * M2 * M3 * (a.q_stride >> 4) >= (1LL << 32))
+    return hipErrorInvalidValue;
   const long long g = (nb + 7) / 8 * 8;
-  hipLaunchKernelGGL((pair_reg_kernel<M1, M2, M3>), dim3((unsigned)g), dim3(256), 0, s, a, (int)nb);
+  const dim3 gr((unsigned)g), b(256);
+  switch (a.fmt) {
+    case 1: hipLaunchKernelGGL((pair_reg_kernel<M1, M2, M3, 1>), gr, b, 0, s, a, (int)nb); break;
+    case 2: hipLaunchKernelGGL((pair_reg_kernel<M1, M2, M3, 2>), gr, b, 0, s, a, (int)nb); break;
+    case 3: hipLaunchKernelGGL((pair_reg_kernel<M1, M2, M3, 3>), gr, b, 0, s, a, (int)nb); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
