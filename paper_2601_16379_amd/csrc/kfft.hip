@@ -897,11 +897,11 @@ template <int R> __device__ inline void dft_last_f(const float2 (&x)[R], float2 
 // workgroups that run together.
 // Bound: the vector units (about 0.9 busy on the 6^3 mesh with the addresses
 // formed per value; FP32 operations take 4 cycles a wave).  So addresses are a
-// uniform base and one 32-bit offset a line, output blocks a table of
-// offsets in LDS,  quads store whole parts: 5.50 -> LN6 ms
-// at 216 k (22779 pairs, single bf16), 10.2 -> LN10 ms at 1000 k (7205 pairs,
-// bf16x3).  WIDE: psi of 4 GiB and more (64-bit
-// offsets).
+// uniform base and one 32-bit offset a line, output blocks a table of offsets
+// in LDS, outputs of axis-1 index above M1 / 2 (never stored: their -q comes
+// first) are passed over, and quads store whole parts: 5.50 -> 3.93 ms at 216 k
+// (22779 pairs, single bf16), 10.2 -> 9.0 ms at 1000 k (7205 pairs, bf16x3).
+// WIDE: psi of 4 GiB and more (64-bit offsets).
 template <int M1, int M2, int M3, int FMT, bool WIDE>
 __global__ __launch_bounds__(1024) void pair_lines_kernel(PairArgs a, int ntot) {
   extern __shared__ float2 pl[];
@@ -1285,7 +1285,7 @@ __device__ inline float2 half_cols(float2 c0, float2 c1, int from) {
 // counts both in order) at the waves that the registers allow.  4x4x4 mesh, 47.5 k
 // pairs of 520 points, bf16x3: 4.28 ms with a wave a pair of 64 points, both orbitals
 // loaded for every pair and outputs staged through LDS; 4.6 ms as now but one lane a
-// point (two waves a SIMD); REGMS ms with two.
+// point (two waves a SIMD); 2.95 ms with two.
 constexpr int PAIR_RB = 8;   // loads of psi_q issued together
 template <int M1, int M2, int M3, int FMT>
 __global__ __launch_bounds__(256, pair_reg_points(M1, M2, M3) == 32 ? 4 : 2) void pair_reg_kernel(PairArgs a, int nblocks) {

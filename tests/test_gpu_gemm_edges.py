@@ -78,3 +78,24 @@ def test_factor_edges(n_ip):
         err = np.max(np.abs(pi @ w @ pi - v)) / np.max(np.abs(v))
         assert ev[0] > 0 and err <= bound, (q, err, bound)
     ctx.close()
+
+
+@pytest.mark.parametrize("kmesh", [(4, 2, 4), (4, 4, 3), (4, 3, 3), (3, 4, 2), (4, 1, 4), (6, 6, 6)])
+@pytest.mark.parametrize("n_ip", [15, 33, 65])
+def test_pair_transform_points(kmesh, n_ip):
+    """The register pair transform with two lanes a point (four along axis 1
+    and an even number, 8 or more, across) and one, and the line transform, at
+    point counts one off their chunks (32, 64, 16); runs of q longer and
+    shorter than a workgroup's waves."""
+    import paper_2601_16379_amd as pkg
+    cfg = dataclasses.replace(inp.get_config("t_small_k2"), kmesh=kmesh, n_ip=n_ip)
+    d = inp.make_inputs(cfg)
+    import torch
+    ctx = pkg.Isdf(d.lattice, cfg.grid, cfg.kmesh, torch.from_numpy(d.orbitals).cuda(),
+                   torch.from_numpy(d.ip_index).cuda())
+    ctx.fit()
+    ctx.coulomb_kernel("fp64")
+    x = ko.ip_values(d.orbitals, d.ip_index)
+    w = np.stack([ctx.get_kernel(q) for q in range(cfg.n_k)])
+    _check(cfg, ctx, x, w, [1, 2, 5, 7], ["fp64", "fp32", "bf16x3"])
+    ctx.close()
