@@ -82,18 +82,18 @@ constexpr int RING = 4;
 // this zero block instead, so that LDS holds zeros there.
 __device__ __attribute__((aligned(16))) unsigned short kZeroVec[8];
 
-// Issue the copies of one operand's stage (128 rows x 128 bytes) into LDS at
-// `dst`: 16 wave-instructions of 8 rows, 4 per wave.  src[j]: this lane's
+// Issue the copies of one operand's stage (128 or 64 rows x 128 bytes) into
+// LDS at `dst`: wave-instructions of 8 rows, N (4 or 2) per wave.  src[j]: this lane's
 // 16-byte source of the wave's j-th instruction at k = 0 (row base plus the
 // slot gslot[j] whose LDS position is this lane's); the address advances by
 // 4 u16 an element of k.  In the last stage of a segment, vectors that start
 // at or past its end are copied from the zero block.
-template <int F>
-__device__ inline void stage_copy(const unsigned short* const (&src)[NCOPY], const int (&gslot)[NCOPY], int k0,
+template <int F, int N>
+__device__ inline void stage_copy(const unsigned short* const (&src)[N], const int (&gslot)[N], int k0,
                                   int kcur, char* dst, int wave) {
   const bool tail = k0 + Fmt<F>::K > kcur;    // the same for the whole workgroup
 #pragma unroll
-  for (int j = 0; j < NCOPY; ++j) {
+  for (int j = 0; j < N; ++j) {
     const int rc = wave + 4 * j;          // rows rc*8 .. rc*8+7
     const unsigned short* g = src[j] + Fmt<F>::EU * k0;
     if (tail && k0 + 8 * (gslot[j] >> Fmt<F>::PL) >= kcur) g = kZeroVec;
@@ -129,12 +129,12 @@ __device__ inline void read_frags_a(const char* buf, Frag<NI, NJ>& f, int rb0, i
     for (int pl = 0; pl < 4; ++pl) f.a[i][pl] = *(const u4*)(p + (lds_slot(row, frag_slot<F>(lk, pl)) << 4));
   }
 }
-template <int F, int NI, int NJ>
+template <int F, int OPB = OPER_B, int NI, int NJ>
 __device__ inline void read_frags_b(const char* buf, Frag<NI, NJ>& f, int cb0, int lr, int lk) {
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int row = cb0 + j * 32 + lr;
-    const char* p = buf + OPER_B + row * ROW_B;
+    const char* p = buf + OPB + row * ROW_B;
 #pragma unroll
     for (int pl = 0; pl < 4; ++pl) f.b[j][pl] = *(const u4*)(p + (lds_slot(row, frag_slot<F>(lk, pl)) << 4));
   }
@@ -262,7 +262,7 @@ __device__ inline void mma_single(const Frag<NI, NJ>& f, int j, f16v (&c_re)[NI]
 // of NJ*32 points is NJ*256 contiguous bytes) and writes it with 16-byte
 // stores; otherwise FP64 accumulation across launches (the first K segment,
 // `first`, stores).
-template <int F, int NI, int NJ>
+template <int F, int NI, int NJ, int T = XT>
 __device__ inline void tile_epilogue(const NtDesc& d, int b, int m0, int n0, int rb0, int cb0,
                                      const f16v (&c_re)[NI][NJ], const f16v (&c_im)[NI][NJ], char* smem, int wave,
                                      int lane, bool first, cplx* part) {
@@ -311,7 +311,7 @@ __device__ inline void tile_epilogue(const NtDesc& d, int b, int m0, int n0, int
   } else if (part) {
     // partial block of the tile, row-major; the offset is opaque so that the
     // addresses are formed here and not held over the K loop
-    int o0 = (rb0 + 4 * lk) * XT + cb0 + lr;
+    int o0 = (rb0 + 4 * lk) * T + cb0 + lr;
     asm volatile("" : "+v"(o0));
     cplx* pp = part + o0;
 #pragma unroll
@@ -320,7 +320,7 @@ __device__ inline void tile_epilogue(const NtDesc& d, int b, int m0, int n0, int
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-          pp[(i * 32 + 8 * (v >> 2) + (v & 3)) * XT + j * 32] =
+          pp[(i * 32 + 8 * (v >> 2) + (v & 3)) * T + j * 32] =
               cmk((double)c_re[i][j][v], (double)c_im[i][j][v]);
   } else {
     int mr = m0 + rb0 + 4 * lk;
@@ -595,7 +595,89 @@ __device__ inline void tile_body_2b(const NtDesc& d, int b, int m0, int n0, int 
   if (!idle) tile_epilogue<F, NI, NJ>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first, part);
 }
 
-template <int F, bool A_CONJ, bool B_CONJ, int KIND, bool RINGP, bool TWOB = false>
+// Small tiles: 64 x 64, a 32 x 32 block a wave, SRING stages of 16 KB.
+constexpr int SOPER_B = X3_SMALL * ROW_B;
+constexpr int SSTAGE_B = 2 * SOPER_B;
+constexpr int SCOPY = X3_SMALL / 32;
+constexpr int SRING = 8;
+
+// One stage of a small tile: as ring_step, without conditions.  Copies past the
+// last stage repeat it into buffers no longer read (so the count in flight stays
+// the same), and the fragments read after the last stage are not used.
+template <int F, bool A_CONJ, bool B_CONJ>
+__device__ inline void small_step(int s, int nst, int kcur, bool live, Frag<1, 1>& cur, Frag<1, 1>& nxt,
+                                  f16v (&c_re)[1][1], f16v (&c_im)[1][1], const unsigned short* const (&asrc)[SCOPY],
+                                  const unsigned short* const (&bsrc)[SCOPY], const int (&gslot)[SCOPY], int rb0,
+                                  int cb0, char* smem, int wave, int lr, int lk) {
+  static_assert(2 * SCOPY * (SRING - 2) == 24, "the count below");
+  // stage s + 1 has landed, and this wave holds its fragments of stage s
+  asm volatile("s_waitcnt vmcnt(24) lgkmcnt(0)" ::: "memory");
+  settle(cur);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  const int k0 = min(s + SRING, nst - 1) * Fmt<F>::K;
+  char* buf = smem + (s % SRING) * SSTAGE_B;
+  const char* nb = smem + ((s + 1) % SRING) * SSTAGE_B;
+  read_frags_a<F>(nb, nxt, rb0, lr, lk);
+  read_frags_b<F, SOPER_B>(nb, nxt, cb0, lr, lk);
+  __builtin_amdgcn_sched_barrier(0);
+  if (k0 + Fmt<F>::K <= kcur) {
+#pragma unroll
+    for (int j = 0; j < SCOPY; ++j) {
+      char* dst = buf + (wave + 4 * j) * 8 * ROW_B;
+      __builtin_amdgcn_global_load_lds((glb_void*)(asrc[j] + Fmt<F>::EU * k0), (lds_void*)dst, 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((glb_void*)(bsrc[j] + Fmt<F>::EU * k0), (lds_void*)(dst + SOPER_B), 16, 0, 0);
+    }
+  } else {
+    stage_copy<F>(asrc, gslot, k0, kcur, buf, wave);
+    stage_copy<F>(bsrc, gslot, k0, kcur, buf + SOPER_B, wave);
+  }
+  if (live) stage_mma<F, 1, 1, A_CONJ, B_CONJ>(cur, c_re, c_im);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int F, bool A_CONJ, bool B_CONJ, bool TRI>
+__device__ inline void tile_body_small(const NtDesc& d, int b, int m0, int n0, int kcur,
+                                       const unsigned short* const (&asrc)[SCOPY],
+                                       const unsigned short* const (&bsrc)[SCOPY], const int (&gslot)[SCOPY], int rb0,
+                                       int cb0, char* smem, int wave, int lane, bool idle, bool first, cplx* part) {
+  const int lr = lane & 31, lk = lane >> 5;
+  f16v c_re[1][1], c_im[1][1];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) c_re[0][0][v] = c_im[0][0][v] = 0.f;
+  constexpr int SK = Fmt<F>::K;
+  const int nst = (kcur + SK - 1) / SK;
+  // with a triangular B, the first stage whose B rows are not all zero (tri_live)
+  const int s0 = TRI && d.ktri ? cb0 / SK : 0;
+  __syncthreads();                        // LDS of the previous tile no longer read
+#pragma unroll
+  for (int s = 0; s < SRING; ++s) {
+    const int k0 = min(s, nst - 1) * SK;
+    stage_copy<F>(asrc, gslot, k0, kcur, smem + s * SSTAGE_B, wave);
+    stage_copy<F>(bsrc, gslot, k0, kcur, smem + s * SSTAGE_B + SOPER_B, wave);
+  }
+  static_assert(2 * SCOPY * (SRING - 1) == 28, "the count below");
+  asm volatile("s_waitcnt vmcnt(28)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  Frag<1, 1> f0, f1;
+  read_frags_a<F>(smem, f0, rb0, lr, lk);
+  read_frags_b<F, SOPER_B>(smem, f0, cb0, lr, lk);
+  const int even = nst & ~1;              // one exit: the accumulators stay where they are
+  for (int s = 0; s < even; s += 2) {
+    small_step<F, A_CONJ, B_CONJ>(s, nst, kcur, !TRI || s >= s0, f0, f1, c_re, c_im, asrc, bsrc, gslot, rb0, cb0, smem,
+                                  wave, lr, lk);
+    small_step<F, A_CONJ, B_CONJ>(s + 1, nst, kcur, !TRI || s + 1 >= s0, f1, f0, c_re, c_im, asrc, bsrc, gslot, rb0, cb0,
+                                  smem, wave, lr, lk);
+  }
+  if (even < nst)
+    small_step<F, A_CONJ, B_CONJ>(even, nst, kcur, true, f0, f1, c_re, c_im, asrc, bsrc, gslot, rb0, cb0, smem, wave, lr,
+                                  lk);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // before LDS is used for anything else
+  if (!idle) tile_epilogue<F, 1, 1, X3_SMALL>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first, part);
+}
+
+template <int F, bool A_CONJ, bool B_CONJ, int KIND, bool RINGP, bool TWOB = false, int T = XT>
 __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, long long t0, long long nt, int seg0,
                                 int nseg, cplx* part) {
   extern __shared__ __attribute__((aligned(16))) char smem[];   // NBUF (RING) stages x (A, B)
@@ -616,8 +698,8 @@ __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, lon
     const NtTile tl = nt_tile(descs, ndesc, t0 + u % nt);
     const NtDesc d = descs[tl.desc];
     const int b = tl.b, tm = tl.tm, tn = tl.tn;
-    cplx* pt = part ? part + u * (XT * XT) : nullptr;
-    const int m0 = tm * XT, n0 = tn * XT;
+    cplx* pt = part ? part + u * (T * T) : nullptr;
+    const int m0 = tm * T, n0 = tn * T;
     // interleaved formats: logical element e at u16 EU*e (e a multiple of 8)
     constexpr int EU = Fmt<F>::EU;
     // a triangular B (zero for k < n) contributes from k = n0 on
@@ -630,11 +712,12 @@ __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, lon
 
     // this lane's sources and slots in its copy instructions; rows past M / N
     // read the last valid row (their outputs are not stored)
-    const unsigned short* asrc[NCOPY];
-    const unsigned short* bsrc[NCOPY];
-    int gslot[NCOPY];
+    constexpr int NC = T / 32;
+    const unsigned short* asrc[NC];
+    const unsigned short* bsrc[NC];
+    int gslot[NC];
 #pragma unroll
-    for (int j = 0; j < NCOPY; ++j) {
+    for (int j = 0; j < NC; ++j) {
       const int row = (wave + 4 * j) * 8 + (lane >> 3);
       gslot[j] = lds_slot(row, lane & 7);     // the slot whose LDS position is lane & 7
       const int ra = min(m0 + row, d.M - 1), rb = min(n0 + row, d.N - 1);
@@ -647,7 +730,12 @@ __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, lon
     // skips lie above the diagonal, which the consumers never read)
     const bool diag = d.herm && tm == tn && d.epi != 3;
     const bool first = seg == 0;
-    if constexpr (RINGP) {
+    if constexpr (T != XT) {
+      // a block outside the product stores nothing
+      const bool idle = (diag && wm < wn) || (d.epi != 3 && (m0 + wm * 32 >= d.M || n0 + wn * 32 >= d.N));
+      tile_body_small<F, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 32, wn * 32, smem, wave,
+                                                    lane, idle, first, pt);
+    } else if constexpr (RINGP) {
       if (d.M - m0 <= 32)
         tile_body_ring<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave,
                                                 lane, diag && wave > 0, first, pt);
@@ -702,15 +790,27 @@ template <int F, int KIND>
 __global__ __launch_bounds__(XNT, 1) void zgemm_ring_kernel(X3_ARGS) {
   x3_tiles<F, false, KIND == 3, KIND, true>(descs, ndesc, t0, nt, seg0, nseg, part);
 }
+
+// 64 x 64 tiles, a 32 x 32 block a wave, eight LDS stages (one workgroup a CU):
+// launches of few tiles, which leave most CUs idle and wait out every stage's
+// latency.  The K chain of an element stays whole and in order (the bits do not
+// change); its stage falls from 1.2 us (128 x 128 tile alone on its CU: 48 MFMAs
+// a wave and two stages ahead) to 0.39 us (12 MFMAs, seven ahead): contraction
+// of one 16-orbital fragment at N_IP = 256 on the 2x2x2 mesh, 128 stages, 154 ->
+// 50 us; its U^q 30 -> 15 us.
+template <int F, int KIND>
+__global__ __launch_bounds__(XNT, 1) void zgemm_small16_kernel(X3_ARGS) {
+  x3_tiles<F, false, KIND == 3, KIND, true, false, X3_SMALL>(descs, ndesc, t0, nt, seg0, nseg, part);
+}
 #undef X3_ARGS
 
 }  // namespace
 
-long long x3_plan(NtDesc* d, int n) {
+long long x3_plan(NtDesc* d, int n, int tile) {
   long long acc = 0;
   for (int i = 0; i < n; ++i) {
-    d[i].tiles_m = ceil_div(d[i].M, XT);
-    d[i].tiles_n = ceil_div(d[i].N, XT);
+    d[i].tiles_m = ceil_div(d[i].M, tile);
+    d[i].tiles_n = ceil_div(d[i].N, tile);
     d[i].tiles_per_batch = d[i].herm ? d[i].tiles_m * (d[i].tiles_m + 1) / 2
                                      : d[i].tiles_m * d[i].tiles_n;
     if (d[i].Klast <= 0 || d[i].Klast > d[i].Kseg) d[i].Klast = d[i].Kseg;
@@ -721,16 +821,23 @@ long long x3_plan(NtDesc* d, int n) {
 }
 
 hipError_t x3_launch(int fmt, const NtDesc* descs_dev, int ndesc, long long t0, long long nt, int seg0, int nseg,
-                     cplx* part, int max_blocks, hipStream_t s, int kind, bool ring) {
+                     cplx* part, int max_blocks, hipStream_t s, int kind, bool ring, int tile) {
   if (nt <= 0 || nseg <= 0) return hipSuccess;
-  if ((fmt != 2 && fmt != 3) || (kind != 2 && kind != 3) || (!part && nseg != 1)) return hipErrorInvalidValue;
+  if ((fmt != 2 && fmt != 3) || (kind != 2 && kind != 3) || (!part && nseg != 1) ||
+      (tile != XT && tile != X3_SMALL))
+    return hipErrorInvalidValue;
   const long long units = nt * nseg, u8 = (units + 7) / 8 * 8;
   max_blocks = max_blocks / 8 * 8;
   const dim3 g((unsigned)(u8 < max_blocks ? u8 : max_blocks)), b(XNT);
 #define COMMA ,
 #define X3_GO(KERNEL, LDS) \
   hipLaunchKernelGGL((KERNEL), g, b, LDS, s, descs_dev, ndesc, t0, nt, seg0, nseg, part)
-  if (ring) {
+  if (tile == X3_SMALL) {
+    if (fmt == 2 && kind == 2) X3_GO(zgemm_small16_kernel<2 COMMA 2>, SRING * SSTAGE_B);
+    else if (fmt == 2) X3_GO(zgemm_small16_kernel<2 COMMA 3>, SRING * SSTAGE_B);
+    else if (kind == 2) X3_GO(zgemm_small16_kernel<3 COMMA 2>, SRING * SSTAGE_B);
+    else X3_GO(zgemm_small16_kernel<3 COMMA 3>, SRING * SSTAGE_B);
+  } else if (ring) {
     if (fmt == 2 && kind == 2) X3_GO(zgemm_ring_kernel<2 COMMA 2>, RING * STAGE_B);
     else if (fmt == 2) X3_GO(zgemm_ring_kernel<2 COMMA 3>, RING * STAGE_B);
     else if (kind == 2) X3_GO(zgemm_ring_kernel<3 COMMA 2>, RING * STAGE_B);

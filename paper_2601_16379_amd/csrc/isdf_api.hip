@@ -348,6 +348,13 @@ void run_nt(Arena& ar, int conj, std::vector<NtDesc>& d, hipStream_t s, int kind
   ar.launch([=] { HIPCHK(nt_launch(prec, conj, dd, n, 0, total, 0, 1, nullptr, blocks, s, kind)); });
 }
 
+// Tile edge of a bf16 product of `units` 64 x 64 tiles (times the K chunks that
+// run side by side): small ones up to two rounds of one workgroup a CU.  Whole
+// batches of 16-orbital fragments (10 tiles each, N_IP = 256, 2x2x2 mesh), small
+// against large: 1 fragment 140 / 291 us, 25 fragments 279 / 411, 50 (500 tiles)
+// 464 / 556; from 600 tiles on the large ones share each CU between two.
+int x3_tile(long long units) { return units <= max_gemm_blocks() / 8 * 2 ? X3_SMALL : X3_TILE; }
+
 // U^q = R^q W^q on bf16 operands.  The single-bf16 product runs the ring
 // pipeline (one workgroup a CU), the bf16x3 one the two-stage pipeline with
 // two workgroups a CU, whatever the tiling (1000-k shape, 14400 pair rows:
@@ -355,13 +362,15 @@ void run_nt(Arena& ar, int conj, std::vector<NtDesc>& d, hipStream_t s, int kind
 // against 0.119 for the triangular factor product, 0.146 against 0.141 for
 // the full one).
 void run_u16(Arena& ar, int prec, std::vector<NtDesc>& d, hipStream_t s) {
-  const long long total = x3_plan(d.data(), (int)d.size());
+  const int n = (int)d.size();
+  long long total = x3_plan(d.data(), n, X3_SMALL);
   if (total == 0) return;
+  const int tile = x3_tile(total);
+  if (tile != X3_SMALL) total = x3_plan(d.data(), n, tile);
   NtDesc* dd = ar.put(d.data(), d.size(), s);
   const bool ring = prec == 3;
   const int cu = max_gemm_blocks() / 8;
-  const int n = (int)d.size();
-  ar.launch([=] { HIPCHK(x3_launch(prec, dd, n, 0, total, 0, 1, nullptr, ring ? cu : 2 * cu, s, 2, ring)); });
+  ar.launch([=] { HIPCHK(x3_launch(prec, dd, n, 0, total, 0, 1, nullptr, ring ? cu : 2 * cu, s, 2, ring, tile)); });
 }
 
 // How the tiles of a fragment contraction of `total` tiles and nch chunks of
@@ -404,11 +413,12 @@ long long part_bytes_wanted(long long total, int nch, long long tile_bytes, int 
 void run_contraction(Arena& ar, int prec, std::vector<NtDesc>& d, int nch, hipStream_t s, char* part,
                      long long part_bytes, const LaunchMark& mark) {
   const bool bf = prec >= 2;
-  const int tile = bf ? X3_TILE : NT_TILE;
-  const long long total = bf ? x3_plan(d.data(), (int)d.size()) : nt_plan(d.data(), (int)d.size());
-  if (total == 0) return;
-  NtDesc* dd = ar.put(d.data(), d.size(), s);
   const int nd = (int)d.size();
+  long long total = bf ? x3_plan(d.data(), nd, X3_SMALL) : nt_plan(d.data(), nd);
+  if (total == 0) return;
+  const int tile = bf ? x3_tile(total * nch) : NT_TILE;
+  if (bf && tile != X3_SMALL) total = x3_plan(d.data(), nd, tile);
+  NtDesc* dd = ar.put(d.data(), d.size(), s);
   // the ring pipeline of the bf16 kernels when the tiling asks for one
   // workgroup a CU
   const bool ring = bf && t_wg_per_cu == 1;
@@ -418,7 +428,7 @@ void run_contraction(Arena& ar, int prec, std::vector<NtDesc>& d, int nch, hipSt
   ar.launch([=] {
     auto go = [&](long long t0, long long nt, int c0, int nc, cplx* pt) {
       if (mark) mark(true);
-      HIPCHK(bf ? x3_launch(prec, dd, nd, t0, nt, c0, nc, pt, blocks, s, 3, ring)
+      HIPCHK(bf ? x3_launch(prec, dd, nd, t0, nt, c0, nc, pt, blocks, s, 3, ring, tile)
                 : nt_launch(prec, 2, dd, nd, t0, nt, c0, nc, pt, blocks, s, 3));
       if (mark) mark(false);
     };
@@ -433,7 +443,7 @@ void run_contraction(Arena& ar, int prec, std::vector<NtDesc>& d, int nch, hipSt
       for (int c = 0; c < nch; c += sp.per) {
         const int nc = std::min(sp.per, nch - c);
         go(sp.whole, sp.rest, c, nc, (cplx*)part);
-        HIPCHK(nt_fold_launch(dd, nd, tile, bf ? X3_TILE : nt_part_tile(sp.rest, nc), sp.whole, sp.rest, c, nc,
+        HIPCHK(nt_fold_launch(dd, nd, tile, bf ? tile : nt_part_tile(sp.rest, nc), sp.whole, sp.rest, c, nc,
                               (const cplx*)part, s));
       }
   });
@@ -1407,14 +1417,18 @@ EriChunks eri_chunks(isdf_ctx c, int prec) {
 // Room that partial blocks of the (unblocked) contraction of these fragments
 // are worth.
 long long part_wanted(isdf_ctx c, const std::vector<FragIn>& fr, int prec) {
-  const int tile = prec >= 2 ? X3_TILE : NT_TILE;
-  long long total = 0;
-  for (const FragIn& f : fr) {
-    const long long t = ((long long)f.nf * f.nf + tile - 1) / tile;
-    total += t * (t + 1) / 2;
-  }
+  const int nch = eri_chunks(c, prec).n;
+  auto tiles = [&](int edge) {
+    long long total = 0;
+    for (const FragIn& f : fr) {
+      const long long t = ((long long)f.nf * f.nf + edge - 1) / edge;
+      total += t * (t + 1) / 2;
+    }
+    return total;
+  };
+  const int tile = prec >= 2 ? x3_tile(tiles(X3_SMALL) * nch) : NT_TILE;
   const int blocks = prec >= 2 && t_wg_per_cu == 1 ? max_gemm_blocks() / 8 : gemm_blocks();
-  return part_bytes_wanted(total, eri_chunks(c, prec).n, (long long)tile * tile * sizeof(cplx), blocks);
+  return part_bytes_wanted(tiles(tile), nch, (long long)tile * tile * sizeof(cplx), blocks);
 }
 
 // Device tables of one pair transform over pair range [p0, p0 + np) of each

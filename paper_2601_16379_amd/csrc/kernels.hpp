@@ -119,9 +119,10 @@ int nt_part_tile(long long nt, int nc);
 hipError_t nt_fold_launch(const NtDesc* descs_dev, int ndesc, int tile, int edge, long long t0, long long nt, int c0,
                           int nc, const cplx* part, hipStream_t s);
 
-// Tile counts of the bf16 products (128 x 128 tiles)
+// Tile counts of the bf16 products (tile x tile, X3_TILE or X3_SMALL)
 constexpr int X3_TILE = 128;
-long long x3_plan(NtDesc* d, int n);
+constexpr int X3_SMALL = 64;          // tiles of launches that would leave most CUs idle
+long long x3_plan(NtDesc* d, int n, int tile);
 // G[(pq)][(sr)] (Hermitian, lower triangle computed; the contraction over the
 // classes {q, -q}) -> eri[p][q][r][s] = G[(pq)][(sr)] + conj(G[(qp)][(rs)])
 // for n fragments in one launch: fragment f reads e + eoff[f] and writes
@@ -136,9 +137,11 @@ hipError_t eri_scatter_batch_launch(const cplx* e, const long long* eoff, cplx* 
 // partial sums of the segment in C, epi 3 stores the operand format), or room
 // for nt * nseg partial tiles (128 x 128 c128 each), as in nt_launch.
 // ring: the ring pipeline (four LDS stages, one workgroup a CU, the next
-// stage's fragments read during the MFMAs; same results bit for bit).
+// stage's fragments read during the MFMAs; same results bit for bit).  tile: as
+// planned; X3_SMALL always runs its own ring (eight stages, one workgroup a CU;
+// the same results again, partial tiles 64 x 64).
 hipError_t x3_launch(int fmt, const NtDesc* descs_dev, int ndesc, long long t0, long long nt, int seg0, int nseg,
-                     cplx* part, int max_blocks, hipStream_t s, int kind, bool ring = false);
+                     cplx* part, int max_blocks, hipStream_t s, int kind, bool ring, int tile);
 // mixed-precision fragment contraction: classes {q, -q} summed in FP32 per
 // launch (one contiguous K range of the classes of a group, the classes
 // split into balanced groups), FP64 across launches.  The initial tiling of

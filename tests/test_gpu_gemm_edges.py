@@ -99,3 +99,20 @@ def test_pair_transform_points(kmesh, n_ip):
     w = np.stack([ctx.get_kernel(q) for q in range(cfg.n_k)])
     _check(cfg, ctx, x, w, [1, 2, 5, 7], ["fp64", "fp32", "bf16x3"])
     ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["bf16x3", "bf16"])
+@pytest.mark.parametrize("n_ip", [33, 72, 129])
+def test_small_bf16_tiles_same_bits(prec, n_ip):
+    """Few 64 x 64 tiles take the small-tile kernel, many the 128 x 128 ones:
+    a fragment alone and in a batch of over two rounds of tiles gets the same
+    sums in the same order, so the same bits."""
+    import torch
+    cfg, ctx, x, w = _context(n_ip)
+    sizes = [1, 5, 9, 12] + [40] * 4              # 4 x 325 tiles of 64 in the large ones alone
+    dev = [torch.from_numpy(inp.make_fragment(cfg, f, n)).cuda() for f, n in enumerate(sizes)]
+    batch = ctx.fragment_eri(dev, prec)
+    for f in range(4):
+        one = ctx.fragment_eri([dev[f]], prec)[0]
+        assert torch.equal(one, batch[f]), (sizes[f], float((one - batch[f]).abs().max()))
+    ctx.close()
