@@ -697,7 +697,9 @@ __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, lon
     const int seg = seg0 + (int)(u / nt);
     const NtTile tl = nt_tile(descs, ndesc, t0 + u % nt);
     const NtDesc d = descs[tl.desc];
-    const int b = tl.b, tm = tl.tm, tn = tl.tn;
+    const int b = tl.b, tm = tl.tm;
+    int tn = tl.tn;
+    if (KIND == 2 && d.rot) tn = (tn + (b * d.tiles_m + tm) / d.rot) % d.tiles_n;
     cplx* pt = part ? part + u * (T * T) : nullptr;
     const int m0 = tm * T, n0 = tn * T;
     // interleaved formats: logical element e at u16 EU*e (e a multiple of 8)

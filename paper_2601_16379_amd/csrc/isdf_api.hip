@@ -14,6 +14,7 @@
 #include <deque>
 #include <functional>
 #include <map>
+#include <numeric>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -367,10 +368,18 @@ void run_u16(Arena& ar, int prec, std::vector<NtDesc>& d, hipStream_t s) {
   if (total == 0) return;
   const int tile = x3_tile(total);
   if (tile != X3_SMALL) total = x3_plan(d.data(), n, tile);
-  NtDesc* dd = ar.put(d.data(), d.size(), s);
   const bool ring = prec == 3;
-  const int cu = max_gemm_blocks() / 8;
-  ar.launch([=] { HIPCHK(x3_launch(prec, dd, n, 0, total, 0, 1, nullptr, ring ? cu : 2 * cu, s, 2, ring, tile)); });
+  const int cu = max_gemm_blocks() / 8, blocks = ring ? cu : 2 * cu;
+  // The column tiles of a triangular factor differ in length, and a workgroup
+  // takes every blocks / 8 -th tile: where that keeps it on a part of the
+  // columns, the order turns once those have been gone through (1000-k shape,
+  // four column tiles, each workgroup on one of them: 14.7 -> 10.0 ms)
+  for (NtDesc& x : d) {
+    const int stride = blocks / 8, g = std::gcd(stride, x.tiles_n);
+    x.rot = x.ktri && g > 1 ? stride / g : 0;
+  }
+  NtDesc* dd = ar.put(d.data(), d.size(), s);
+  ar.launch([=] { HIPCHK(x3_launch(prec, dd, n, 0, total, 0, 1, nullptr, blocks, s, 2, ring, tile)); });
 }
 
 // How the tiles of a fragment contraction of `total` tiles and nch chunks of

@@ -64,6 +64,9 @@ struct NtDesc {
   int cseg;               // K segments per chunk (0 = all)
   int npad;               // epi 3: columns written (zeros from N on); 0 = ldc
   int ktri;               // B[n][k] = 0 for k < n: the mixed kernels start each column
+  // bf16 U^q: column tiles of row r (over the batch) are taken in the order
+  // turned by r / rot (0: as they are)
+  int rot;
                           // tile's K range at its first column (FP64 reads the zeros)
   long long tile_begin;
 };
