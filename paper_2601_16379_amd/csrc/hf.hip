@@ -6,19 +6,31 @@
 
 namespace {
 
-// n[J] = sum_k rho[k][J][J]
+// n[J] = sum_k rho[k][J][J]: 32 threads a J, each every 32nd k (a line of memory
+// an entry, so the time is the depth of the chain of loads: one thread a J
+// measured 0.59 ms at 1000 k, N_IP 416, this 0.04), their sums added in order.
 __global__ __launch_bounds__(256) void hf_diag_sum_kernel(const cplx* __restrict__ rho, int nk, int nip,
                                                         cplx* __restrict__ n) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= nip) return;
+  __shared__ cplx part[32][8];
+  const int jl = threadIdx.x >> 5, t = threadIdx.x & 31;
+  const int j = blockIdx.x * 8 + jl;
   const long long nn = (long long)nip * nip;
   double re = 0.0, im = 0.0;
-  for (int k = 0; k < nk; ++k) {
-    const cplx v = rho[(long long)k * nn + (long long)j * nip + j];
-    re += v.x;
-    im += v.y;
+  if (j < nip) {
+#pragma unroll 8
+    for (int k = t; k < nk; k += 32) {
+      const cplx v = rho[(long long)k * nn + (long long)j * nip + j];
+      re += v.x;
+      im += v.y;
+    }
   }
-  n[j] = cmk(re, im);
+  part[t][jl] = cmk(re, im);
+  __syncthreads();
+  if (threadIdx.x < 8 && blockIdx.x * 8 + threadIdx.x < nip) {
+    cplx x = part[0][threadIdx.x];
+    for (int i = 1; i < 32; ++i) x = cadd(x, part[i][threadIdx.x]);
+    n[blockIdx.x * 8 + threadIdx.x] = x;
+  }
 }
 
 // v[I] = scale * sum_J W[I][J] n[J] (W conjugated when conj): one wavefront
@@ -55,7 +67,7 @@ __global__ __launch_bounds__(256) void hf_scale_kernel(const cplx* __restrict__ 
 }  // namespace
 
 hipError_t hf_diag_sum_launch(const cplx* rho, int nk, int nip, cplx* n, hipStream_t s) {
-  hipLaunchKernelGGL(hf_diag_sum_kernel, dim3((nip + 255) / 256), dim3(256), 0, s, rho, nk, nip, n);
+  hipLaunchKernelGGL(hf_diag_sum_kernel, dim3((nip + 7) / 8), dim3(256), 0, s, rho, nk, nip, n);
   return hipGetLastError();
 }
 

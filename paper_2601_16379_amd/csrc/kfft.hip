@@ -314,129 +314,123 @@ __global__ __launch_bounds__(256) void xconv_kernel(XconvArgs a, int etile) {
   }
 }
 
-// The exchange convolution on a fixed M1 x M2 x M3 mesh with every line in
-// registers (as kconv_lines_kernel): LDS holds the tiles of rho and W, each
-// [k][etile] with rows padded to an odd stride.  The axis-3 lines of rho
-// and of W come straight from HBM and are transformed (rho with exp(-i k.R),
-// W with exp(+i q.R)), the axis-2 lines of both pass through LDS, the
-// axis-1 lines of both are transformed, multiplied and transformed back in
-// registers, and the product goes back along axes 2 and 3, the last
-// straight to HBM: five LDS passes and four barriers a tile.
-template <int M1, int M2, int M3>
-__global__ __launch_bounds__(512) void xconv_lines_kernel(XconvArgs a, int etile, int ntiles) {
+// The exchange convolution on a fixed M x M x M mesh with every line in
+// registers (as kconv_lines_kernel), one line a thread.  W goes through the LDS
+// tile [k][etile] (rows padded to an odd stride) first: axis 3 straight from
+// HBM, axis 2 in LDS, and its axis-1 lines stay in the registers of their
+// threads; then rho through the same tile, multiplied on its axis-1 lines and
+// taken back along axes 1, 2 and 3, the last straight to HBM.
+// Bound: rho read and written once and W read (10^3 mesh, N_IP 416: 2.8 + 2.8 +
+// 1.4 to 2.8 GB).  One tile in LDS lets two workgroups share a CU, whose loads
+// cover each other's passes: 3.53 -> 2.25 ms against rho and W side by side (128 KB,
+// one workgroup a CU).
+template <int M>
+__global__ __launch_bounds__(640, 4) void xconv_lines_kernel(XconvArgs a, int etile, int ntiles) {
   extern __shared__ cplx xl[];
-  constexpr int NK = M1 * M2 * M3;
   const int per = (ntiles + 7) >> 3;
   const int tile = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
   if (tile >= ntiles) return;
   const int eshift = __builtin_ctz(etile);
-  const int rs = M3 * etile + 1;
-  cplx* br = xl;
-  cplx* bw = xl + M1 * M2 * rs;
+  const int rs = M * etile + 1;
   const long long e0 = (long long)tile * etile;
-  const long long rem = a.n_elem - e0;
-  const int ne = rem < etile ? (int)rem : etile;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  for (int l = tid; l < (NK / M3) << eshift; l += nt) {
-    const int e = l & (etile - 1), k12 = l >> eshift;
-    cplx x[M3], y[M3];
+  const int l = threadIdx.x, e = l & (etile - 1), r = l >> eshift;
+  const bool on = l < (M * M) << eshift;             // this thread has a line
+  const bool in = on && e0 + e < a.n_elem;
+  cplx* p3 = xl + r * rs + e;                                 // axis 3: (r1, r2) = r, stride etile
+  cplx* p2 = xl + (r / M) * M * rs + (r % M) * etile + e;     // axis 2: (r1, r3), stride rs
+  cplx* p1 = xl + (r / M) * rs + (r % M) * etile + e;         // axis 1: (r2, r3), stride M rs
+  cplx x[M], y[M];
 #pragma unroll
-    for (int j = 0; j < M3; ++j) {
-      x[j] = y[j] = cmk(0.0, 0.0);
-      if (e < ne) {
-        const int k = k12 * M3 + j;
-        x[j] = a.rho[(long long)k * a.n_elem + e0 + e];
-        const int sel = a.wsel[k];
-        y[j] = a.w[(long long)(sel >> 1) * a.n_elem + e0 + e];
-        if (sel & 1) y[j].y = -y[j].y;
-      }
-    }
-    dft_line<M3, -1>(x);
-    dft_line<M3, 1>(y);
-    const int o = k12 * rs + e;
-#pragma unroll
-    for (int j = 0; j < M3; ++j) {
-      br[o + j * etile] = x[j];
-      bw[o + j * etile] = y[j];
+  for (int j = 0; j < M; ++j) {
+    y[j] = cmk(0.0, 0.0);
+    if (in) {
+      const int sel = a.wsel[r * M + j];
+      y[j] = a.w[(long long)(sel >> 1) * a.n_elem + e0 + e];
+      if (sel & 1) y[j].y = -y[j].y;
     }
   }
-  __syncthreads();
-  for (int l = tid; l < (NK / M2) << eshift; l += nt) {
-    const int e = l & (etile - 1), r = l >> eshift;
-    const int o = (r / M3) * M2 * rs + (r % M3) * etile + e;
-    cplx x[M2], y[M2];
+  if (on) {
+    dft_line<M, 1>(y);
 #pragma unroll
-    for (int j = 0; j < M2; ++j) {
-      x[j] = br[o + j * rs];
-      y[j] = bw[o + j * rs];
-    }
-    dft_line<M2, -1>(x);
-    dft_line<M2, 1>(y);
-#pragma unroll
-    for (int j = 0; j < M2; ++j) {
-      br[o + j * rs] = x[j];
-      bw[o + j * rs] = y[j];
-    }
+    for (int j = 0; j < M; ++j) p3[j * etile] = y[j];
   }
   __syncthreads();
-  for (int l = tid; l < (NK / M1) << eshift; l += nt) {
-    const int e = l & (etile - 1), r = l >> eshift;
-    const int o = (r / M3) * rs + (r % M3) * etile + e;
-    cplx x[M1], y[M1];
+  if (on) {
 #pragma unroll
-    for (int j = 0; j < M1; ++j) {
-      x[j] = br[o + j * M2 * rs];
-      y[j] = bw[o + j * M2 * rs];
-    }
-    dft_line<M1, -1>(x);
-    dft_line<M1, 1>(y);
+    for (int j = 0; j < M; ++j) y[j] = p2[j * rs];
+    dft_line<M, 1>(y);
 #pragma unroll
-    for (int j = 0; j < M1; ++j) x[j] = cmul(x[j], y[j]);
-    dft_line<M1, 1>(x);
-#pragma unroll
-    for (int j = 0; j < M1; ++j) br[o + j * M2 * rs] = x[j];
+    for (int j = 0; j < M; ++j) p2[j * rs] = y[j];
   }
   __syncthreads();
-  for (int l = tid; l < (NK / M2) << eshift; l += nt) {
-    const int e = l & (etile - 1), r = l >> eshift;
-    const int o = (r / M3) * M2 * rs + (r % M3) * etile + e;
-    cplx x[M2];
+  if (on) {
 #pragma unroll
-    for (int j = 0; j < M2; ++j) x[j] = br[o + j * rs];
-    dft_line<M2, 1>(x);
+    for (int j = 0; j < M; ++j) y[j] = p1[j * M * rs];
+    dft_line<M, 1>(y);
+  }
+  const cplx* rho = a.rho + (long long)(r * M) * a.n_elem + e0 + e;
 #pragma unroll
-    for (int j = 0; j < M2; ++j) br[o + j * rs] = x[j];
+  for (int j = 0; j < M; ++j) {
+    x[j] = cmk(0.0, 0.0);
+    if (in) x[j] = rho[j * a.n_elem];
+  }
+  __syncthreads();                                   // every line of W is in registers
+  if (on) {
+    dft_line<M, -1>(x);
+#pragma unroll
+    for (int j = 0; j < M; ++j) p3[j * etile] = x[j];
   }
   __syncthreads();
-  for (int l = tid; l < (NK / M3) << eshift; l += nt) {
-    const int e = l & (etile - 1), k12 = l >> eshift;
-    if (e >= ne) continue;
-    cplx x[M3];
+  if (on) {
 #pragma unroll
-    for (int j = 0; j < M3; ++j) x[j] = br[k12 * rs + e + j * etile];
-    dft_line<M3, 1>(x);
+    for (int j = 0; j < M; ++j) x[j] = p2[j * rs];
+    dft_line<M, -1>(x);
 #pragma unroll
-    for (int j = 0; j < M3; ++j) a.rho[(long long)(k12 * M3 + j) * a.n_elem + e0 + e] = cscale(x[j], a.scale);
+    for (int j = 0; j < M; ++j) p2[j * rs] = x[j];
+  }
+  __syncthreads();
+  if (on) {
+#pragma unroll
+    for (int j = 0; j < M; ++j) x[j] = p1[j * M * rs];
+    dft_line<M, -1>(x);
+#pragma unroll
+    for (int j = 0; j < M; ++j) x[j] = cmul(x[j], y[j]);
+    dft_line<M, 1>(x);
+#pragma unroll
+    for (int j = 0; j < M; ++j) p1[j * M * rs] = x[j];
+  }
+  __syncthreads();
+  if (on) {
+#pragma unroll
+    for (int j = 0; j < M; ++j) x[j] = p2[j * rs];
+    dft_line<M, 1>(x);
+#pragma unroll
+    for (int j = 0; j < M; ++j) p2[j * rs] = x[j];
+  }
+  __syncthreads();
+  if (in) {
+#pragma unroll
+    for (int j = 0; j < M; ++j) x[j] = p3[j * etile];
+    dft_line<M, 1>(x);
+    cplx* out = a.rho + (long long)(r * M) * a.n_elem + e0 + e;
+#pragma unroll
+    for (int j = 0; j < M; ++j) out[j * a.n_elem] = cscale(x[j], a.scale);
   }
 }
 
-template <int M1, int M2, int M3>
+template <int M>
 hipError_t xconv_lines_launch(const XconvArgs& a, hipStream_t s) {
-  constexpr int NK = M1 * M2 * M3;
-  constexpr int LMAX = NK / (M1 < M2 ? (M1 < M3 ? M1 : M3) : (M2 < M3 ? M2 : M3));
-  // largest power-of-two element tile with at most 512 lines an axis pass
-  // and both padded tiles in at most 160 KB of LDS
+  // largest power-of-two element tile with at most 640 lines an axis pass and
+  // two padded tiles in the 160 KB of LDS
   int etile = 1;
-  while (LMAX * etile * 2 <= 512 && 2 * (size_t)M1 * M2 * (M3 * etile * 2 + 1) * sizeof(cplx) <= 160 * 1024)
-    etile *= 2;
+  while (M * M * etile * 2 <= 640 && (size_t)M * M * (M * etile * 2 + 1) * sizeof(cplx) <= 80 * 1024) etile *= 2;
   const long long ntiles = (a.n_elem + etile - 1) / etile;
   if (ntiles <= 0) return hipSuccess;
   if (ntiles > (1LL << 28)) return hipErrorInvalidValue;
   const long long blocks = ((ntiles + 7) / 8) * 8;
-  const int threads = (LMAX * etile + 63) / 64 * 64;
-  const size_t lds = 2 * (size_t)M1 * M2 * (M3 * etile + 1) * sizeof(cplx);
-  hipLaunchKernelGGL((xconv_lines_kernel<M1, M2, M3>), dim3((unsigned)blocks), dim3(threads), lds, s, a, etile,
-                     (int)ntiles);
+  const int threads = (M * M * etile + 63) / 64 * 64;
+  const size_t lds = (size_t)M * M * (M * etile + 1) * sizeof(cplx);
+  hipLaunchKernelGGL(xconv_lines_kernel<M>, dim3((unsigned)blocks), dim3(threads), lds, s, a, etile, (int)ntiles);
   return hipGetLastError();
 }
 
@@ -1472,9 +1466,9 @@ hipError_t xconv_launch(const XconvArgs& a, hipStream_t s) {
   if (!a.rho || !a.w || !a.wsel) return hipErrorInvalidValue;
   if (a.m1 > MAXM || a.m2 > MAXM || a.m3 > MAXM || a.m1 < 1 || a.m2 < 1 || a.m3 < 1) return hipErrorInvalidValue;
   if (a.m1 == a.m2 && a.m2 == a.m3) {
-    if (a.m1 == 6) return xconv_lines_launch<6, 6, 6>(a, s);
-    if (a.m1 == 8) return xconv_lines_launch<8, 8, 8>(a, s);
-    if (a.m1 == 10) return xconv_lines_launch<10, 10, 10>(a, s);
+    if (a.m1 == 6) return xconv_lines_launch<6>(a, s);
+    if (a.m1 == 8) return xconv_lines_launch<8>(a, s);
+    if (a.m1 == 10) return xconv_lines_launch<10>(a, s);
   }
   const int nk = a.m1 * a.m2 * a.m3;
   int etile = 1;                        // two [nk][etile] columns in at most 64 KB

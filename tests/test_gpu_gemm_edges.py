@@ -116,3 +116,27 @@ def test_small_bf16_tiles_same_bits(prec, n_ip):
         one = ctx.fragment_eri([dev[f]], prec)[0]
         assert torch.equal(one, batch[f]), (sizes[f], float((one - batch[f]).abs().max()))
     ctx.close()
+
+
+@pytest.mark.parametrize("kmesh", [(6, 6, 6), (8, 8, 8)])
+@pytest.mark.parametrize("n_ip", [7, 16, 19])
+def test_jk_cubes(kmesh, n_ip):
+    """J and K on the meshes whose exchange convolution keeps W's lines in
+    registers, at element counts that do and do not fill its tiles; 1e-11
+    relative given the GPU's W (FP64 k transforms of N_IP^2 elements)."""
+    import paper_2601_16379_amd as pkg
+    from oracle import hf
+    cfg = dataclasses.replace(inp.get_config("t_small_k2"), kmesh=kmesh, n_ip=n_ip)
+    d = inp.make_inputs(cfg)
+    ctx = pkg.Isdf(d.lattice, cfg.grid, cfg.kmesh, d.orbitals, d.ip_index)
+    ctx.fit()
+    ctx.coulomb_kernel("fp64")
+    x = ko.ip_values(d.orbitals, d.ip_index)
+    w = np.stack([ctx.get_kernel(q) for q in range(cfg.n_k)])
+    dm = inp.make_density(cfg)
+    j, k = ctx.hf_jk(dm)
+    ks = [0, 1, cfg.n_k // 2 + 3, cfg.n_k - 1]
+    k_ref, j_ref = hf.exchange_at(x, w, dm, cfg.kmesh, ks), hf.coulomb(x, w, dm)
+    assert np.max(np.abs(k[ks] - k_ref)) <= 1e-11 * np.max(np.abs(k_ref))
+    assert np.max(np.abs(j - j_ref)) <= 1e-11 * np.max(np.abs(j_ref))
+    ctx.close()
