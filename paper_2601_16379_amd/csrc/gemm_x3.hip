@@ -386,7 +386,7 @@ __device__ inline void tri_live(bool tri, int s, int sk, int cb0, bool& l0, bool
 // each): two LDS stages, each stage's fragments read from LDS at its start
 // (the waves of the other workgroup keep the matrix cores busy meanwhile),
 // copies one stage ahead, one barrier a stage.
-template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ, bool TRI>
+template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ>
 __device__ inline void tile_body(const NtDesc& d, int b, int m0, int n0, int kcur,
                                  const unsigned short* const (&asrc)[NCOPY], const unsigned short* const (&bsrc)[NCOPY],
                                  const int (&gslot)[NCOPY], int rb0, int cb0, char* smem, int wave, int lane,
@@ -424,13 +424,7 @@ __device__ inline void tile_body(const NtDesc& d, int b, int m0, int n0, int kcu
     read_frags_b<F>(buf, f, cb0, lr, lk);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     settle(f);
-    if constexpr (TRI) {
-      bool l0, l1;
-      tri_live(d.ktri != 0, s, SK, cb0, l0, l1);
-      if (!idle) stage_mma_tri<F, NI, NJ, A_CONJ, B_CONJ>(f, c_re, c_im, l0, l1);
-    } else {
-      if (!idle) stage_mma<F, NI, NJ, A_CONJ, B_CONJ>(f, c_re, c_im);
-    }
+    if (!idle) stage_mma<F, NI, NJ, A_CONJ, B_CONJ>(f, c_re, c_im);
   }
   if (!idle) tile_epilogue<F, NI, NJ>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first, part);
 }
@@ -441,8 +435,8 @@ __device__ inline void tile_body(const NtDesc& d, int b, int m0, int n0, int kcu
 // everyone's), and every wave has read stage s, so its buffer takes the
 // copies of stage s + RING.  One barrier a stage; the copies run up to
 // RING - 1 stages ahead of the MFMAs.
-template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ, bool TRI>
-__device__ inline void ring_step(int s, int nst, int kcur, bool tri, Frag<NI, NJ>& cur, Frag<NI, NJ>& nxt,
+template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ>
+__device__ inline void ring_step(int s, int nst, int kcur, Frag<NI, NJ>& cur, Frag<NI, NJ>& nxt,
                                  f16v (&c_re)[NI][NJ], f16v (&c_im)[NI][NJ],
                                  const unsigned short* const (&asrc)[NCOPY],
                                  const unsigned short* const (&bsrc)[NCOPY], const int (&gslot)[NCOPY],
@@ -464,13 +458,7 @@ __device__ inline void ring_step(int s, int nst, int kcur, bool tri, Frag<NI, NJ
     read_frags_a<F>(nb, nxt, rb0, lr, lk);
     read_frags_b<F>(nb, nxt, cb0, lr, lk);
   }
-  if constexpr (TRI) {
-    bool l0, l1;
-    tri_live(tri, s, SK, cb0, l0, l1);
-    if (!idle) stage_mma_tri<F, NI, NJ, A_CONJ, B_CONJ>(cur, c_re, c_im, l0, l1);
-  } else {
-    if (!idle) stage_mma<F, NI, NJ, A_CONJ, B_CONJ>(cur, c_re, c_im);
-  }
+  if (!idle) stage_mma<F, NI, NJ, A_CONJ, B_CONJ>(cur, c_re, c_im);
   if (more) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     settle(nxt);
@@ -479,7 +467,7 @@ __device__ inline void ring_step(int s, int nst, int kcur, bool tri, Frag<NI, NJ
 
 // K loop and epilogue of one tile on the ring pipeline (same blocks, MFMA
 // order and epilogues as tile_body, so the same results bit for bit).
-template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ, bool TRI>
+template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ>
 __device__ inline void tile_body_ring(const NtDesc& d, int b, int m0, int n0, int kcur,
                                       const unsigned short* const (&asrc)[NCOPY],
                                       const unsigned short* const (&bsrc)[NCOPY], const int (&gslot)[NCOPY],
@@ -514,10 +502,10 @@ __device__ inline void tile_body_ring(const NtDesc& d, int b, int m0, int n0, in
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   settle(f0);
   for (int s = 0; s < nst; s += 2) {
-    ring_step<F, NI, NJ, A_CONJ, B_CONJ, TRI>(s, nst, kcur, d.ktri != 0, f0, f1, c_re, c_im, asrc, bsrc, gslot, rb0,
+    ring_step<F, NI, NJ, A_CONJ, B_CONJ>(s, nst, kcur, f0, f1, c_re, c_im, asrc, bsrc, gslot, rb0,
                                               cb0, smem, wave, lr, lk, idle);
     if (s + 1 < nst)
-      ring_step<F, NI, NJ, A_CONJ, B_CONJ, TRI>(s + 1, nst, kcur, d.ktri != 0, f1, f0, c_re, c_im, asrc, bsrc, gslot,
+      ring_step<F, NI, NJ, A_CONJ, B_CONJ>(s + 1, nst, kcur, f1, f0, c_re, c_im, asrc, bsrc, gslot,
                                                 rb0, cb0, smem, wave, lr, lk, idle);
   }
   if (!idle) tile_epilogue<F, NI, NJ>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first, part);
@@ -535,7 +523,7 @@ __device__ inline void tile_body_ring(const NtDesc& d, int b, int m0, int n0, in
 // each): two LDS stages, each stage's fragments read from LDS at its start
 // (the waves of the other workgroup keep the matrix cores busy meanwhile),
 // copies two stages ahead.
-template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ, bool TRI>
+template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ>
 __device__ inline void tile_body_2b(const NtDesc& d, int b, int m0, int n0, int kcur,
                                  const unsigned short* const (&asrc)[NCOPY], const unsigned short* const (&bsrc)[NCOPY],
                                  const int (&gslot)[NCOPY], int rb0, int cb0, char* smem, int wave, int lane,
@@ -578,19 +566,7 @@ __device__ inline void tile_body_2b(const NtDesc& d, int b, int m0, int n0, int 
       stage_copy<F>(asrc, gslot, (s + NBUF) * SK, kcur, buf, wave);
       stage_copy<F>(bsrc, gslot, (s + NBUF) * SK, kcur, buf + OPER_B, wave);
     }
-    if constexpr (TRI) {
-      bool l0, l1;
-      tri_live(d.ktri != 0, s, SK, cb0, l0, l1);
-      if (!idle) stage_mma_tri<F, NI, NJ, A_CONJ, B_CONJ>(f, c_re, c_im, l0, l1);
-    } else if (!idle) {
-      if constexpr (F == 2) {
-        mma_half<NI, NJ, A_CONJ, B_CONJ>(f, 0, c_re, c_im);
-        if (NJ == 2) mma_half<NI, NJ, A_CONJ, B_CONJ>(f, NJ - 1, c_re, c_im);
-      } else {
-        mma_single<NI, NJ, A_CONJ, B_CONJ>(f, 0, c_re, c_im);
-        if (NJ == 2) mma_single<NI, NJ, A_CONJ, B_CONJ>(f, NJ - 1, c_re, c_im);
-      }
-    }
+    if (!idle) stage_mma<F, NI, NJ, A_CONJ, B_CONJ>(f, c_re, c_im);
   }
   if (!idle) tile_epilogue<F, NI, NJ>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first, part);
 }
@@ -677,6 +653,243 @@ __device__ inline void tile_body_small(const NtDesc& d, int b, int m0, int n0, i
   if (!idle) tile_epilogue<F, 1, 1, X3_SMALL>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first, part);
 }
 
+// ---- U^q = R^q W^q on 128 x 128 tiles as one stream of stages ----
+// One workgroup a CU; the stages of its tiles follow one another in UR LDS
+// buffers, copied up to UR - 1 ahead across the tile boundaries, and a tile's
+// outputs go to the operand format straight from the accumulators (quad_store),
+// past the LDS.  The MFMAs and their order are those of tile_body.
+constexpr int UR = 4;
+
+// The copy side: the tile being copied and its next stage.
+template <int F>
+struct UFlow {
+  const unsigned short *a[NCOPY], *b[NCOPY];
+  int gslot[NCOPY];
+  int kcur, k0;                           // of the tile
+  int it;                                 // its place in the workgroup's sequence
+  int gi;                                 // stages copied in all
+  bool more;
+};
+
+struct UTile {
+  int b, m0, n0;
+};
+__device__ inline int u_unit(int it, int nt) { return (it & 7) * ((nt + 7) >> 3) + (it >> 3); }   // XCD-contiguous
+__device__ inline bool u_valid(int it, int nt) { return it < ((nt + 7) & ~7) && u_unit(it, nt) < nt; }
+// (the quotients are formed in vector registers and read back: everything that
+// steers the stream stays scalar)
+__device__ inline int u_div(int x, int y) { return __builtin_amdgcn_readfirstlane((unsigned)x / (unsigned)y); }
+__device__ inline UTile u_tile(const NtDesc& d, int nt, int it) {
+  const int u = u_unit(it, nt), b = u_div(u, d.tiles_per_batch), lt = u - b * d.tiles_per_batch;
+  const int tm = u_div(lt, d.tiles_n);
+  int tn = lt - tm * d.tiles_n;
+  if (d.rot) {
+    tn += u_div(b * d.tiles_m + tm, d.rot);
+    tn -= u_div(tn, d.tiles_n) * d.tiles_n;
+  }
+  return UTile{b, tm * XT, tn * XT};
+}
+
+template <int F>
+__device__ inline void u_start(UFlow<F>& f, const NtDesc& d, int nt, int wave, int lane) {
+  constexpr int EU = Fmt<F>::EU;
+  const UTile t = u_tile(d, nt, f.it);
+  const int kstart = d.ktri ? t.n0 : 0;   // a triangular B contributes from k = n0 on
+  const unsigned short* As = (const unsigned short*)d.A + EU * (t.b * d.sA_bat + kstart);
+  const unsigned short* Bs = (const unsigned short*)d.B + EU * (t.b * d.sB_bat + kstart);
+#pragma unroll
+  for (int j = 0; j < NCOPY; ++j) {
+    const int row = (wave + 4 * j) * 8 + (lane >> 3);
+    f.a[j] = As + EU * ((long long)min(t.m0 + row, d.M - 1) * d.lda) + 8 * f.gslot[j];
+    f.b[j] = Bs + EU * ((long long)min(t.n0 + row, d.N - 1) * d.ldb) + 8 * f.gslot[j];
+  }
+  f.kcur = d.Klast - kstart;
+  f.k0 = 0;
+}
+
+// Copy the next stage of the stream, if there is one.
+template <int F>
+__device__ inline void u_issue(UFlow<F>& f, const NtDesc& d, int nt, char* smem, int wave, int lane) {
+  if (!f.more) return;
+  char* buf = smem + (f.gi % UR) * STAGE_B;
+  if (f.k0 + Fmt<F>::K <= f.kcur) {
+#pragma unroll
+    for (int j = 0; j < NCOPY; ++j) {
+      char* dst = buf + (wave + 4 * j) * 8 * ROW_B;
+      __builtin_amdgcn_global_load_lds((glb_void*)(f.a[j] + Fmt<F>::EU * f.k0), (lds_void*)dst, 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((glb_void*)(f.b[j] + Fmt<F>::EU * f.k0), (lds_void*)(dst + OPER_B), 16, 0, 0);
+    }
+  } else {
+    stage_copy<F>(f.a, f.gslot, f.k0, f.kcur, buf, wave);
+    stage_copy<F>(f.b, f.gslot, f.k0, f.kcur, buf + OPER_B, wave);
+  }
+  ++f.gi;
+  f.k0 += Fmt<F>::K;
+  if (f.k0 >= f.kcur) {
+    f.more = u_valid(f.it + gridDim.x, nt);
+    if (f.more) {
+      f.it += gridDim.x;
+      u_start<F>(f, d, nt, wave, lane);
+    }
+  }
+}
+
+// Wait until a stage has landed: `newer` stages were copied after it.  Where a
+// whole tile's outputs (64 store instructions, counted in order with the copies)
+// were stored after it as well, 40 in flight leave it landed.
+__device__ inline void u_wait(int newer, bool stored) {
+  static_assert(2 * NCOPY == 8 && UR == 4, "the counts below");
+  if (stored) asm volatile("s_waitcnt vmcnt(40)" ::: "memory");
+  else if (newer >= 2) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+  else if (newer == 1) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Stage g of the stream: fragments in `cur`; those of the next stage go to
+// `nxt` (not used after a tile's last).  l0, l1: column blocks that are not
+// zero in B (tri_live), used unless WHOLE.
+template <int F, int NI, int NJ, bool WHOLE>
+__device__ inline void u_step(UFlow<F>& f, const NtDesc& d, int nt, int& g, int ge, bool l0, bool l1,
+                              Frag<NI, NJ>& cur, Frag<NI, NJ>& nxt, f16v (&c_re)[NI][NJ], f16v (&c_im)[NI][NJ],
+                              int rb0, int cb0, char* smem, int wave, int lane) {
+  const int lr = lane & 31, lk = lane >> 5;
+  u_wait(f.gi - 2 - g, g + 1 < ge);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  settle(cur);
+  // stage g + 1 is there and every wave has read stage g: its buffer is free
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  u_issue<F>(f, d, nt, smem, wave, lane);
+  const char* nb = smem + ((g + 1) % UR) * STAGE_B;
+  __builtin_amdgcn_sched_barrier(0);
+  read_frags_a<F>(nb, nxt, rb0, lr, lk);
+  read_frags_b<F>(nb, nxt, cb0, lr, lk);
+  if constexpr (WHOLE) {
+    // the reads spread over the MFMAs: issued ahead of them they fill the LDS
+    // queue, and the MFMAs wait for their turn
+    stage_mma<F, NI, NJ, false, false>(cur, c_re, c_im);
+#pragma unroll
+    for (int i = 0; i < 4 * (NI + NJ); ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                             // a read of LDS
+      __builtin_amdgcn_sched_group_barrier(0x8, NI * NJ * (F == 2 ? 12 : 8) / (4 * (NI + NJ)), 0);   // MFMAs
+    }
+  } else {
+    stage_mma_tri<F, NI, NJ, false, false>(cur, c_re, c_im, l0, l1);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  ++g;
+}
+
+// The outputs of a wave's block (tile_epilogue's layout) in the operand format;
+// columns up to npad are stored, zero from N on.
+template <int F, int NI, int NJ, bool FULL>
+__device__ inline void u_store(const NtDesc& d, int b, int m0, int n0, const f16v (&c_re)[NI][NJ],
+                               const f16v (&c_im)[NI][NJ], int npad, int lane) {
+  constexpr int EB = 2 * Fmt<F>::EU;      // bytes per element
+  const int lr = lane & 31, lk = lane >> 5;
+  char* C = (char*)d.C + EB * ((long long)b * d.sC_bat + (long long)m0 * d.ldc + n0);
+  long long part = 2 * quad_part<F>(4 * lk * d.ldc + lr);
+  asm volatile("" : "+v"(part));          // formed here, not held over the K loop
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const bool in = FULL || n0 + j * 32 + lr < d.N;
+      const bool col = FULL || n0 + j * 32 + (lr & ~7) < npad;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = i * 32 + 8 * (v >> 2) + (v & 3);
+        const float re = in ? c_re[i][j][v] : 0.f, im = in ? c_im[i][j][v] : 0.f;
+        if (FULL || (col && m0 + row + 4 * lk < d.M))
+          quad_store<F>(C + (long long)row * d.ldc * EB + j * 32 * EB + part, re, im);
+      }
+    }
+}
+
+// The stages and outputs of one tile.
+template <int F, int NI, int NJ>
+__device__ inline void u_body(UFlow<F>& f, const NtDesc& d, int nt, const UTile& t, int& g, int& ge, int rb0, int cb0,
+                              char* smem, int wave, int lane) {
+  constexpr int SK = Fmt<F>::K;
+  const int lr = lane & 31, lk = lane >> 5;
+  const int kcur = d.Klast - (d.ktri ? t.n0 : 0);
+  const int nst = (kcur + SK - 1) / SK;
+  // from this stage on every column block of the wave counts (tri_live)
+  const int s1 = d.ktri ? min(nst, (cb0 + (NJ - 1) * 32) / SK) : 0;
+  f16v c_re[NI][NJ], c_im[NI][NJ];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) c_re[i][j][v] = c_im[i][j][v] = 0.f;
+  Frag<NI, NJ> f0, f1;
+  read_frags_a<F>(smem + (g % UR) * STAGE_B, f0, rb0, lr, lk);
+  read_frags_b<F>(smem + (g % UR) * STAGE_B, f0, cb0, lr, lk);
+  int s = 0;
+#pragma unroll 1
+  for (; s < s1; ++s) {
+    bool l0, l1;
+    tri_live(true, s, SK, cb0, l0, l1);
+    u_step<F, NI, NJ, false>(f, d, nt, g, ge, l0, l1, f0, f1, c_re, c_im, rb0, cb0, smem, wave, lane);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    settle(f1);
+    f0 = f1;
+  }
+  // pairs, then an odd one: a loop of one exit keeps the accumulators in place
+  const int pairs = (nst - s) >> 1;
+#pragma unroll 1
+  for (int i = 0; i < pairs; ++i) {
+    u_step<F, NI, NJ, true>(f, d, nt, g, ge, true, true, f0, f1, c_re, c_im, rb0, cb0, smem, wave, lane);
+    u_step<F, NI, NJ, true>(f, d, nt, g, ge, true, true, f1, f0, c_re, c_im, rb0, cb0, smem, wave, lane);
+  }
+  if ((nst - s) & 1)
+    u_step<F, NI, NJ, true>(f, d, nt, g, ge, true, true, f0, f1, c_re, c_im, rb0, cb0, smem, wave, lane);
+  const int npad = d.npad ? d.npad : (int)d.ldc;
+  if (NI == 2 && t.m0 + XT <= d.M && t.n0 + XT <= d.N) {
+    u_store<F, NI, NJ, true>(d, t.b, t.m0 + rb0, t.n0 + cb0, c_re, c_im, npad, lane);
+    ge = f.gi;
+  } else {
+    u_store<F, NI, NJ, false>(d, t.b, t.m0 + rb0, t.n0 + cb0, c_re, c_im, npad, lane);
+  }
+}
+
+// Bound: the matrix cores and what one wave a SIMD cannot lay beside them (0.41
+// busy at 1000 k; the rest outputs, 17 operations a value, and the steps between
+// stages).  Whole tiles one after the other with two workgroups a CU, outputs
+// staged through LDS and every tile's first stages waited for -> now: bf16x3
+// 47.5 k pairs on 4x4x4 (N_IP 520) 6.8 -> 6.5 ms; single bf16 at 216 k (N_IP 520) 5.9 ->
+// 4.8 ms; 1000 k (N_IP 416) 10.0 ms both.  Two workgroups a CU with two stages
+// each measured 7.6, 6.6 and 10.7 ms.
+template <int F>
+__global__ __launch_bounds__(XNT, 1) void zgemm_u16_kernel(NtDesc d, int nt) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];   // UR stages x (A, B)
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (!u_valid(blockIdx.x, nt)) return;
+  UFlow<F> f;
+#pragma unroll
+  for (int j = 0; j < NCOPY; ++j) f.gslot[j] = lds_slot((wave + 4 * j) * 8 + (lane >> 3), lane & 7);
+  f.it = blockIdx.x;
+  f.gi = 0;
+  f.more = true;
+  u_start<F>(f, d, nt, wave, lane);
+#pragma unroll 1
+  for (int i = 0; i < UR; ++i) u_issue<F>(f, d, nt, smem, wave, lane);
+  int g = 0, ge = 0;                      // stages done; stages copied before the last whole tile's stores
+  u_wait(f.gi - 1, false);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  for (int it = blockIdx.x; u_valid(it, nt); it += gridDim.x) {
+    const UTile t = u_tile(d, nt, it);
+    const int wm = wave >> 1, wn = wave & 1;
+    // strips of at most 32 rows or columns: a 32 x 32 block a wave
+    if (d.M - t.m0 <= 32) u_body<F, 1, 1>(f, d, nt, t, g, ge, 0, wave * 32, smem, wave, lane);
+    else if (d.N - t.n0 <= 32) u_body<F, 1, 1>(f, d, nt, t, g, ge, wave * 32, 0, smem, wave, lane);
+    else u_body<F, 2, 2>(f, d, nt, t, g, ge, wm * 64, wn * 64, smem, wave, lane);
+  }
+}
+
 template <int F, bool A_CONJ, bool B_CONJ, int KIND, bool RINGP, bool TWOB = false, int T = XT>
 __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, long long t0, long long nt, int seg0,
                                 int nseg, cplx* part) {
@@ -697,9 +910,7 @@ __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, lon
     const int seg = seg0 + (int)(u / nt);
     const NtTile tl = nt_tile(descs, ndesc, t0 + u % nt);
     const NtDesc d = descs[tl.desc];
-    const int b = tl.b, tm = tl.tm;
-    int tn = tl.tn;
-    if (KIND == 2 && d.rot) tn = (tn + (b * d.tiles_m + tm) / d.rot) % d.tiles_n;
+    const int b = tl.b, tm = tl.tm, tn = tl.tn;
     cplx* pt = part ? part + u * (T * T) : nullptr;
     const int m0 = tm * T, n0 = tn * T;
     // interleaved formats: logical element e at u16 EU*e (e a multiple of 8)
@@ -739,33 +950,33 @@ __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, lon
                                                     lane, idle, first, pt);
     } else if constexpr (RINGP) {
       if (d.M - m0 <= 32)
-        tile_body_ring<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave,
+        tile_body_ring<F, 1, 1, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave,
                                                 lane, diag && wave > 0, first, pt);
       else if (d.N - n0 <= 32)
-        tile_body_ring<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wave * 32, 0, smem, wave,
+        tile_body_ring<F, 1, 1, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wave * 32, 0, smem, wave,
                                                 lane, false, first, pt);
       else
-        tile_body_ring<F, 2, 2, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 64, wn * 64, smem,
+        tile_body_ring<F, 2, 2, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 64, wn * 64, smem,
                                                 wave, lane, diag && wm < wn, first, pt);
     } else if constexpr (TWOB) {
       if (d.M - m0 <= 32)
-        tile_body_2b<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave, lane,
+        tile_body_2b<F, 1, 1, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave, lane,
                                               diag && wave > 0, first, pt);
       else if (d.N - n0 <= 32)
-        tile_body_2b<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wave * 32, 0, smem, wave, lane,
+        tile_body_2b<F, 1, 1, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wave * 32, 0, smem, wave, lane,
                                               false, first, pt);
       else
-        tile_body_2b<F, 2, 2, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 64, wn * 64, smem, wave,
+        tile_body_2b<F, 2, 2, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 64, wn * 64, smem, wave,
                                               lane, diag && wm < wn, first, pt);
     } else {
       if (d.M - m0 <= 32)
-        tile_body<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave, lane,
+        tile_body<F, 1, 1, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave, lane,
                                            diag && wave > 0, first, pt);
       else if (d.N - n0 <= 32)
-        tile_body<F, 1, 1, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wave * 32, 0, smem, wave, lane,
+        tile_body<F, 1, 1, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wave * 32, 0, smem, wave, lane,
                                            false, first, pt);
       else
-        tile_body<F, 2, 2, A_CONJ, B_CONJ, KIND == 2>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 64, wn * 64, smem, wave,
+        tile_body<F, 2, 2, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 64, wn * 64, smem, wave,
                                            lane, diag && wm < wn, first, pt);
     }
   }
@@ -775,9 +986,8 @@ __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, lon
 // the fragment contraction (kind 3, B conjugated)
 #define X3_ARGS const NtDesc *__restrict__ descs, int ndesc, long long t0, long long nt, int seg0, int nseg, cplx *part
 
-template <int KIND>
 __global__ __launch_bounds__(XNT, 2) void zgemm_x3_kernel(X3_ARGS) {
-  x3_tiles<2, false, KIND == 3, KIND, false>(descs, ndesc, t0, nt, seg0, nseg, part);
+  x3_tiles<2, false, true, 3, false>(descs, ndesc, t0, nt, seg0, nseg, part);
 }
 
 // two barriers a stage: the fragment contraction of launches with few tiles
@@ -788,9 +998,9 @@ __global__ __launch_bounds__(XNT, 2) void zgemm_c2b_kernel(X3_ARGS) {
 }
 
 // ring pipeline (one workgroup a CU), both formats
-template <int F, int KIND>
+template <int F>
 __global__ __launch_bounds__(XNT, 1) void zgemm_ring_kernel(X3_ARGS) {
-  x3_tiles<F, false, KIND == 3, KIND, true>(descs, ndesc, t0, nt, seg0, nseg, part);
+  x3_tiles<F, false, true, 3, true>(descs, ndesc, t0, nt, seg0, nseg, part);
 }
 
 // 64 x 64 tiles, a 32 x 32 block a wave, eight LDS stages (one workgroup a CU):
@@ -822,11 +1032,22 @@ long long x3_plan(NtDesc* d, int n, int tile) {
   return acc;
 }
 
+hipError_t u16_launch(int fmt, const NtDesc& d, long long nt, int max_blocks, hipStream_t s) {
+  if (nt <= 0) return hipSuccess;
+  if ((fmt != 2 && fmt != 3) || nt > (1LL << 30) || d.nseg != 1 || d.epi != 3 || d.herm) return hipErrorInvalidValue;
+  const long long u8 = (nt + 7) / 8 * 8;
+  max_blocks = max_blocks / 8 * 8;
+  const dim3 g((unsigned)(u8 < max_blocks ? u8 : max_blocks)), b(XNT);
+  if (fmt == 2) hipLaunchKernelGGL(zgemm_u16_kernel<2>, g, b, UR * STAGE_B, s, d, (int)nt);
+  else hipLaunchKernelGGL(zgemm_u16_kernel<3>, g, b, UR * STAGE_B, s, d, (int)nt);
+  return hipGetLastError();
+}
+
 hipError_t x3_launch(int fmt, const NtDesc* descs_dev, int ndesc, long long t0, long long nt, int seg0, int nseg,
                      cplx* part, int max_blocks, hipStream_t s, int kind, bool ring, int tile) {
   if (nt <= 0 || nseg <= 0) return hipSuccess;
   if ((fmt != 2 && fmt != 3) || (kind != 2 && kind != 3) || (!part && nseg != 1) ||
-      (tile != XT && tile != X3_SMALL))
+      (tile != XT && tile != X3_SMALL) || (kind == 2 && tile != X3_SMALL))
     return hipErrorInvalidValue;
   const long long units = nt * nseg, u8 = (units + 7) / 8 * 8;
   max_blocks = max_blocks / 8 * 8;
@@ -840,23 +1061,17 @@ hipError_t x3_launch(int fmt, const NtDesc* descs_dev, int ndesc, long long t0, 
     else if (kind == 2) X3_GO(zgemm_small16_kernel<3 COMMA 2>, SRING * SSTAGE_B);
     else X3_GO(zgemm_small16_kernel<3 COMMA 3>, SRING * SSTAGE_B);
   } else if (ring) {
-    if (fmt == 2 && kind == 2) X3_GO(zgemm_ring_kernel<2 COMMA 2>, RING * STAGE_B);
-    else if (fmt == 2) X3_GO(zgemm_ring_kernel<2 COMMA 3>, RING * STAGE_B);
-    else if (kind == 2) X3_GO(zgemm_ring_kernel<3 COMMA 2>, RING * STAGE_B);
-    else X3_GO(zgemm_ring_kernel<3 COMMA 3>, RING * STAGE_B);
+    if (fmt == 2) X3_GO(zgemm_ring_kernel<2>, RING * STAGE_B);
+    else X3_GO(zgemm_ring_kernel<3>, RING * STAGE_B);
   } else if (fmt == 3) {
     // single bf16: 32 MFMAs a stage (against 48 in bf16x3) leave less time to
     // cover a one-stage prefetch; the contraction always takes the two-barrier
-    // loop (0.378 against 0.354 of bf16 peak on the 120-orbital 1000-k shape),
-    // U^q the ring
-    if (kind == 2) return hipErrorInvalidValue;
+    // loop (0.378 against 0.354 of bf16 peak on the 120-orbital 1000-k shape)
     X3_GO(zgemm_c2b_kernel<3>, NBUF * STAGE_B);
-  } else if (kind == 2) {
-    X3_GO(zgemm_x3_kernel<2>, NBUF * STAGE_B);
   } else if (units < 2LL * g.x) {
     X3_GO(zgemm_c2b_kernel<2>, NBUF * STAGE_B);
   } else {
-    X3_GO(zgemm_x3_kernel<3>, NBUF * STAGE_B);
+    X3_GO(zgemm_x3_kernel, NBUF * STAGE_B);
   }
 #undef X3_GO
 #undef COMMA

@@ -356,30 +356,24 @@ void run_nt(Arena& ar, int conj, std::vector<NtDesc>& d, hipStream_t s, int kind
 // 464 / 556; from 600 tiles on the large ones share each CU between two.
 int x3_tile(long long units) { return units <= max_gemm_blocks() / 8 * 2 ? X3_SMALL : X3_TILE; }
 
-// U^q = R^q W^q on bf16 operands.  The single-bf16 product runs the ring
-// pipeline (one workgroup a CU), the bf16x3 one the two-stage pipeline with
-// two workgroups a CU, whatever the tiling (1000-k shape, 14400 pair rows:
-// single bf16 0.274 of bf16 peak on the ring against 0.255; bf16x3 0.127
-// against 0.119 for the triangular factor product, 0.146 against 0.141 for
-// the full one).
-void run_u16(Arena& ar, int prec, std::vector<NtDesc>& d, hipStream_t s) {
-  const int n = (int)d.size();
-  long long total = x3_plan(d.data(), n, X3_SMALL);
-  if (total == 0) return;
-  const int tile = x3_tile(total);
-  if (tile != X3_SMALL) total = x3_plan(d.data(), n, tile);
-  const bool ring = prec == 3;
-  const int cu = max_gemm_blocks() / 8, blocks = ring ? cu : 2 * cu;
+// U^q = R^q W^q on bf16 operands.
+void run_u16(Arena& ar, int prec, NtDesc d, hipStream_t s) {
+  const int blocks = max_gemm_blocks() / 8;      // one workgroup a CU
+  const long long small = x3_plan(&d, 1, X3_SMALL);
+  if (small == 0) return;
+  if (x3_tile(small) == X3_SMALL) {
+    NtDesc* dd = ar.put(&d, 1, s);
+    ar.launch([=] { HIPCHK(x3_launch(prec, dd, 1, 0, small, 0, 1, nullptr, blocks, s, 2, false, X3_SMALL)); });
+    return;
+  }
+  const long long total = x3_plan(&d, 1, X3_TILE);
   // The column tiles of a triangular factor differ in length, and a workgroup
   // takes every blocks / 8 -th tile: where that keeps it on a part of the
   // columns, the order turns once those have been gone through (1000-k shape,
   // four column tiles, each workgroup on one of them: 14.7 -> 10.0 ms)
-  for (NtDesc& x : d) {
-    const int stride = blocks / 8, g = std::gcd(stride, x.tiles_n);
-    x.rot = x.ktri && g > 1 ? stride / g : 0;
-  }
-  NtDesc* dd = ar.put(d.data(), d.size(), s);
-  ar.launch([=] { HIPCHK(x3_launch(prec, dd, n, 0, total, 0, 1, nullptr, blocks, s, 2, ring, tile)); });
+  const int stride = blocks / 8, g = std::gcd(stride, d.tiles_n);
+  d.rot = d.ktri && g > 1 ? stride / g : 0;
+  ar.launch([=] { HIPCHK(u16_launch(prec, d, total, blocks, s)); });
 }
 
 // How the tiles of a fragment contraction of `total` tiles and nch chunks of
@@ -1693,7 +1687,7 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     d[0].epi = prec == 0 ? 0 : 3;
     d[0].npad = (int)ld;
     if (prec < 2) run_nt(ws.arena, 0, d, s, 2, prec);
-    else run_u16(ws.arena, prec, d, s);
+    else run_u16(ws.arena, prec, d[0], s);
   };
   // (pq|rs) = sum_q sum_J U^q_{(pq),J} conj(R^q_{(sr),J})  (eq. (19), R^{-q}_{rs} = conj R^q_{sr}).
   // The term of -q is the conjugate of that of q with (pq) -> (qp) and

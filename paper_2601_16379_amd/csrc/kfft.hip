@@ -803,43 +803,6 @@ __global__ __launch_bounds__(256) void pair32_kernel(PairArgs a) {
   }
 }
 
-// ---- 16-bit operand stores of four consecutive points by the lanes of a quad ----
-// Each lane holds the values of one point (the quad's four are consecutive, the
-// first a multiple of four); the quad exchanges them by DPP so that each lane
-// stores one whole part: 8 bytes (4 points of one of the four planes) in bf16
-// hi+lo, 4 bytes (2 points of one of the two) in single bf16, against four
-// (two) 2-byte stores a lane.
-template <int CTRL> __device__ inline unsigned quad_mov(unsigned v) {
-  return (unsigned)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
-}
-// quad_part: u16 offset of the part this lane stores, for its point's element
-// offset off; output rows further on add a multiple of 8 elements.
-template <int FMT> __device__ inline long long quad_part(long long off) {
-  const int t = threadIdx.x & 3;
-  return FMT == 2 ? (off >> 3) * 32 + t * 8 + (off & 4) : (off >> 3) * 16 + (t >> 1) * 8 + (off & 4) + 2 * (t & 1);
-}
-template <int FMT> __device__ inline void quad_store(char* o, float re, float im) {
-  constexpr int X1 = 0xB1, X2 = 0x4E, SWAP12 = 0xD8;   // quad_perm [1,0,3,2], [2,3,0,1], [0,2,1,3]
-  const int t = threadIdx.x & 3;
-  const unsigned rh = bf16_bits_of(re), ih = bf16_bits_of(im);
-  // byte selectors of v_perm (s0, s1): even lanes (own.lo, other.lo), odd (other.hi, own.hi)
-  const unsigned sel = (t & 1) ? 0x07060302u : 0x01000504u;
-  if constexpr (FMT == 2) {
-    const unsigned rl = bf16_bits_of(re - bf16_value((unsigned short)rh));
-    const unsigned il = bf16_bits_of(im - bf16_value((unsigned short)ih));
-    const unsigned d0 = rh | (rl << 16), d1 = ih | (il << 16);
-    // points (2i, 2i + 1) of planes t & 1 (n0) and 2 + (t & 1) (n1)
-    const unsigned n0 = __builtin_amdgcn_perm(d0, quad_mov<X1>(d0), sel);
-    const unsigned n1 = __builtin_amdgcn_perm(d1, quad_mov<X1>(d1), sel);
-    const unsigned r = quad_mov<X2>(t < 2 ? n1 : n0);
-    *(uint2*)o = t < 2 ? make_uint2(n0, r) : make_uint2(r, n1);
-  } else {
-    const unsigned d = rh | (ih << 16);
-    const unsigned n = __builtin_amdgcn_perm(d, quad_mov<X1>(d), sel);   // lanes: re01, im01, re23, im23
-    *(unsigned*)o = quad_mov<SWAP12>(n);
-  }
-}
-
 // The last axis of the line transform: dft_any_f with the roundings of the
 // length-3 halves of a length-6 line written out (one output of each contracted,
 // the other not), so that they do not hang on which outputs are kept.
