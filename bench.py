@@ -158,7 +158,7 @@ GEMM_OF_STAGE = {"frag_eri": {"fp64": "zgemm_nt_kernel<0, 64, 3>", "fp32": "zgem
                  "frag_u": {"fp64": "zgemm_nt_kernel<0, 64, 2>", "fp32": "zgemm_nt_kernel<1, 64, 2>",
                             "bf16x3": "zgemm_u16_kernel<2>", "bf16": "zgemm_u16_kernel<3>"}}
 KERNEL_OF_STAGE = {"frag_pair": "pair_", "v_gemm": "zgemm_nt_kernel<0, 64, 1>", "rhs_t": "rhs_t_kernel<",
-                   "rhs_kconv": "kconv_", "grid_fft": "slab_kernel_c<"}
+                   "rhs_kconv": "kconv_", "grid_fft": "slab_kernel_"}
 
 
 def kernel_name(stage, prec):

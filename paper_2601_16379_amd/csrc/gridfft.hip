@@ -331,6 +331,100 @@ __global__ __launch_bounds__(256) void slab_kernel_c(GridFftArgs a, int S) {
   }
 }
 
+// slab_kernel_c for N = NA NB: both axes in place in one LDS tile.  Stage 1 of
+// an axis (NA-point DFTs over j1 of element NB j1 + j2) leaves output k1 where
+// input j1 was, and stage 2 (NB-point DFTs over j2) output k1 + NA k2 at
+// NB k1 + k2: every thread writes only what it read, and the order is undone by
+// the addresses of the last store.  The first stage reads HBM (8 lanes a line of
+// 128 bytes at N = 32), the last writes it: six LDS passes and three barriers a
+// slab, rows padded to an odd pitch.
+// Bound: LDS passes between HBM's read and write.  N = 32, 112 x 640 grids (37.6
+// GB each way): 31.1 -> 16.9 ms against two tiles, ten passes and two workgroups
+// a CU.  The sums and their order are those of fft_lines_r.
+template <int N>
+__global__ __launch_bounds__(256) void slab_kernel_r(GridFftArgs a, int S) {
+  constexpr int N2 = N * N, NA = radix_a<N>(), NB = N / NA, P = N | 1, SP = N * P;
+  extern __shared__ cplx sm[];
+  cplx* buf = sm;                       // [S][N][P]
+  cplx* tw = sm + S * SP;
+  cplx* ph = tw + N;                    // [S][2N]: (i1, i2) factors, then i3 factors
+  for (int t = threadIdx.x; t < N; t += blockDim.x) tw[t] = cexpipi(-2.0 * t / N);
+  const long long nslab = (long long)a.nq * a.n_ip * N;
+  const long long s0 = (long long)blockIdx.x * S;
+  const int ns = (int)((nslab - s0) < S ? (nslab - s0) : S);
+  for (int t = threadIdx.x; t < ns * 2 * N; t += blockDim.x) {
+    const int s = t / (2 * N), r = t % (2 * N);
+    const long long slab = s0 + s;
+    const int i1 = (int)(slab % N);
+    const int qi = (int)(slab / N / a.n_ip);
+    double qf[3];
+    q_frac(a, q_of(a, qi), qf);
+    ph[t] = r < N ? cexpipi(-2.0 * (qf[0] * i1 + qf[1] * r) / N) : cexpipi(-2.0 * (qf[2] * (r - N)) / N);
+  }
+  auto slab_of = [&](int s) {
+    const long long slab = s0 + s, qI = slab / N;
+    return a.data + (qI / a.n_ip) * a.q_stride + ((qI % a.n_ip) * N + slab % N) * N2;
+  };
+  __syncthreads();
+  // along i3, stage 1, from HBM
+  for (int it = threadIdx.x; it < ns * N * NB; it += blockDim.x) {
+    const int j2 = it % NB, l = it / NB, i2 = l % N, s = l / N;
+    const cplx* src = slab_of(s) + i2 * N + j2;
+    const cplx* phs = ph + s * 2 * N;
+    cplx x[NA], y[NA];
+#pragma unroll
+    for (int j1 = 0; j1 < NA; ++j1) x[j1] = src[NB * j1];
+#pragma unroll
+    for (int j1 = 0; j1 < NA; ++j1) {
+      x[j1] = cmul(x[j1], cmul(phs[i2], phs[N + NB * j1 + j2]));
+      asm volatile("" : "+v"(x[j1].x), "+v"(x[j1].y));   // rounded: not contracted into the sums
+    }
+    small_dft<NA>(x, y);
+    cplx* o = buf + s * SP + i2 * P + j2;
+    o[0] = y[0];
+#pragma unroll
+    for (int k1 = 1; k1 < NA; ++k1) o[NB * k1] = cmul(y[k1], tw[(j2 * k1) % N]);
+  }
+  __syncthreads();
+  // stage 2
+  for (int it = threadIdx.x; it < ns * N * NA; it += blockDim.x) {
+    const int i2 = it % N, r = it / N, k1 = r % NA, s = r / NA;
+    cplx* o = buf + s * SP + i2 * P + NB * k1;
+    cplx x[NB], y[NB];
+#pragma unroll
+    for (int j2 = 0; j2 < NB; ++j2) x[j2] = o[j2];
+    small_dft<NB>(x, y);
+#pragma unroll
+    for (int k2 = 0; k2 < NB; ++k2) o[k2] = y[k2];
+  }
+  __syncthreads();
+  // along i2, stage 1 (column c of the tile)
+  for (int it = threadIdx.x; it < ns * N * NB; it += blockDim.x) {
+    const int c = it % N, r = it / N, j2 = r % NB, s = r / NB;
+    cplx* o = buf + s * SP + j2 * P + c;
+    cplx x[NA], y[NA];
+#pragma unroll
+    for (int j1 = 0; j1 < NA; ++j1) x[j1] = o[NB * j1 * P];
+    small_dft<NA>(x, y);
+    o[0] = y[0];
+#pragma unroll
+    for (int k1 = 1; k1 < NA; ++k1) o[NB * k1 * P] = cmul(y[k1], tw[(j2 * k1) % N]);
+  }
+  __syncthreads();
+  // stage 2, to HBM: row k1 + NA k2, column c of the tile is i3 = c / NB + NA (c mod NB)
+  for (int it = threadIdx.x; it < ns * N * NA; it += blockDim.x) {
+    const int c = it % N, r = it / N, k1 = r % NA, s = r / NA;
+    const cplx* o = buf + s * SP + NB * k1 * P + c;
+    cplx x[NB], y[NB];
+#pragma unroll
+    for (int j2 = 0; j2 < NB; ++j2) x[j2] = o[j2 * P];
+    small_dft<NB>(x, y);
+    cplx* dst = slab_of(s) + k1 * N + c / NB + NA * (c % NB);
+#pragma unroll
+    for (int k2 = 0; k2 < NB; ++k2) dst[NA * k2 * N] = y[k2];
+  }
+}
+
 // One workgroup takes a block of COLS_C columns of one q for up to `ipb`
 // interpolation points in turn: the Coulomb factor of its elements depends on
 // (q, i1, column) only, so it is formed once and kept in registers.  32
@@ -401,15 +495,19 @@ hipError_t launch_cubic(const GridFftArgs& a, hipStream_t s) {
   constexpr int N2 = N * N;
   int S = 2048 / N2;
   if (S < 1) S = 1;
-  size_t ldsA = (2 * (size_t)S * N2 + N + 2 * (size_t)S * N) * sizeof(cplx);
+  constexpr bool RADIX = radix_a<N>() != 0;
+  constexpr size_t TILE = RADIX ? (size_t)N * (N | 1) : 2 * (size_t)N2;   // LDS values a slab
+  size_t ldsA = (S * TILE + N + 2 * (size_t)S * N) * sizeof(cplx);
   while (ldsA > 150 * 1024 && S > 1) {
     --S;
-    ldsA = (2 * (size_t)S * N2 + N + 2 * (size_t)S * N) * sizeof(cplx);
+    ldsA = (S * TILE + N + 2 * (size_t)S * N) * sizeof(cplx);
   }
   if (ldsA > 160 * 1024) return hipErrorInvalidValue;
   const long long nslab = (long long)a.nq * a.n_ip * N;
   if (nslab <= 0) return hipSuccess;
-  hipLaunchKernelGGL(slab_kernel_c<N>, dim3((unsigned)((nslab + S - 1) / S)), dim3(256), ldsA, s, a, S);
+  const dim3 gA((unsigned)((nslab + S - 1) / S));
+  if constexpr (RADIX) hipLaunchKernelGGL(slab_kernel_r<N>, gA, dim3(256), ldsA, s, a, S);
+  else hipLaunchKernelGGL(slab_kernel_c<N>, gA, dim3(256), ldsA, s, a, S);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t ldsB = (2 * (size_t)N * COLS_C + N) * sizeof(cplx);
