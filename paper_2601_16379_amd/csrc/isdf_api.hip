@@ -82,10 +82,12 @@ void* scratch_ptr(int device) {
 // allocating and freeing them cost more than the call (a device allocation of
 // memory that was freed shortly before waits while it is cleared, at about 10
 // GB/s: 0.1 to 0.9 s for the 2.9 GB of a Coulomb-exchange build on a 1000-k
-// mesh whose kernels take 7 ms).  At most POOL_BYTES_MAX a context; all pools
-// are handed back when a device allocation of this library fails, before a
-// context plans its buffers, and with their context.  Buffers in a pool are
-// not in use: a call returns its buffers after its stream has drained.
+// mesh whose kernels take 7 ms).  At most POOL_BYTES_MAX a context, and at most
+// half of what is then free on the device (the caller's own allocations go on
+// beside them); all pools are handed back when a device allocation of this
+// library fails and before a context plans its buffers, and a context's before
+// its fragment workspace grows and with it.  Buffers in a pool are not in use: a
+// call returns its buffers after its stream has drained.
 constexpr size_t POOL_BYTES_MAX = (size_t)24 << 30;
 class IdlePool {
  public:
@@ -117,6 +119,12 @@ class IdlePool {
   bool give(void* p, size_t bytes) {
     std::lock_guard<std::mutex> lk(mu_);
     if (total_ + bytes > POOL_BYTES_MAX) return false;
+    size_t fr = 0, tot = 0;
+    if (hipMemGetInfo(&fr, &tot) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    if (total_ + bytes > fr / 2) return false;
     idle_.emplace_back(p, bytes);
     total_ += bytes;
     return true;
@@ -842,12 +850,19 @@ void release_fit_buffers(isdf_ctx c) {
 // Workspace bytes of one served batch.
 long long serve_cap(isdf_ctx c) { return c->budget / c->max_inflight; }
 
+// Room in a fragment workspace.  The context's idle buffers go back first: its
+// size was chosen as if they were free, with a margin left to the caller.
+void grow_workspace(isdf_ctx c, Workspace& ws, size_t bytes) {
+  if (bytes > ws.mem.bytes && !ws.mem.fixed) c->pool.drain();
+  ws.mem.ensure(bytes);
+}
+
 // Serving workspaces sized to their share of the budget (idle ones only:
 // called at isdf_serve_start and after a Coulomb kernel, under exclusive use).
 void reserve_workspaces(isdf_ctx c) {
   std::lock_guard<std::mutex> lk(c->mu);
   if (!c->serving && c->ws_pool.empty()) return;
-  for (Workspace* w : c->ws_pool) w->mem.ensure((size_t)serve_cap(c));
+  for (Workspace* w : c->ws_pool) grow_workspace(c, *w, (size_t)serve_cap(c));
 }
 
 // The fit reclaims the memory of idle fragment workspaces (the context is
@@ -1467,12 +1482,12 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     ws.arena.reserve(p.arena_bytes);
     if (!ws.mem.fixed && p.bytes + want > ws.mem.bytes && p.bytes + want <= cap) {
       try {
-        ws.mem.ensure(p.bytes + want);
+        grow_workspace(c, ws, p.bytes + want);
       } catch (const Fail&) {
         // the plan alone, below
       }
     }
-    ws.mem.ensure(p.bytes);
+    grow_workspace(c, ws, p.bytes);
   } else {
     if (p.bytes > ws.mem.bytes) throw Fail{ISDF_E_INVALID, "captured batch larger than its workspace"};
     ws.arena.used = 0;
@@ -1810,7 +1825,7 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
 
 // Memory a synchronous fragment call may use: what is free on the device
 // plus what the workspace already holds and the context's idle buffers (handed
-// back when the workspace cannot grow beside them), less a margin.
+// back before the workspace grows), less a margin.
 size_t sync_cap(isdf_ctx c, const Workspace& ws) {
   size_t fr = 0, tot = 0;
   if (hipMemGetInfo(&fr, &tot) != hipSuccess) {

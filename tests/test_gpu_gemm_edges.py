@@ -163,3 +163,22 @@ def test_grid_transform_sizes(n):
         err = np.max(np.abs(pi @ w @ pi - v)) / np.max(np.abs(v))
         assert ev[0] > 0 and err <= bound, (q, err, bound)
     ctx.close()
+
+
+def test_idle_buffers_yield_to_fragment_workspace():
+    """Buffers kept after a J/K build go back before the fragment workspace
+    grows: the memory a fragment call leaves free does not depend on an earlier
+    build."""
+    import torch
+    free = []
+    for build in (False, True):
+        cfg, ctx, x, w = _context(500)
+        dev = [torch.from_numpy(inp.make_fragment(cfg, 0, 40)).cuda()]
+        if build:
+            ctx.hf_jk(inp.make_density(cfg))
+        ctx.fragment_eri(dev, "fp64")
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        free.append(torch.cuda.mem_get_info()[0])
+        ctx.close()
+    assert abs(free[0] - free[1]) <= 16 << 20, free      # rho alone is 8 x 500 x 500 x 16 bytes = 32 MB
