@@ -29,15 +29,16 @@
 // contraction runs the two-barrier loop, which hides more latency
 // (zgemm_c2b_kernel: 0.143 against 0.126 of peak at 216 k).  Both loops
 // issue the same MFMAs in the same order: the results do not depend on the
-// choice.  The single-bf16 contraction always runs the two-barrier loop.  In LDS a row keeps its eight 16-byte slots (2 k-groups x 4 planes)
-// in an order XOR-permuted by the row, so that the 32x32 fragment reads
+// choice.  The single-bf16 contraction always runs the two-barrier loop.  U^q
+// (short tiles) and products of few tiles have kernels of their own below.  In
+// LDS a row keeps its eight 16-byte slots (2 k-groups x 4 planes) in an order XOR-permuted by the row, so that the 32x32 fragment reads
 // (lane -> row l%32, k-group l/32) hit distinct banks.
 //
 // Rows beyond M / N are loaded from the last valid row (their outputs are
 // dropped); 16-byte vectors that start beyond the segment length are copied
 // from a zero block.  Each lane's copy sources are computed once per tile.
-// One K segment per launch; epilogues as in the 128-tile FP32 kernel (split
-// store, FP64 accumulation across launches).
+// One K segment per launch, or with partial blocks several; epilogues: the
+// operand format, FP64 accumulation across launches, or a partial block.
 #include "kernels.hpp"
 
 namespace {
