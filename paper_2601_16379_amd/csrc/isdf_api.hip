@@ -2317,8 +2317,12 @@ isdf_status isdf_select_points(const int32_t grid[3], const int32_t kmesh[3], in
     piv.alloc(sizeof(int) * n_ip);
     dmax.alloc(sizeof(double) * n_ip);
     state.alloc(SEL_STATE_BYTES);
-    // several columns a pass where there is room for their partial sums
-    int ncols = SEL_COLS;
+    // several columns a pass where there is room for their partial sums and the
+    // pass is bound by reading the orbitals: from the L2s a column more costs as
+    // much as the first (one against eight columns, us a step: 0.5 MB of orbitals
+    // 14.1 / 17.2, 9 MB 15.5 / 15.8, 17 MB 18.4 / 18.8, 35 MB 30.5 / 23.7, 213 MB
+    // 60 / 37)
+    int ncols = sizeof(cplx) * nrows * ng <= ((size_t)20 << 20) ? 1 : SEL_COLS;
     try {
       part.alloc(sizeof(cplx) * pl.nslice * ng * ncols);
     } catch (const Fail&) {
