@@ -110,5 +110,6 @@ __device__ inline void tri_solve64(Tri64& t, int rb) {
       for (int u = 0; u < 2; ++u) tri_sub<CJ>(acc[u], t.T[d][c0 + 2 * g + u], x);
     }
     tri_step<CJ, 0>(t, acc, c0, rb, row, g);
+    wave_sync();                         // the next unknowns read what the quad's other lanes stored
   }
 }

@@ -31,6 +31,13 @@ __device__ inline cplx cexpipi(double x) {
   return cmk(c, s);
 }
 
+// LDS values stored by lanes of this wavefront are there for its other lanes.
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 static inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
 
 // Store one complex value in one of the operand formats of the NT GEMMs:

@@ -7,6 +7,9 @@
 //                     none); wave LATE runs late after every barrier (-1: none).
 //                     Prints the result of every wave, or "hang" when a barrier
 //                     waits for a wave that has left.
+//   tri RB CJ LATE    substitution of 16 right hand sides, RB unknowns, conjugated
+//                     triangle for CJ = 1; lane LATE of every quad runs late after
+//                     every exchange (-1: none).  Prints the largest deviation.
 #include <chrono>
 #include <cmath>
 #include <condition_variable>
@@ -60,7 +63,7 @@ static Barrier* g_wave[4];                     // 64 threads each
 static double g_lane[256];
 static Barrier g_quad[64];                     // 4 lanes each
 static int g_quad_v[256];
-static int g_late = -1;
+static int g_late = -1, g_late_lane = -1;
 static void nap() { std::this_thread::sleep_for(std::chrono::milliseconds(4)); }
 
 static void __syncthreads() {
@@ -82,8 +85,10 @@ static int __builtin_amdgcn_update_dpp(int, int v, int ctrl, int, int, bool) {
   g_quad[t >> 2].wait();
   const int r = g_quad_v[(t & ~3) + (ctrl & 3)];
   g_quad[t >> 2].wait();
+  if ((t & 3) == g_late_lane) std::this_thread::sleep_for(std::chrono::microseconds(200));
   return r;
 }
+static void wave_sync() { g_wave[threadIdx.x >> 6]->wait(); }
 
 #include "chol_steps.hpp"
 
@@ -172,7 +177,50 @@ static int run_diag(int n, int bad, int late) {
   return 0;
 }
 
+template <bool CJ>
+static int run_tri(int rb, int late) {
+  static Tri64 t;
+  std::mt19937 gen(11);
+  std::normal_distribution<double> g;
+  for (int c = 0; c < CHOL_NB; ++c) {
+    for (int d = 0; d < CHOL_NB; ++d) t.T[d][c] = d < c ? cmk(0.1 * g(gen), 0.1 * g(gen)) : cmk(d == c, 0.0);
+    const double diag = 1.0 + 0.5 * (c % 3);
+    t.T[c][c] = cmk(diag, 0.0);
+    t.rinv[c] = 1.0 / diag;
+    for (int r = 0; r < 64; ++r) t.X[r][c] = cmk(g(gen), g(gen));
+  }
+  const Tri64 in = t;
+  Barrier w0(64);
+  g_wave[0] = &w0;
+  g_late_lane = late;
+  std::vector<std::thread> th;
+  for (int i = 0; i < 64; ++i)
+    th.emplace_back([&, i] {
+      threadIdx.x = i;
+      tri_solve64<CJ>(t, rb);
+    });
+  for (auto& x : th) x.join();
+  double err = 0.0;
+  for (int r = 0; r < 16; ++r) {
+    cplx x[CHOL_NB];
+    for (int c = 0; c < rb; ++c) {
+      cplx s = in.X[r][c];
+      for (int d = 0; d < c; ++d) {
+        const cplx l = cmk(in.T[d][c].x, CJ ? -in.T[d][c].y : in.T[d][c].y);
+        s.x -= l.x * x[d].x - l.y * x[d].y;
+        s.y -= l.x * x[d].y + l.y * x[d].x;
+      }
+      x[c] = cscale(s, in.rinv[c]);
+      err = std::fmax(err, std::hypot(x[c].x - t.X[r][c].x, x[c].y - t.X[r][c].y) / (1.0 + std::hypot(x[c].x, x[c].y)));
+    }
+  }
+  printf("%.3e\n", err);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   if (argc == 5 && !strcmp(argv[1], "diag")) return run_diag(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]));
+  if (argc == 5 && !strcmp(argv[1], "tri"))
+    return atoi(argv[3]) ? run_tri<true>(atoi(argv[2]), atoi(argv[4])) : run_tri<false>(atoi(argv[2]), atoi(argv[4]));
   return 2;
 }

@@ -43,3 +43,13 @@ def test_breakdown_leaves_together(driver, col, late):
     """A breakdown is seen by every wave at the same barrier, whichever of them
     reads the flag late."""
     assert _run(driver, "diag", 64, col, late) == "breakdown"
+
+
+@pytest.mark.parametrize("conj", [0, 1])
+@pytest.mark.parametrize("late", [-1, 0, 1, 2, 3])
+@pytest.mark.parametrize("rb", [1, 8, 9, 64])
+def test_substitution(driver, rb, conj, late):
+    """Unknowns that another lane of the quad stored are read after its store,
+    whichever lane is late.  Two orders of the same sums: 64 roundings of terms
+    that the 0.1-sized triangle keeps within a few times the result."""
+    assert float(_run(driver, "tri", rb, conj, late)) <= 64 * 8 * 2.0 ** -53
