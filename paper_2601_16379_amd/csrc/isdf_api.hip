@@ -85,12 +85,15 @@ void* scratch_ptr(int device) {
 // mesh whose kernels take 7 ms).  At most POOL_BYTES_MAX a context, and at most
 // half of what is then free on the device (the caller's own allocations go on
 // beside them); all pools are handed back when a device allocation of this
-// library fails and before a context plans its buffers, and a context's before
-// its fragment workspace grows and with it.  Buffers in a pool are not in use: a
-// call returns its buffers after its stream has drained.
+// library fails, before a context plans its buffers and before a fragment
+// workspace grows, and a context's with it.  What is planned from the free
+// memory counts every pool of the device as free: no context is refused room
+// that another one keeps idle.  Buffers in a pool are not in use: a call returns
+// its buffers after its stream has drained.
 constexpr size_t POOL_BYTES_MAX = (size_t)24 << 30;
 class IdlePool {
  public:
+  int device = 0;
   IdlePool() {
     std::lock_guard<std::mutex> lk(registry_mu());
     registry().insert(this);
@@ -138,6 +141,14 @@ class IdlePool {
   size_t bytes() {
     std::lock_guard<std::mutex> lk(mu_);
     return total_;
+  }
+  // Idle bytes of every context on a device.
+  static size_t bytes_on(int device) {
+    std::lock_guard<std::mutex> lk(registry_mu());
+    size_t n = 0;
+    for (IdlePool* p : registry())
+      if (p->device == device) n += p->bytes();
+    return n;
   }
   // Hands back every context's idle buffers; true when there were any.
   static bool drain_all() {
@@ -850,10 +861,10 @@ void release_fit_buffers(isdf_ctx c) {
 // Workspace bytes of one served batch.
 long long serve_cap(isdf_ctx c) { return c->budget / c->max_inflight; }
 
-// Room in a fragment workspace.  The context's idle buffers go back first: its
-// size was chosen as if they were free, with a margin left to the caller.
-void grow_workspace(isdf_ctx c, Workspace& ws, size_t bytes) {
-  if (bytes > ws.mem.bytes && !ws.mem.fixed) c->pool.drain();
+// Room in a fragment workspace.  All idle buffers go back first: its size was
+// chosen as if they were free, with a margin left to the caller.
+void grow_workspace(Workspace& ws, size_t bytes) {
+  if (bytes > ws.mem.bytes && !ws.mem.fixed) IdlePool::drain_all();
   ws.mem.ensure(bytes);
 }
 
@@ -862,7 +873,7 @@ void grow_workspace(isdf_ctx c, Workspace& ws, size_t bytes) {
 void reserve_workspaces(isdf_ctx c) {
   std::lock_guard<std::mutex> lk(c->mu);
   if (!c->serving && c->ws_pool.empty()) return;
-  for (Workspace* w : c->ws_pool) grow_workspace(c, *w, (size_t)serve_cap(c));
+  for (Workspace* w : c->ws_pool) grow_workspace(*w, (size_t)serve_cap(c));
 }
 
 // The fit reclaims the memory of idle fragment workspaces (the context is
@@ -1482,12 +1493,12 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
     ws.arena.reserve(p.arena_bytes);
     if (!ws.mem.fixed && p.bytes + want > ws.mem.bytes && p.bytes + want <= cap) {
       try {
-        grow_workspace(c, ws, p.bytes + want);
+        grow_workspace(ws, p.bytes + want);
       } catch (const Fail&) {
         // the plan alone, below
       }
     }
-    grow_workspace(c, ws, p.bytes);
+    grow_workspace(ws, p.bytes);
   } else {
     if (p.bytes > ws.mem.bytes) throw Fail{ISDF_E_INVALID, "captured batch larger than its workspace"};
     ws.arena.used = 0;
@@ -1824,15 +1835,15 @@ void enqueue_batch(isdf_ctx c, Workspace& ws, int prec, const std::vector<FragIn
 }
 
 // Memory a synchronous fragment call may use: what is free on the device
-// plus what the workspace already holds and the context's idle buffers (handed
-// back before the workspace grows), less a margin.
+// plus what the workspace already holds and the idle buffers of the device's
+// contexts (handed back before the workspace grows), less a margin.
 size_t sync_cap(isdf_ctx c, const Workspace& ws) {
   size_t fr = 0, tot = 0;
   if (hipMemGetInfo(&fr, &tot) != hipSuccess) {
     (void)hipGetLastError();
     return ws.mem.bytes;
   }
-  const size_t avail = fr + ws.mem.bytes + c->pool.bytes();
+  const size_t avail = fr + ws.mem.bytes + IdlePool::bytes_on(c->device);
   const size_t margin = std::max<size_t>((size_t)1 << 28, avail / 16);
   return avail > margin ? avail - margin : 0;
 }
@@ -2032,6 +2043,7 @@ void setup_context(isdf_ctx c, const double* lattice, const int32_t grid[3], con
   c->stream = (hipStream_t)hip_stream;
   c->has_orbitals = with_orbitals;
   HIPCHK(hipGetDevice(&c->device));
+  c->pool.device = c->device;
   memcpy(c->lattice, lattice, sizeof(c->lattice));
   // reciprocal rows b_i: 2 pi (A^-1)^T
   const double* A = lattice;
@@ -3250,11 +3262,11 @@ isdf_status isdf_drpa(isdf_ctx ctx, const void* mo_coeff, const double* mo_energ
     size_t fr = 0, tot = 0;
     HIPCHK(hipMemGetInfo(&fr, &tot));
     const long long per_w = hn * (long long)sizeof(cplx);
-    int nbw = (int)std::min<long long>(n_omega, (long long)(0.9 * (double)(fr + c->pool.bytes())) / per_w);
+    int nbw = (int)std::min<long long>(n_omega, (long long)(0.9 * (double)(fr + IdlePool::bytes_on(c->device))) / per_w);
     if (nbw < 1) {
       HIPCHK(hipStreamSynchronize(s));
       c->sync_ws.mem.release();
-      c->pool.drain();
+      IdlePool::drain_all();
       HIPCHK(hipMemGetInfo(&fr, &tot));
       nbw = (int)std::min<long long>(n_omega, (long long)(0.9 * (double)fr) / per_w);
     }
