@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <deque>
+#include <exception>
 #include <functional>
 #include <map>
 #include <numeric>
@@ -89,7 +90,7 @@ void* scratch_ptr(int device) {
 // workspace grows, and a context's with it.  What is planned from the free
 // memory counts every pool of the device as free: no context is refused room
 // that another one keeps idle.  Buffers in a pool are not in use: a call returns
-// its buffers after its stream has drained.
+// its buffers after its stream has drained, and one that fails frees them.
 constexpr size_t POOL_BYTES_MAX = (size_t)24 << 30;
 class IdlePool {
  public:
@@ -738,9 +739,10 @@ struct Exclusive {
 };
 
 // Workspace buffer of a synchronous call: from the context's idle buffers, to
-// which it returns (in order on the context's stream, like every later use).
-// When the device is full, the idle workspace of synchronous fragment calls is
-// handed back and the allocation tried once more.
+// which it returns at the call's end (the stream has drained).  A call that
+// fails may still have work queued and keeps nothing: its buffers are freed,
+// which waits for the device.  When the device is full, the idle workspace of
+// synchronous fragment calls is handed back and the allocation tried once more.
 struct PoolBuf {
   isdf_ctx c = nullptr;
   void* p = nullptr;
@@ -749,7 +751,7 @@ struct PoolBuf {
   PoolBuf(const PoolBuf&) = delete;
   PoolBuf& operator=(const PoolBuf&) = delete;
   ~PoolBuf() {
-    if (p && !c->pool.give(p, bytes)) (void)hipFree(p);
+    if (p && (std::uncaught_exceptions() > 0 || !c->pool.give(p, bytes))) (void)hipFree(p);
   }
   template <class T> T* as() const { return reinterpret_cast<T*>(p); }
 };

@@ -47,3 +47,19 @@ def test_idle_buffers_yield_to_another_context():
         one.close()
         two.close()
     assert abs(free[0] - free[1]) <= RHO // 2, free
+
+
+def test_failed_call_keeps_nothing():
+    """A call that fails after its workspace was allocated (a transform whose
+    polarisabilities overflow) leaves the device memory as it found it."""
+    import paper_2601_16379_amd as pkg
+    cfg, ctx = _context()
+    c, e, n_occ = inp.make_mo(cfg)
+    tau, _ = inp.laplace_grid(3, 1.0)
+    _, ow = inp.laplace_grid(2, 1.0)
+    before = _free()
+    with pytest.raises(pkg.IsdfError) as ex:
+        ctx.drpa(c, e, n_occ, tau, ow, np.full((2, 3), 1e300 + 0j))
+    assert ex.value.status == -4
+    assert before - _free() <= RHO // 2
+    ctx.close()
