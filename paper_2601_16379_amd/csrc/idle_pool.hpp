@@ -50,8 +50,9 @@ class IdlePool {
     idle_.erase(idle_.begin() + best);
     return p;
   }
-  // Keeps a buffer (false: no room for it).
-  bool give(void* p, size_t bytes) {
+  // Keeps a buffer (false: no room for it).  Called where a call's buffers go out
+  // of scope, so nothing leaves it by an exception.
+  bool give(void* p, size_t bytes) noexcept try {
     std::lock_guard<std::mutex> lk(mu_);
     if (total_ + bytes > POOL_BYTES_MAX) return false;
     size_t fr = 0, tot = 0;
@@ -63,6 +64,8 @@ class IdlePool {
     idle_.emplace_back(p, bytes);
     total_ += bytes;
     return true;
+  } catch (...) {
+    return false;
   }
   void drain() {
     std::lock_guard<std::mutex> lk(mu_);

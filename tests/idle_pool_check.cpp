@@ -20,6 +20,14 @@ static hipError_t hipMemGetInfo(size_t* fr, size_t* tot) {
 }
 static hipError_t hipGetLastError() { return hipSuccess; }
 
+static bool g_no_host_memory = false;
+void* operator new(size_t n) {
+  if (g_no_host_memory) throw std::bad_alloc();
+  return malloc(n);
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
+
 #include "idle_pool.hpp"
 
 #define CHECK(x)               \
@@ -67,9 +75,24 @@ static int all() {
   return 0;
 }
 
+// without host memory for its entry a buffer is refused, and nothing is thrown
+// out of the destructor that offers it
+static int nohost() {
+  IdlePool p;
+  g_no_host_memory = true;
+  const bool kept = p.give(ptr(0), 100);
+  g_no_host_memory = false;
+  CHECK(!kept && p.bytes() == 0);
+  CHECK(p.give(ptr(0), 100) && p.bytes() == 100);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   if (argc != 2) return 2;
-  const int rc = !strcmp(argv[1], "sizes") ? sizes() : !strcmp(argv[1], "limits") ? limits() : !strcmp(argv[1], "all") ? all() : 2;
+  const int rc = !strcmp(argv[1], "sizes") ? sizes()
+                 : !strcmp(argv[1], "limits") ? limits()
+                 : !strcmp(argv[1], "all") ? all()
+                 : !strcmp(argv[1], "nohost") ? nohost() : 2;
   if (rc == 0) printf("ok\n");
   return rc;
 }

@@ -21,7 +21,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["sizes", "limits", "all"])
+@pytest.mark.parametrize("what", ["sizes", "limits", "all", "nohost"])
 def test_pool(driver, what):
     r = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
     assert (r.returncode, r.stdout.strip()) == (0, "ok")
