@@ -449,9 +449,10 @@ isdf_status isdf_load(isdf_ctx* out, const char* path, void* hip_stream);
  *   flags  ISDF_HF_DEVICE: dm, j_out, k_out are device pointers (else host).
  * Device workspace N_k N_IP^2 + N_k n_orb N_IP complex numbers (17.3 + 0.9 GB
  * at N_k = 1000, N_IP = 1040), kept by the context for the next such call up
- * to 24 GiB and handed back when a device allocation of the library needs it,
- * with the next isdf_create and with the context; the idle workspace of
- * isdf_fragment_eri is handed back first when the device is full.
+ * to 24 GiB and to half of the free device memory (nothing of a call that
+ * fails).  Handed back by isdf_release_idle, when a device allocation of the
+ * library needs it, with the next isdf_create and with the context.  The idle
+ * workspace of isdf_fragment_eri is handed back when the device is full.
  * Synchronous.  Errors: ISDF_E_STATE before isdf_coulomb_kernel,
  * ISDF_E_INVALID for null or (with ISDF_HF_DEVICE) non-device pointers and
  * for K on meshes of more than 2048 k points, ISDF_E_NOMEM, ISDF_E_DEVICE.
@@ -537,6 +538,14 @@ isdf_status isdf_drpa(isdf_ctx ctx, const void* mo_coeff, const double* mo_energ
                       int32_t n_tau, const double* tau, int32_t n_omega, const double* omega_weight,
                       const void* transform, double* integrand_out, double* class_out, double* e_drpa_out,
                       double* e_second_out, uint32_t flags);
+
+/*
+ * Frees the device workspace that the context keeps between isdf_hf_jk,
+ * isdf_sos_mp2 and isdf_drpa calls, for a caller that needs the memory for
+ * allocations of its own; the next such call allocates again.  Results do not
+ * depend on it.  ISDF_E_INVALID for a null context.
+ */
+isdf_status isdf_release_idle(isdf_ctx ctx);
 
 isdf_status isdf_destroy(isdf_ctx ctx);
 /* Message of the last failed call on ctx; with ctx == NULL, the message of the

@@ -17,7 +17,7 @@ namespace {
 // half of what is then free on the device (the caller's own allocations go on
 // beside them); all pools are handed back when a device allocation of this
 // library fails, before a context plans its buffers and before a fragment
-// workspace grows, and a context's with it.  What is planned from the free
+// workspace grows, and a context's with it and on request (isdf_release_idle).  What is planned from the free
 // memory counts every pool of the device as free: no context is refused room
 // that another one keeps idle.  Buffers in a pool are not in use: a call returns
 // its buffers after its stream has drained, and one that fails frees them.

@@ -2799,6 +2799,10 @@ double isdf_stage_ms(isdf_ctx ctx, const char* name) {
   return it == ctx->timer.ms.end() ? -1.0 : (double)it->second;
 }
 
+isdf_status isdf_release_idle(isdf_ctx ctx) {
+  return guarded(ctx, [&] { ctx->pool.drain(); });
+}
+
 isdf_status isdf_destroy(isdf_ctx ctx) {
   if (!ctx) return ISDF_E_INVALID;
   (void)isdf_serve_stop(ctx);

@@ -37,7 +37,7 @@ EXPORTS = ["isdf_create", "isdf_fit", "isdf_coulomb_kernel", "isdf_get_metric",
            "isdf_serve_stop", "isdf_stats", "isdf_stage_ms", "isdf_stage_total", "isdf_stage_reset", "isdf_plan_bytes", "isdf_storage_model_bytes",
            "isdf_graph_create", "isdf_graph_launch", "isdf_graph_destroy", "isdf_autotune", "isdf_set_tiling",
            "isdf_save", "isdf_load", "isdf_fragment_eri_static", "isdf_select_points", "isdf_hf_jk",
-           "isdf_sos_mp2", "isdf_drpa", "isdf_destroy", "isdf_last_error", "isdf_version"]
+           "isdf_sos_mp2", "isdf_drpa", "isdf_release_idle", "isdf_destroy", "isdf_last_error", "isdf_version"]
 
 
 class IsdfError(RuntimeError):
@@ -91,6 +91,7 @@ def load_library(path=LIB_PATH):
         "isdf_hf_jk": (I32, [P, P, P, P, U32]),
         "isdf_sos_mp2": (I32, [P, P, P, I32, I32, I32, P, P, P, P, P, U32]),
         "isdf_drpa": (I32, [P, P, P, I32, I32, I32, P, I32, P, P, P, P, P, P, U32]),
+        "isdf_release_idle": (I32, [P]),
         "isdf_serve_start": (I32, [P, I32, I32, I64]),
         "isdf_submit": (I32, [P, ctypes.POINTER(Request), ctypes.POINTER(ctypes.c_uint64)]),
         "isdf_submit_n": (I32, [P, I32, ctypes.POINTER(Request), ctypes.POINTER(ctypes.c_uint64)]),
@@ -411,6 +412,11 @@ class Isdf:
         if per_class:
             out["classes"] = cls
         return out
+
+    def release_idle(self):
+        """``isdf_release_idle``: hands back the device memory kept between
+        ``hf_jk``, ``sos_mp2`` and ``drpa`` calls."""
+        self._check(self.lib.isdf_release_idle(self.h), "isdf_release_idle")
 
     def graph(self, coeffs, out, prec="bf16x3"):
         """The fragment pipeline of this batch (device tensors ``coeffs``, ERIs

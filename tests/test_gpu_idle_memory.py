@@ -63,3 +63,50 @@ def test_failed_call_keeps_nothing():
     assert ex.value.status == -4
     assert before - _free() <= RHO // 2
     ctx.close()
+
+
+def _calls(cfg, ctx):
+    """J/K, MP2 and dRPA with workspaces of several sizes, as functions."""
+    c, e, n_occ = inp.make_mo(cfg)
+    tau, tw = inp.laplace_grid(3, 1.0)
+    om, ow = inp.laplace_grid(2, 1.0)
+    g = inp.quadrature_transform(tau, tw, om)
+    dm = inp.make_density(cfg)
+    return {"jk": lambda: ctx.hf_jk(dm),
+            "j": lambda: ctx.hf_jk(dm, want_k=False)[0],
+            "mp2": lambda: ctx.sos_mp2(c, e, n_occ, tau, tw)["integrand"],
+            "mp2 fewer": lambda: ctx.sos_mp2(np.ascontiguousarray(c[:, :, 1:5]), e[:, 1:5], 2, tau, tw)["integrand"],
+            "drpa": lambda: ctx.drpa(c, e, n_occ, tau, ow, g)["integrand"],
+            "drpa one": lambda: ctx.drpa(c, e, n_occ, tau, ow[:1], g[:1])["integrand"]}
+
+
+def test_release_idle_hands_everything_back():
+    cfg, ctx = _context()
+    calls = _calls(cfg, ctx)
+    for f in calls.values():              # the arenas and code of every call
+        f()
+    ctx.release_idle()
+    before = _free()
+    for name, f in calls.items():
+        f()
+        kept = before - _free()
+        assert kept > RHO // 2 or name == "j", (name, kept)
+        ctx.release_idle()
+        assert _free() == before, name
+    ctx.close()
+
+
+def test_calls_in_turn_equal_calls_alone():
+    """Results do not depend on what an earlier call of another size left in the
+    buffers it handed on."""
+    cfg, ctx = _context()
+    calls = _calls(cfg, ctx)
+    alone = {}
+    for name, f in calls.items():
+        ctx.release_idle()
+        alone[name] = f()
+    rng = np.random.default_rng(5)
+    for name in rng.choice(list(calls), 30):
+        for a, b in zip(np.atleast_1d(calls[name]()), np.atleast_1d(alone[name])):
+            assert np.array_equal(a, b), name
+    ctx.close()
