@@ -30,8 +30,9 @@
 // (zgemm_c2b_kernel: 0.143 against 0.126 of peak at 216 k).  Both loops
 // issue the same MFMAs in the same order: the results do not depend on the
 // choice.  The single-bf16 contraction always runs the two-barrier loop.  U^q
-// (short tiles) and products of few tiles have kernels of their own below.  In
-// LDS a row keeps its eight 16-byte slots (2 k-groups x 4 planes) in an order XOR-permuted by the row, so that the 32x32 fragment reads
+// (but for bf16x3 rows far apart, run_u16) and products of few tiles have kernels
+// of their own below.  In LDS a row keeps its eight 16-byte slots (2 k-groups x 4
+// planes) in an order XOR-permuted by the row, so that the 32x32 fragment reads
 // (lane -> row l%32, k-group l/32) hit distinct banks.
 //
 // Rows beyond M / N are loaded from the last valid row (their outputs are
@@ -387,7 +388,7 @@ __device__ inline void tri_live(bool tri, int s, int sk, int cb0, bool& l0, bool
 // each): two LDS stages, each stage's fragments read from LDS at its start
 // (the waves of the other workgroup keep the matrix cores busy meanwhile),
 // copies one stage ahead, one barrier a stage.
-template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ>
+template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ, int KIND>
 __device__ inline void tile_body(const NtDesc& d, int b, int m0, int n0, int kcur,
                                  const unsigned short* const (&asrc)[NCOPY], const unsigned short* const (&bsrc)[NCOPY],
                                  const int (&gslot)[NCOPY], int rb0, int cb0, char* smem, int wave, int lane,
@@ -425,7 +426,13 @@ __device__ inline void tile_body(const NtDesc& d, int b, int m0, int n0, int kcu
     read_frags_b<F>(buf, f, cb0, lr, lk);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     settle(f);
-    if (!idle) stage_mma<F, NI, NJ, A_CONJ, B_CONJ>(f, c_re, c_im);
+    if constexpr (KIND == 2) {
+      bool l0, l1;
+      tri_live(d.ktri != 0, s, SK, cb0, l0, l1);
+      stage_mma_tri<F, NI, NJ, A_CONJ, B_CONJ>(f, c_re, c_im, l0, l1);
+    } else {
+      if (!idle) stage_mma<F, NI, NJ, A_CONJ, B_CONJ>(f, c_re, c_im);
+    }
   }
   if (!idle) tile_epilogue<F, NI, NJ>(d, b, m0, n0, rb0, cb0, c_re, c_im, smem, wave, lane, first, part);
 }
@@ -911,7 +918,10 @@ __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, lon
     const int seg = seg0 + (int)(u / nt);
     const NtTile tl = nt_tile(descs, ndesc, t0 + u % nt);
     const NtDesc d = descs[tl.desc];
-    const int b = tl.b, tm = tl.tm, tn = tl.tn;
+    const int b = tl.b, tm = tl.tm;
+    int tn = tl.tn;
+    if constexpr (KIND == 2 && T == XT)
+      if (d.rot) tn = (tn + (b * d.tiles_m + tm) / d.rot) % d.tiles_n;
     cplx* pt = part ? part + u * (T * T) : nullptr;
     const int m0 = tm * T, n0 = tn * T;
     // interleaved formats: logical element e at u16 EU*e (e a multiple of 8)
@@ -971,13 +981,13 @@ __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, lon
                                               lane, diag && wm < wn, first, pt);
     } else {
       if (d.M - m0 <= 32)
-        tile_body<F, 1, 1, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave, lane,
+        tile_body<F, 1, 1, A_CONJ, B_CONJ, KIND>(d, b, m0, n0, kcur, asrc, bsrc, gslot, 0, wave * 32, smem, wave, lane,
                                            diag && wave > 0, first, pt);
       else if (d.N - n0 <= 32)
-        tile_body<F, 1, 1, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wave * 32, 0, smem, wave, lane,
+        tile_body<F, 1, 1, A_CONJ, B_CONJ, KIND>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wave * 32, 0, smem, wave, lane,
                                            false, first, pt);
       else
-        tile_body<F, 2, 2, A_CONJ, B_CONJ>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 64, wn * 64, smem, wave,
+        tile_body<F, 2, 2, A_CONJ, B_CONJ, KIND>(d, b, m0, n0, kcur, asrc, bsrc, gslot, wm * 64, wn * 64, smem, wave,
                                            lane, diag && wm < wn, first, pt);
     }
   }
@@ -989,6 +999,11 @@ __device__ inline void x3_tiles(const NtDesc* __restrict__ descs, int ndesc, lon
 
 __global__ __launch_bounds__(XNT, 2) void zgemm_x3_kernel(X3_ARGS) {
   x3_tiles<2, false, true, 3, false>(descs, ndesc, t0, nt, seg0, nseg, part);
+}
+
+// U^q in bf16x3 where zgemm_u16_kernel is the slower one (run_u16)
+__global__ __launch_bounds__(XNT, 2) void zgemm_x3u_kernel(X3_ARGS) {
+  x3_tiles<2, false, false, 2, false>(descs, ndesc, t0, nt, seg0, nseg, part);
 }
 
 // two barriers a stage: the fragment contraction of launches with few tiles
@@ -1048,7 +1063,7 @@ hipError_t x3_launch(int fmt, const NtDesc* descs_dev, int ndesc, long long t0, 
                      cplx* part, int max_blocks, hipStream_t s, int kind, bool ring, int tile) {
   if (nt <= 0 || nseg <= 0) return hipSuccess;
   if ((fmt != 2 && fmt != 3) || (kind != 2 && kind != 3) || (!part && nseg != 1) ||
-      (tile != XT && tile != X3_SMALL) || (kind == 2 && tile != X3_SMALL))
+      (tile != XT && tile != X3_SMALL) || (kind == 2 && tile != X3_SMALL && (fmt != 2 || ring)))
     return hipErrorInvalidValue;
   const long long units = nt * nseg, u8 = (units + 7) / 8 * 8;
   max_blocks = max_blocks / 8 * 8;
@@ -1061,6 +1076,8 @@ hipError_t x3_launch(int fmt, const NtDesc* descs_dev, int ndesc, long long t0, 
     else if (fmt == 2) X3_GO(zgemm_small16_kernel<2 COMMA 3>, SRING * SSTAGE_B);
     else if (kind == 2) X3_GO(zgemm_small16_kernel<3 COMMA 2>, SRING * SSTAGE_B);
     else X3_GO(zgemm_small16_kernel<3 COMMA 3>, SRING * SSTAGE_B);
+  } else if (kind == 2) {
+    X3_GO(zgemm_x3u_kernel, NBUF * STAGE_B);
   } else if (ring) {
     if (fmt == 2) X3_GO(zgemm_ring_kernel<2>, RING * STAGE_B);
     else X3_GO(zgemm_ring_kernel<3>, RING * STAGE_B);

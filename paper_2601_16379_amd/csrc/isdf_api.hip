@@ -290,12 +290,28 @@ void run_u16(Arena& ar, int prec, NtDesc d, hipStream_t s) {
     return;
   }
   const long long total = x3_plan(&d, 1, X3_TILE);
+  // bf16x3 rows 4 MB apart and further: the copies of zgemm_u16_kernel's one
+  // workgroup a CU miss the address translation cache (0.11 to 0.14 of the
+  // requests, against under 0.015 up to 3.2 MB), and two workgroups a CU hide
+  // more of that.  Same process and buffers, one against two: 10^3 mesh, N_IP 1300
+  // (5.3 MB) 75.4 / 71.3 ms, 1040 (4.2 MB) 88.6 to 94.4 / 89.0 to 91.8, 1008 (4.1
+  // MB) 75.3 / 75.2, 976 (3.9 MB) 69.6 / 70.7, 800 (3.2 MB) 52.3 / 54.7; 8^3, 1300
+  // (2.7 MB) 61.0 / 63.5; 6^3, 1040 (0.9 MB) 17.1 / 18.3.  In a process whose memory
+  // came in larger pieces N_IP 1040 missed less and took 71.4 / 76.6.  Without the
+  // factor the line is the same (1040: 93.2 / 87.8; 800: 47.0 / 50.1).  Single bf16
+  // gains from one workgroup throughout (10^3, 1040: 34.9 / 39.6).
+  const bool two = prec == 2 && d.lda * 8 >= 4000000;
   // The column tiles of a triangular factor differ in length, and a workgroup
   // takes every blocks / 8 -th tile: where that keeps it on a part of the
   // columns, the order turns once those have been gone through (1000-k shape,
   // four column tiles, each workgroup on one of them: 14.7 -> 10.0 ms)
-  const int stride = blocks / 8, g = std::gcd(stride, d.tiles_n);
+  const int nblk = two ? 2 * blocks : blocks, stride = nblk / 8, g = std::gcd(stride, d.tiles_n);
   d.rot = d.ktri && g > 1 ? stride / g : 0;
+  if (two) {
+    NtDesc* dd = ar.put(&d, 1, s);
+    ar.launch([=] { HIPCHK(x3_launch(prec, dd, 1, 0, total, 0, 1, nullptr, nblk, s, 2, false, X3_TILE)); });
+    return;
+  }
   ar.launch([=] { HIPCHK(u16_launch(prec, d, total, blocks, s)); });
 }
 

@@ -134,8 +134,8 @@ hipError_t eri_scatter_batch_launch(const cplx* e, const long long* eoff, cplx* 
                                     int n, int maxnf, hipStream_t s);
 // NT GEMM on bf16 operands with the 32x32x16 matrix cores (128 x 128 tiles,
 // direct-to-LDS operand copies): F = 2 the hi+lo format (bf16x3), F = 3 single
-// bf16; plan with x3_plan.  Kind 2 without conjugation (U^q, at X3_SMALL only)
-// and kind 3 with B conjugated (the contraction).  Tiles [t0, t0 + nt), K segments
+// bf16; plan with x3_plan.  Kind 2 without conjugation (U^q, at X3_SMALL, and at
+// X3_TILE in F = 2 without ring) and kind 3 with B conjugated (the contraction).  Tiles [t0, t0 + nt), K segments
 // [seg0, seg0 + nseg); part: null (nseg = 1: epi 1 accumulates the FP32
 // partial sums of the segment in C, epi 3 stores the operand format), or room
 // for nt * nseg partial tiles (128 x 128 c128 each), as in nt_launch.
