@@ -168,9 +168,12 @@ def kernel_name(stage, prec):
     return KERNEL_OF_STAGE.get(stage, stage)
 
 
-# other kernels of a stage (the contraction of launches with few tiles)
-KERNEL_ALT = {("frag_eri", "bf16x3"): "zgemm_c2b_kernel<2>", ("frag_eri", "fp64"): "zgemm_nt_kernel<0, 32, 3>",
-              ("frag_eri", "fp32"): "zgemm_nt_kernel<1, 32, 3>"}
+# other kernels of a stage, and the launches that run them
+FEW_TILES, ROWS_APART = "launches of fewer tiles than two rounds", "pair rows 4 MB apart and further"
+KERNEL_ALT = {("frag_eri", "bf16x3"): ("zgemm_c2b_kernel<2>", FEW_TILES),
+              ("frag_eri", "fp64"): ("zgemm_nt_kernel<0, 32, 3>", FEW_TILES),
+              ("frag_eri", "fp32"): ("zgemm_nt_kernel<1, 32, 3>", FEW_TILES),
+              ("frag_u", "bf16x3"): ("zgemm_x3u_kernel", ROWS_APART)}
 
 
 def counter_traffic(stage, workload, prec):
@@ -189,7 +192,7 @@ def counter_traffic(stage, workload, prec):
         if not os.path.exists(fp) or hashlib.sha256(open(fp, "rb").read()).hexdigest() != h:
             return None
     # bytes per launch over every kernel of the stage, weighted by dispatches
-    keys = [kernel_name(stage, prec)] + ([KERNEL_ALT[(stage, prec)]] if (stage, prec) in KERNEL_ALT else [])
+    keys = [kernel_name(stage, prec)] + ([KERNEL_ALT[(stage, prec)][0]] if (stage, prec) in KERNEL_ALT else [])
     tot = n = 0
     for name, v in prof["kernels"].items():
         if any(k in name for k in keys):
@@ -322,7 +325,7 @@ def roofline_entry(ctx, stage_tot, cfg, nfs, prec, steps):
     if roof["kernel"].count("<") > roof["kernel"].count(">"):   # a prefix of the profiler's name
         roof["kernel"] += ">"
     if (dom, prec) in KERNEL_ALT:
-        roof["kernel"] += " (" + KERNEL_ALT[(dom, prec)] + " for launches of fewer tiles than two rounds)"
+        roof["kernel"] += " (%s for %s)" % KERNEL_ALT[(dom, prec)]
     roof["avg_launch_ms"] = avg_ms
     roof["launches_per_step"] = kn / steps
     roof["algorithmic_per_launch"] = amount / kn * (1e9 if unit == "GB" else 1e12)
@@ -434,12 +437,20 @@ def hf_leg(ctx, cfg, d, inp, np, torch, reps, oracle):
     return out
 
 
+def select_bytes(cfg):
+    """The fewest bytes isdf_select_points moves for all N_IP points: a pass
+    over the orbitals forms the columns of up to eight points above 20 MiB of
+    orbitals, else of one; a step reads the earlier factor columns once."""
+    n, orb = cfg.n_ip, cfg.n_k * cfg.n_orb * cfg.n_g * 16.0
+    passes = -(-n // 8) if orb > 20 << 20 else n
+    return passes * orb + cfg.n_g * 8.0 * (n * (n - 1) / 2 + 3 * n)
+
+
 def select_leg(cfg, d, pkg, np, torch, oracle):
     """Interpolation points by pivoted Cholesky (isdf_select_points) on the
-    cell's device-resident orbitals, all N_IP points, timed once; the step's
-    algorithmic bytes (read the orbitals once, the earlier factor columns at
-    their values once) against HBM; with `oracle`, two oracle steps on the
-    host scaled to N_IP steps."""
+    cell's device-resident orbitals, all N_IP points, timed once; its fewest
+    bytes against HBM; with `oracle`, two oracle steps on the host scaled to
+    N_IP steps."""
     orb = torch.from_numpy(d.orbitals).cuda()
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -447,9 +458,7 @@ def select_leg(cfg, d, pkg, np, torch, oracle):
     t = time.perf_counter() - t0
     del orb
     torch.cuda.empty_cache()
-    nrows = cfg.n_k * cfg.n_orb
-    n = cfg.n_ip
-    byts = n * nrows * cfg.n_g * 16.0 + cfg.n_g * 8.0 * (n * (n - 1) / 2 + 3 * n)
+    n, byts = cfg.n_ip, select_bytes(cfg)
     out = {"s": t, "points": n, "ms_per_step": 1e3 * t / n, "bytes": byts, "GBps": byts / t / 1e9,
            "frac_of_8TBps": byts / t / 8e12, "residual_first_last": [float(res[0]), float(res[-1])]}
     if oracle:
