@@ -152,7 +152,9 @@ isdf_status isdf_create(isdf_ctx* out, const double* lattice, const int32_t grid
  *              its decay measures how well the first i points span the pair
  *              products).
  *   hip_stream  stream of the launches (0 = null stream).
- * Synchronous; device workspace n_ip N_g 8 bytes plus a few tens of
+ * Synchronous; device workspace n_ip N_g 8 bytes, the partial sums of the
+ * columns that a pass forms (at most 64 MiB + 128 N_g bytes; 8 MiB + 16 N_g
+ * bytes where those do not fit or the orbitals take 20 MiB or less) and a few
  * grid-sized vectors (and a copy of host orbitals), freed on return.  Errors
  * (message from isdf_last_error(NULL)): ISDF_E_INVALID for bad sizes or
  * pointers; ISDF_E_NUMERIC when a step's largest residual is not positive
