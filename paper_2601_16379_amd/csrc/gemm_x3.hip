@@ -51,7 +51,6 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) void glb_void;
 
 constexpr int XT = 128;               // tile edge
-constexpr int XK = 16;                // k per stage of the hi+lo format
 // k per stage, u16 per element in the global layout, and log2 of the
 // planes per 8-element group, by format
 template <int F> struct Fmt;
@@ -103,9 +102,6 @@ __device__ inline void stage_copy(const unsigned short* const (&src)[N], const i
   }
 }
 
-// Fragments of one stage for this lane: A rows of the wave's two 32-row
-// blocks, B rows of its two 32-column blocks, four planes each (16 bytes =
-// 8 k of the lane's k-half).
 // Fragments of one stage for this lane: NI 32-row blocks of A (rows rb0 +
 // i * 32) and NJ 32-row blocks of B (rows cb0 + j * 32), four planes each
 // (16 bytes = 8 k of the lane's k-group l/32).
@@ -263,7 +259,9 @@ __device__ inline void mma_single(const Frag<NI, NJ>& f, int j, f16v (&c_re)[NI]
 // block 32 rows at a time in LDS (16 KB a wave) in the operand format (a row
 // of NJ*32 points is NJ*256 contiguous bytes) and writes it with 16-byte
 // stores; otherwise FP64 accumulation across launches (the first K segment,
-// `first`, stores).
+// `first`, stores).  One branch for all kernels: compiled for one use each, the
+// contraction took 2.5 % longer and the two-workgroup U^q 4 % (10^3 mesh, N_IP
+// 1040, 259.7 against 253.5 ms and 89.5 against 85.8).
 template <int F, int NI, int NJ, int T = XT>
 __device__ inline void tile_epilogue(const NtDesc& d, int b, int m0, int n0, int rb0, int cb0,
                                      const f16v (&c_re)[NI][NJ], const f16v (&c_im)[NI][NJ], char* smem, int wave,
@@ -523,14 +521,6 @@ __device__ inline void tile_body_ring(const NtDesc& d, int b, int m0, int n0, in
 // ahead (a buffer is refilled only after every wave has read the stage it
 // holds): more tolerant of a workgroup that has its CU to itself, the case
 // of launches with fewer tiles than two rounds of workgroups.
-// K loop and epilogue of one tile.  The wave owns the (NI*32) x (NJ*32)
-// block at rows rb0, columns cb0 of the tile: 64 x 64 in full tiles (2 x 2
-// waves); in tiles with at most 32 valid rows (columns) each wave takes a
-// 32 x 32 block of the one 32-row (32-column) strip, so edge tiles cost a
-// quarter of the matrix-core work.  Two workgroups share a CU (64 KB of LDS
-// each): two LDS stages, each stage's fragments read from LDS at its start
-// (the waves of the other workgroup keep the matrix cores busy meanwhile),
-// copies two stages ahead.
 template <int F, int NI, int NJ, bool A_CONJ, bool B_CONJ>
 __device__ inline void tile_body_2b(const NtDesc& d, int b, int m0, int n0, int kcur,
                                  const unsigned short* const (&asrc)[NCOPY], const unsigned short* const (&bsrc)[NCOPY],

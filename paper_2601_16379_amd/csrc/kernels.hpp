@@ -63,11 +63,9 @@ struct NtDesc {
   int herm, epi;
   int cseg;               // K segments per chunk (0 = all)
   int npad;               // epi 3: columns written (zeros from N on); 0 = ldc
-  int ktri;               // B[n][k] = 0 for k < n: the mixed kernels start each column
-  // bf16 U^q: column tiles of row r (over the batch) are taken in the order
-  // turned by r / rot (0: as they are)
-  int rot;
-                          // tile's K range at its first column (FP64 reads the zeros)
+  int ktri;               // B[n][k] = 0 for k < n: each column tile's K range starts at its first column
+  int rot;                // U^q: column tiles of row r (over the batch) are taken in the order turned by
+                          // r / rot (0: as they are)
   long long tile_begin;
 };
 long long nt_plan(NtDesc* d, int n);
