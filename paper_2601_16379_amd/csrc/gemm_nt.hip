@@ -14,7 +14,7 @@
 // bf16 formats have their own kernel in gemm_x3.hip.)
 //
 // Bound: the matrix cores; in FP64 (64 cycles a 16x16x4 MFMA) in practice the
-// power they draw: with the cores busy 0.84 of the cycles the clock falls
+// power they draw: with the cores busy 0.80 of the cycles the clock falls
 // from 2.4 to 2.0-2.25 GHz.  A workgroup of 256 threads takes a 64 x 64 tile
 // (four waves of 2 x 2 blocks of 16 x 16), two workgroups a CU.  A stage of
 // both operands (2 x 16 KB) is copied from global memory straight into LDS

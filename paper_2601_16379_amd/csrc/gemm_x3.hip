@@ -852,13 +852,15 @@ __device__ inline void u_body(UFlow<F>& f, const NtDesc& d, int nt, const UTile&
   }
 }
 
-// Bound: the matrix cores and what one wave a SIMD cannot lay beside them (0.41
-// busy at 1000 k; the rest outputs, 17 operations a value, and the steps between
-// stages).  Whole tiles one after the other with two workgroups a CU, outputs
-// staged through LDS and every tile's first stages waited for -> now: bf16x3
-// 47.5 k pairs on 4x4x4 (N_IP 520) 6.8 -> 6.5 ms; single bf16 at 216 k (N_IP 520) 5.9 ->
-// 4.8 ms; 1000 k (N_IP 416) 10.0 ms both.  Two workgroups a CU with two stages
-// each measured 7.6, 6.6 and 10.7 ms.
+// Bound: the matrix cores and what one wave a SIMD cannot lay beside them (busy
+// 0.50 of the cycles in bf16x3 and 0.38 in single bf16 at 216 k, N_IP 800; the
+// rest outputs, 17 operations a value, and the steps between stages).  Whole tiles
+// one after the other with two workgroups a CU, outputs staged through LDS and
+// every tile's first stages waited for -> now: bf16x3 47.5 k pairs on 4x4x4 (N_IP
+// 520) 6.8 -> 6.5 ms; single bf16 at 216 k (N_IP 520) 5.9 -> 4.8 ms; 1000 k (N_IP
+// 416) 10.0 ms both; bf16x3 rows 4 MB apart are slower and keep the former loop
+// (run_u16).  Two workgroups a CU with two stages each measured 7.6, 6.6 and 10.7
+// ms.
 template <int F>
 __global__ __launch_bounds__(XNT, 1) void zgemm_u16_kernel(NtDesc d, int nt) {
   extern __shared__ __attribute__((aligned(16))) char smem[];   // UR stages x (A, B)

@@ -852,8 +852,8 @@ template <int R> __device__ inline void dft_last_f(const float2 (&x)[R], float2 
 // neighbours in that order): half tiles, whose LDS lets two workgroups
 // share a CU, still read and write whole cache lines between two
 // workgroups that run together.
-// Bound: the vector units (about 0.9 busy on the 6^3 mesh with the addresses
-// formed per value; FP32 operations take 4 cycles a wave).  So addresses are a
+// Bound: the vector units (216 k, N_IP 800: an operation issued in 0.2 of a
+// SIMD's cycles, each of 4 cycles, so about 0.8 busy).  So addresses are a
 // uniform base and one 32-bit offset a line, output blocks a table of offsets
 // in LDS, outputs of axis-1 index above M1 / 2 (never stored: their -q comes
 // first) are passed over, and quads store whole parts: 5.50 -> 3.93 ms at 216 k
