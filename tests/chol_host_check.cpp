@@ -44,7 +44,7 @@ class Barrier {
       cv_.notify_all();
       return;
     }
-    if (!cv_.wait_for(lk, std::chrono::seconds(3), [&] { return gen_ != gen; })) throw Hang{};
+    if (!cv_.wait_for(lk, std::chrono::seconds(20), [&] { return gen_ != gen; })) throw Hang{};
   }
 
  private:
